@@ -29,33 +29,33 @@ def listed():
         # the whole solver on the smallest configuration: constant c, point source, 8 poles,
         # degree 8, FP64, to 1e-8
         {"name": "solve_f64_32", "kind": "solve", "n": 32, "ppw": 10.0, "J": 8, "eps": 0.5, "q": 8, "tol": 1e-8},
-        # the shifted solves of the plain FP64 method: 96^3 random medium, 12 poles, 4 sources,
-        # as the operator is created (no launch shape set)
+        # the shifted solves of the plain FP64 method: 96^3 random medium, 12 poles, 4 sources
+        # ("tune": the systems that the launch-shape tuner times, as programs that solve often
+        # have it do once per operator; 0: the operator as it is created)
         {"name": "shifted_f64_96", "kind": "shifted", "form": "fd", "nz": 96, "ny": 96, "nx": 96, "prec": 64,
-         "nrhs": 4, "ppw": 10.0, "medium": "grf", "rhs": "gauss", "J": 12, "eps": 0.25, "q": 8, "shape": ""},
+         "nrhs": 4, "ppw": 10.0, "medium": "grf", "rhs": "gauss", "J": 12, "eps": 0.25, "q": 8, "tune": 2},
         # the same problem in mixed precision, with the contour that the library's rule chooses
         # (eps 0.01, degree 10)
         {"name": "shifted_f32_96", "kind": "shifted", "form": "fd", "nz": 96, "ny": 96, "nx": 96, "prec": 32,
-         "nrhs": 4, "ppw": 10.0, "medium": "grf", "rhs": "gauss", "J": 12, "eps": 0.01, "q": 10, "shape": ""},
+         "nrhs": 4, "ppw": 10.0, "medium": "grf", "rhs": "gauss", "J": 12, "eps": 0.01, "q": 10, "tune": 0},
         # the dominant work of the benchmark solve: 256^3 layered medium, 16 poles, point sources,
-        # FP32 sweeps, the launch shape that the tuner takes there
+        # FP32 sweeps
         {"name": "shifted_f32_256", "kind": "shifted", "form": "fd", "nz": 256, "ny": 256, "nx": 256, "prec": 32,
-         "nrhs": 4, "ppw": 8.0, "medium": "layered", "rhs": "point", "J": 16, "eps": 0.01, "q": 10,
-         "shape": "3,8,2,64,2,4"},
+         "nrhs": 4, "ppw": 8.0, "medium": "layered", "rhs": "point", "J": 16, "eps": 0.01, "q": 10, "tune": 8},
         # one application of the preconditioner in plain FP64 (the benchmark's FP64 arm), on a grid
-        # whose sides differ, pairs of factors per pass
+        # whose sides differ
         {"name": "fci_f64_128", "kind": "fci", "nz": 112, "ny": 128, "nx": 144, "nrhs": 2, "ppw": 8.0,
-         "medium": "layered", "rhs": "gauss", "J": 6, "eps": 0.04, "q": 10, "shape": "1,8,2,16,1,1"},
+         "medium": "layered", "rhs": "gauss", "J": 6, "eps": 0.04, "q": 10, "tune": 4},
         # independent operators of different sizes in one call, FP32
         {"name": "batch_f32", "kind": "batch", "count": 8, "lo": 48, "hi": 128, "prec": 32, "J": 8, "eps": 0.02,
          "q": 10},
         # the double-size formulation of the same shifted solves
         {"name": "two_f32_128", "kind": "shifted", "form": "two", "nz": 128, "ny": 128, "nx": 128, "prec": 32,
-         "nrhs": 1, "ppw": 8.0, "medium": "layered", "rhs": "point", "J": 16, "eps": 0.02, "q": 8, "shape": ""},
+         "nrhs": 1, "ppw": 8.0, "medium": "layered", "rhs": "point", "J": 16, "eps": 0.02, "q": 8, "tune": 0},
         # the Fourier-spectral operator at its sampling of 2.25 points per wavelength
         {"name": "spectral_f32_128", "kind": "shifted", "form": "spectral", "nz": 128, "ny": 128, "nx": 128,
          "prec": 32, "nrhs": 1, "ppw": 2.25, "medium": "layered", "rhs": "point", "J": 16, "eps": 0.25, "q": 5,
-         "shape": ""},
+         "tune": 0},
         # the learned preconditioner's network on a full grid, as one inner step evaluates it
         {"name": "net_eval_256", "kind": "net_eval", "nz": 256, "ny": 256, "nx": 256},
         # loss and gradients of one training crop with the residual loss
@@ -88,20 +88,16 @@ def draw(rng):
         d = [_side(rng, 24, top) for _ in range(3)]
         J = 2 * rng.randint(2, 8)
         nrhs = rng.randint(1, max(1, min(8, int(2.4e8 / (J * d[0] * d[1] * d[2])))))
-        shape = ""
-        if form == "fd" and rng.random() < 0.6:
-            shape = rng.choice(("3,8,2,64,2,4", "3,8,2,16,2,1", "2,8,2,0,1,2")) if prec == 32 else \
-                rng.choice(("1,8,2,16,1,1", "1,8,2,64,1,2"))
         return {"kind": kind, "form": form, "nz": d[0], "ny": d[1], "nx": d[2], "prec": prec, "nrhs": nrhs,
                 "ppw": rng.uniform(2.25, 4.0) if form == "spectral" else rng.uniform(6.0, 12.0), "medium": medium,
                 "rhs": rng.choice(("point", "gauss")), "J": J, "eps": math.exp(rng.uniform(math.log(0.02), math.log(0.5))),
-                "q": rng.choice((5, 8, 8, 10, 10, 12)), "shape": shape}
+                "q": rng.choice((5, 8, 8, 10, 10, 12)), "tune": rng.choice((0, 2, 8)) if form == "fd" else 0}
     if kind == "fci":
         d = [_side(rng, 24, 144) for _ in range(3)]
         return {"kind": kind, "nz": d[0], "ny": d[1], "nx": d[2], "nrhs": rng.randint(1, 3), "ppw": rng.uniform(6.0, 12.0),
                 "medium": medium, "rhs": rng.choice(("point", "gauss")), "J": 2 * rng.randint(2, 6),
                 "eps": math.exp(rng.uniform(math.log(0.05), math.log(0.5))), "q": rng.choice((7, 8, 10)),
-                "shape": rng.choice(("", "1,8,2,16,1,1"))}
+                "tune": rng.choice((0, 2))}
     if kind == "batch":
         lo = rng.choice((24, 32, 48))
         return {"kind": kind, "count": rng.randint(2, 10), "lo": lo, "hi": rng.randint(64, 120), "prec": rng.choice((32, 32, 64)),
@@ -246,8 +242,8 @@ def _operator(case, shape, seed):
     p = _parts(case, shape, seed)
     cls = hfci.SpectralOperator if p["form"] == "spectral" else hfci.Operator
     op = cls(_context(), p["c"], p["h"], p["omega"], p["cells"], RHO2)
-    if case.get("shape"):
-        op.set_tune(case.get("prec", 64), *[int(v) for v in case["shape"].split(",")])
+    if case.get("tune"):
+        op.autotune(case.get("prec", 64), case["tune"])
     base = op
     if p["form"] == "two":
         op = base.case_two()
