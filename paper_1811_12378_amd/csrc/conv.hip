@@ -289,97 +289,134 @@ __global__ __launch_bounds__(256) void zconv48_kernel(Dims d, View in, const uin
   }
 }
 
-// Weight gradient partials for one tap: P[chunk][tap][co][ci] = sum over the chunk's voxels
-// of dz[v][co] * x[v + off_tap][ci].  GEMM with k = voxel (16 voxels per MFMA step);
-// the 16 k-values of a lane are gathered (4 per lane) from channels-last memory.
-template <int CT_OUT, int CT_IN>
-__global__ __launch_bounds__(256) void conv_wgrad_kernel(Dims d, View x, View dz, int chunk, float* __restrict__ part) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tap = blockIdx.y;
-  const int dzz = tap / 9 - 1, dyy = (tap / 3) % 3 - 1, dxx = tap % 3 - 1;
-  const long nvox = (long)d.x * d.y * d.z;
-  const long vb = (long)blockIdx.x * chunk;
-  const long ve = vb + chunk < nvox ? vb + chunk : nvox;
+// Weight and bias gradient of one layer: dw[tap][co][ci] = sum over voxels of dz[v][co] *
+// x[v + off_tap][ci] and db[co] = sum of dz[v][co], as per-block partial sums.
+// A GEMM whose k index runs over voxels, so both operands are needed with the voxels of a
+// channel side by side while memory is channels-last.  A block stages a 32 x 4 x tz voxel
+// tile of dz and the same tile of 16 input channels with its halo in LDS, transposed to
+// [channel][row][x] (two x-neighbours packed per 4-byte write), and its nine waves take one
+// (dz, dy) pair of taps each: per row of 32 voxels one 16x16x32 MFMA per tap and 16 output
+// channels, the taps dx = -1, 0, 1 from one set of LDS reads shifted by 16 bits in registers.
+// So memory is read about once per 16 input channels (the halo comes from L2), and the
+// accumulators stay in registers over all tiles of a block.  Rows are 48 values (x at 8, so
+// that 16-byte reads are aligned), a channel's rows are padded to an odd multiple of 64 bytes
+// (the 16 channels of a read then spread over the banks).
+// What it replaces (2-byte gathers per lane and tap from channels-last memory, one tap per
+// block) took 994 us for a 16 -> 16 layer on 64^3 voxels and 1321 us for the 48 -> 16 one,
+// plus 90 us per layer for the bias sums.
+constexpr int WGX = 32, WGY = 4, WGZ = 4;            // voxel tile
+constexpr int WGR = (WGY + 2) * (WGZ + 2);           // rows of the input tile with halo
+constexpr int WGXP = 48, WGX0 = 8;                   // values per input row, position of x = 0
+constexpr int WGXS = WGR * WGXP + 32;                // values per input channel (3520 bytes)
+constexpr int WGDS = WGY * WGZ * WGX + 32;           // values per dz channel (1088 bytes)
+constexpr int WGNT = 9 * 64;
+static_assert((WGXS * 2 / 64) % 2 == 1 && (WGDS * 2 / 64) % 2 == 1, "channel strides spread over the banks");
+
+template <int CT>
+__global__ __launch_bounds__(WGNT) void conv_wgrad_kernel(Dims d, View x, View dz, int cin, int tz, int ntiles,
+                                                          float* __restrict__ part, float* __restrict__ bpart) {
+  __shared__ __align__(16) uint16_t xs[16 * WGXS];
+  __shared__ __align__(16) uint16_t ds[CT * 16 * WGDS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = lane & 15, kq = lane >> 4;
-  constexpr int NT = CT_OUT * CT_IN;  // output tiles, distributed over the 4 waves
-  constexpr int PER = (NT + 3) / 4;
-  f4v acc[PER];
+  const int ci0 = blockIdx.y * 16;
+  const int tx = (d.x + WGX - 1) / WGX, ty = (d.y + WGY - 1) / WGY;
+  const int tdz = wave / 3, tdy = wave % 3;  // this wave's taps: offsets (tdz - 1, tdy - 1, *)
+  f4v acc[3][CT], bacc[CT];
 #pragma unroll
-  for (int i = 0; i < PER; ++i) acc[i] = f4v{0.f, 0.f, 0.f, 0.f};
-  for (long k0 = vb; k0 < ve; k0 += 16) {
-    // this lane's 4 voxels of the k-block
-    s4v bfr[CT_IN];
-    s4v afr[CT_OUT];
-    long vv[4];
-    long vin[4];
-    bool okv[4], okin[4];
+  for (int t = 0; t < CT; ++t) {
+    bacc[t] = f4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      vv[r] = k0 + kq * 4 + r;
-      okv[r] = vv[r] < ve;
-      const Coord c = coord_of(okv[r] ? vv[r] : 0, d);
-      const int zz = c.z + dzz, yy = c.y + dyy, xx = c.x + dxx;
-      okin[r] = okv[r] && zz >= 0 && zz < d.z && yy >= 0 && yy < d.y && xx >= 0 && xx < d.x;
-      vin[r] = okin[r] ? ((long)zz * d.y + yy) * d.x + xx : 0;
+    for (int i = 0; i < 3; ++i) acc[i][t] = f4v{0.f, 0.f, 0.f, 0.f};
+  }
+  // eight channels of voxels (xg, xg + 1) of a view into eight rows' 4-byte words, zeros
+  // outside the grid
+  auto stage = [&](const View& v, int c0, int zg, int yg, int xg, uint16_t* dst, int stride) {
+    uint4 a = make_uint4(0, 0, 0, 0), b = a;
+    if (zg >= 0 && zg < d.z && yg >= 0 && yg < d.y) {
+      const uint16_t* p = v.p + (((long)zg * d.y + yg) * d.x + xg) * v.cs + v.off + c0;
+      if (xg >= 0 && xg < d.x) a = *reinterpret_cast<const uint4*>(p);
+      if (xg + 1 >= 0 && xg + 1 < d.x) b = *reinterpret_cast<const uint4*>(p + v.cs);
     }
+    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
 #pragma unroll
-    for (int t = 0; t < CT_OUT; ++t)
+    for (int k = 0; k < 4; ++k) {
+      *reinterpret_cast<uint32_t*>(dst + (2 * k) * stride) = __builtin_amdgcn_perm(bw[k], aw[k], 0x05040100u);
+      *reinterpret_cast<uint32_t*>(dst + (2 * k + 1) * stride) = __builtin_amdgcn_perm(bw[k], aw[k], 0x07060302u);
+    }
+  };
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const int x0 = (tile % tx) * WGX, y0 = (tile / tx) % ty * WGY, z0 = tile / (tx * ty) * tz;
+    // input: rows (lz, ly) of the tile with halo, voxel pairs at x0 - 2 + 2 i for i < 18
+    for (int i = tid; i < 2 * (tz + 2) * (WGY + 2) * 18; i += WGNT) {
+      const int pr = i % 18, r = i / 18 % ((tz + 2) * (WGY + 2)), half = i / (18 * (tz + 2) * (WGY + 2));
+      stage(x, ci0 + half * 8, z0 - 1 + r / (WGY + 2), y0 - 1 + r % (WGY + 2), x0 - 2 + 2 * pr,
+            xs + half * 8 * WGXS + r * WGXP + WGX0 - 2 + 2 * pr, WGXS);
+    }
+    for (int i = tid; i < CT * 2 * tz * WGY * 16; i += WGNT) {
+      const int pr = i % 16, r = i / 16 % (tz * WGY), oct = i / (16 * tz * WGY);
+      const int zg = z0 + r / WGY;
+      stage(dz, oct * 8, zg, y0 + r % WGY, x0 + 2 * pr, ds + oct * 8 * WGDS + r * WGX + 2 * pr, WGDS);
+    }
+    __syncthreads();
+    for (int r = 0; r < tz * WGY; ++r) {
+      const uint16_t* xp = xs + row * WGXS + ((r / WGY + tdz) * (WGY + 2) + r % WGY + tdy) * WGXP + WGX0 + 8 * kq;
+      const uint4 c = *reinterpret_cast<const uint4*>(xp);
+      const uint32_t lo = *reinterpret_cast<const uint32_t*>(xp - 2), hi = *reinterpret_cast<const uint32_t*>(xp + 8);
+      const uint32_t s1 = __builtin_amdgcn_alignbit(c.y, c.x, 16), s2 = __builtin_amdgcn_alignbit(c.z, c.y, 16),
+                     s3 = __builtin_amdgcn_alignbit(c.w, c.z, 16);
+      const b8v bm = __builtin_bit_cast(b8v, make_uint4(__builtin_amdgcn_alignbit(c.x, lo, 16), s1, s2, s3));
+      const b8v b0 = __builtin_bit_cast(b8v, c);
+      const b8v bp = __builtin_bit_cast(b8v, make_uint4(s1, s2, s3, __builtin_amdgcn_alignbit(hi, c.w, 16)));
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        afr[t][r] = okv[r] ? (short)dz.p[vv[r] * dz.cs + dz.off + t * 16 + row] : (short)0;
-#pragma unroll
-    for (int t = 0; t < CT_IN; ++t)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        bfr[t][r] = okin[r] ? (short)x.p[vin[r] * x.cs + x.off + t * 16 + row] : (short)0;
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int tile = wave + 4 * i;
-      if (tile < NT) {
-        const int to = tile / CT_IN, ti = tile % CT_IN;
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(afr[to], bfr[ti], acc[i], 0, 0, 0);
+      for (int t = 0; t < CT; ++t) {
+        const b8v a = Frag<8>::load(ds + (t * 16 + row) * WGDS + r * WGX + 8 * kq);
+        acc[0][t] = Frag<8>::mma(a, bm, acc[0][t]);
+        acc[1][t] = Frag<8>::mma(a, b0, acc[1][t]);
+        acc[2][t] = Frag<8>::mma(a, bp, acc[2][t]);
+        if (wave == 4 && ci0 == 0) {  // the centre pair's wave also sums dz (a product with ones)
+          const uint32_t one = 0x3f803f80u;
+          bacc[t] = Frag<8>::mma(a, __builtin_bit_cast(b8v, make_uint4(one, one, one, one)), bacc[t]);
+        }
       }
     }
+    __syncthreads();
   }
-  const int cout = CT_OUT * 16, cin = CT_IN * 16;
-  float* out = part + ((size_t)blockIdx.x * 27 + tap) * cout * cin;
+  // accumulator: rows (output channels) 4 kq + r, column (input channel) row
+  const int cout = CT * 16;
+  float* out = part + (size_t)blockIdx.x * 27 * cout * cin;
 #pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    const int tile = wave + 4 * i;
-    if (tile < NT) {
-      const int to = tile / CT_IN, ti = tile % CT_IN;
+  for (int i = 0; i < 3; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) out[(size_t)(to * 16 + kq * 4 + r) * cin + ti * 16 + row] = acc[i][r];
-    }
-  }
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        out[((size_t)((tdz * 3 + tdy) * 3 + i) * cout + t * 16 + 4 * kq + r) * cin + ci0 + row] = acc[i][t][r];
+  if (wave == 4 && ci0 == 0 && row == 0)
+#pragma unroll
+    for (int t = 0; t < CT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bpart[(size_t)blockIdx.x * cout + t * 16 + 4 * kq + r] = bacc[t][r];
 }
 
-// sum over chunks, fixed order: out[i] = sum_c part[c][i]  (optionally += into out)
-__global__ void sum_chunks_kernel(const float* __restrict__ part, int nchunk, long len, float* __restrict__ out,
-                                  int accumulate) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= len) return;
-  float s = accumulate ? out[i] : 0.f;
-  for (int c = 0; c < nchunk; ++c) s += part[(size_t)c * len + i];
-  out[i] = s;
-}
-
-// per-channel sums over voxels (bias gradient): partials per block, then sum_chunks
-__global__ __launch_bounds__(256) void chan_sum_kernel(View g, int C, long nvox, int per_block, float* __restrict__ part) {
-  const long vb = (long)blockIdx.x * per_block;
-  const long ve = vb + per_block < nvox ? vb + per_block : nvox;
-  __shared__ float sh[256];
-  for (int c = 0; c < C; ++c) {
-    float s = 0.f;
-    for (long v = vb + threadIdx.x; v < ve; v += 256) s += bf2f(g.p[v * g.cs + g.off + c]);
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) part[(size_t)blockIdx.x * C + c] = sh[0];
-    __syncthreads();
+// sum over chunks, fixed order: out[i] = sum_c part[c][i].  A block
+// takes 64 values; 16 waves sum every 16th chunk each, then the 16 sums in order (one thread
+// per value over all chunks left most of the chip idle: 22 us per layer on 64^3 voxels).
+__global__ __launch_bounds__(1024) void sum_chunks_kernel(const float* __restrict__ part, int nchunk, long len,
+                                                          float* __restrict__ out) {
+  __shared__ float sh[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long i = (long)blockIdx.x * 64 + lane;
+  float s = 0.f;
+  if (i < len)
+    for (int c = wave; c < nchunk; c += 16) s += part[(size_t)c * len + i];
+  sh[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < len) {
+    s = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) s += sh[w][lane];
+    out[i] = s;
   }
 }
 
@@ -536,6 +573,10 @@ __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, 
 
 unsigned blocks_for(long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
+void launch_sum_chunks(hipStream_t s, const float* part, int nchunk, long len, float* out) {
+  hipLaunchKernelGGL(sum_chunks_kernel, dim3(blocks_for(len, 64)), dim3(1024), 0, s, part, nchunk, len, out);
+}
+
 template <int KB>
 void fwd_dispatch(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, const float* bias, int relu, View out,
                   int cout) {
@@ -551,17 +592,22 @@ void fwd_dispatch(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, co
   }
 }
 
-template <int CO>
-void wgrad_dispatch_in(hipStream_t s, Dims d, View x, View dz, int cin, int chunk, unsigned nch, float* part) {
-  const dim3 g(nch, 27);
-  switch (cin / 16) {
-    case 1: hipLaunchKernelGGL((conv_wgrad_kernel<CO, 1>), g, dim3(256), 0, s, d, x, dz, chunk, part); break;
-    case 2: hipLaunchKernelGGL((conv_wgrad_kernel<CO, 2>), g, dim3(256), 0, s, d, x, dz, chunk, part); break;
-    case 3: hipLaunchKernelGGL((conv_wgrad_kernel<CO, 3>), g, dim3(256), 0, s, d, x, dz, chunk, part); break;
-    case 4: hipLaunchKernelGGL((conv_wgrad_kernel<CO, 4>), g, dim3(256), 0, s, d, x, dz, chunk, part); break;
-    case 6: hipLaunchKernelGGL((conv_wgrad_kernel<CO, 6>), g, dim3(256), 0, s, d, x, dz, chunk, part); break;
-    default: break;
-  }
+// tile depth and blocks per 16 input channels of the weight gradient: tiles of four planes,
+// fewer where that leaves the chip idle (one plane on the coarsest grids), and blocks enough
+// for about one and a half per CU, each summing several tiles (a block's partial sums are
+// 27 x cout x 16 values: more blocks cost more in the final sum than they gain)
+struct WgradPlan {
+  int tz, ntiles, nblk;
+};
+WgradPlan wgrad_plan(Dims d, int cin) {
+  WgradPlan p;
+  const long txy = (long)((d.x + WGX - 1) / WGX) * ((d.y + WGY - 1) / WGY);
+  p.tz = WGZ;
+  while (p.tz > 1 && txy * ((d.z + p.tz - 1) / p.tz) * (cin / 16) < 256) p.tz /= 2;
+  p.ntiles = (int)(txy * ((d.z + p.tz - 1) / p.tz));
+  const int want = (384 + cin / 16 - 1) / (cin / 16);
+  p.nblk = p.ntiles < want ? p.ntiles : want;
+  return p;
 }
 
 }  // namespace
@@ -598,44 +644,22 @@ void launch_conv_fwd(hipStream_t s, Dims d, View in, int cin, const uint16_t* w,
     fwd_dispatch<4>(s, d, in, cin, w, bias, relu ? 1 : 0, out, cout);
 }
 
-int wgrad_chunk() { return 2048; }
-
-void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw,
-                       bool accumulate) {
-  const long nvox = (long)d.x * d.y * d.z;
-  const int chunk = wgrad_chunk();
-  const unsigned nch = (unsigned)((nvox + chunk - 1) / chunk);
+void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db) {
+  const WgradPlan p = wgrad_plan(d, cin);
+  const dim3 g(p.nblk, cin / 16);
+  float* bpart = part + (size_t)p.nblk * 27 * cout * cin;
   switch (cout / 16) {
-    case 1: wgrad_dispatch_in<1>(s, d, x, dz, cin, chunk, nch, part); break;
-    case 2: wgrad_dispatch_in<2>(s, d, x, dz, cin, chunk, nch, part); break;
-    case 3: wgrad_dispatch_in<3>(s, d, x, dz, cin, chunk, nch, part); break;
-    case 4: wgrad_dispatch_in<4>(s, d, x, dz, cin, chunk, nch, part); break;
-    case 6: wgrad_dispatch_in<6>(s, d, x, dz, cin, chunk, nch, part); break;
+    case 1: hipLaunchKernelGGL((conv_wgrad_kernel<1>), g, dim3(WGNT), 0, s, d, x, dz, cin, p.tz, p.ntiles, part, bpart); break;
+    case 2: hipLaunchKernelGGL((conv_wgrad_kernel<2>), g, dim3(WGNT), 0, s, d, x, dz, cin, p.tz, p.ntiles, part, bpart); break;
+    case 4: hipLaunchKernelGGL((conv_wgrad_kernel<4>), g, dim3(WGNT), 0, s, d, x, dz, cin, p.tz, p.ntiles, part, bpart); break;
     default: break;
   }
-  const long len = 27L * cout * cin;
-  hipLaunchKernelGGL(sum_chunks_kernel, dim3(blocks_for(len)), dim3(256), 0, s, part, (int)nch, len, dw,
-                     accumulate ? 1 : 0);
+  launch_sum_chunks(s, part, p.nblk, 27L * cout * cin, dw);
+  launch_sum_chunks(s, bpart, p.nblk, cout, db);
 }
 
 long wgrad_part_floats(Dims d, int cin, int cout) {
-  const long nvox = (long)d.x * d.y * d.z;
-  const long nch = (nvox + wgrad_chunk() - 1) / wgrad_chunk();
-  return nch * 27L * cin * cout;
-}
-
-long bias_part_floats(Dims d, int C) {
-  const long nvox = (long)d.x * d.y * d.z;
-  return ((nvox + 4095) / 4096) * C;
-}
-
-void launch_bias_grad(hipStream_t s, Dims d, View g, int C, float* part, float* db, bool accumulate) {
-  const long nvox = (long)d.x * d.y * d.z;
-  const int per = 4096;
-  const unsigned nb = (unsigned)((nvox + per - 1) / per);
-  hipLaunchKernelGGL(chan_sum_kernel, dim3(nb), dim3(256), 0, s, g, C, nvox, per, part);
-  hipLaunchKernelGGL(sum_chunks_kernel, dim3(blocks_for(C)), dim3(256), 0, s, part, (int)nb, (long)C, db,
-                     accumulate ? 1 : 0);
+  return (long)wgrad_plan(d, cin).nblk * (27L * cin * cout + cout);
 }
 
 void launch_flip_transpose(hipStream_t s, const uint16_t* w, int cout, int cin, uint16_t* wt) {
@@ -681,7 +705,7 @@ void launch_head_back(hipStream_t s, View h, long nvox, const float* W, const fl
                       float* dWb /* [34]: dW (32) then db (2) */) {
   const unsigned nb = blocks_for(nvox);
   hipLaunchKernelGGL(head_back_kernel, dim3(nb), dim3(256), 0, s, h, nvox, W, dout, dh, part);
-  hipLaunchKernelGGL(sum_chunks_kernel, dim3(1), dim3(256), 0, s, part, (int)nb, 34L, dWb, 0);
+  launch_sum_chunks(s, part, (int)nb, 34L, dWb);
 }
 
 void launch_adam(hipStream_t s, float* p, const float* g, float* m, float* v, long n, float lr, float b1, float b2,

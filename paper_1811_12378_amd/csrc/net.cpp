@@ -152,7 +152,6 @@ Net::Acts Net::acts(Dims d, bool backward) {
     for (int l = 0; l < kNL; ++l) {
       const Dims dl = (l < C2A || l >= D1A) ? a.d1 : ((l < C3A || l >= D2A) ? a.d2 : a.d3);
       part = std::max(part, wgrad_part_floats(dl, layers[l].cin, layers[l].cout));
-      part = std::max(part, bias_part_floats(dl, layers[l].cout));
     }
     a.part = (float*)ws.get("net_part", (size_t)part * sizeof(float));
   }
@@ -191,8 +190,7 @@ void Net::conv_back(const Acts& a, int l, Dims d, View in, View post, View dh, V
   const int ci = layers[l].cin, co = layers[l].cout;
   const View dz = V(a.gz, co);
   launch_relu_mask(s, dh, post, co, nv, dz);
-  launch_conv_wgrad(s, d, in, ci, dz, co, a.part, g + layers[l].w_off, false);
-  launch_bias_grad(s, d, dz, co, a.part, g + layers[l].b_off, false);
+  launch_conv_wgrad(s, d, in, ci, dz, co, a.part, g + layers[l].w_off, g + layers[l].b_off);
   if (din.p) launch_conv_fwd(s, d, dz, co, wt + layers[l].w_off, nullptr, false, din, ci);
 }
 

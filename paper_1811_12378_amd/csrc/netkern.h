@@ -21,10 +21,8 @@ bool conv_shape_ok(int cin, int cout);
 void launch_conv_fwd(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, const float* bias, bool relu,
                      View out, int cout);
 long wgrad_part_floats(Dims d, int cin, int cout);
-void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw,
-                       bool accumulate);
-long bias_part_floats(Dims d, int C);
-void launch_bias_grad(hipStream_t s, Dims d, View g, int C, float* part, float* db, bool accumulate);
+// weight gradient dw [27][cout][cin] and bias gradient db [cout] (part: wgrad_part_floats)
+void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db);
 void launch_flip_transpose(hipStream_t s, const uint16_t* w, int cout, int cin, uint16_t* wt);
 void launch_f32_to_bf16(hipStream_t s, const float* a, long n, uint16_t* b);
 void launch_relu_mask(hipStream_t s, View dh, View post, int C, long nvox, View dz);
