@@ -155,7 +155,7 @@ enum {
   HFCI_PROF_APPLY = 2,     /* hfci_apply                                           */
   HFCI_PROF_FP_LAST = 3,   /* last factor of a step (adds the constant term y1)    */
   HFCI_PROF_FP_INIT = 4,   /* first and last factor of step one (from f, to y1)    */
-  HFCI_PROF_FP_TRIPLE = 5, /* three middle factors in one pass (launch shape fuse 2)  */
+  HFCI_PROF_FP_TRIPLE = 5, /* three or four middle factors in one pass                 */
   HFCI_PROF_N = 6
 };
 
@@ -203,7 +203,7 @@ hfci_status hfci_op_info(const hfci_op* op, double* out7);
  *           ty = 8) = as 1 for the two-factor passes, but every plane of every stream
  *           is loaded from HBM straight into a ring of P + 2 LDS slots (P = 2 planes
  *           ahead for pd = 2, 4 for pd = 3) without passing through registers, so
- *           more planes are in flight; single factors, and two-factor passes on
+ *           more planes are in flight; single factors, and multi-factor passes on
  *           grids with an odd nx or vectors of 2 GiB or more, run as kern 1;
  *           3 (HFCI_F32 only, fuse = 1 or 2, ty = 8, pd = 2) = as 2, with the middle
  *           two-factor passes on 64 x 28 output tiles (the input halo and kappa then
@@ -213,8 +213,11 @@ hfci_status hfci_op_info(const hfci_op* op, double* out7);
  *   tune[2] pd:   HBM streams are issued pd planes ahead (kern 0: 1 or 2;
  *                 kern 1: 1..3 with ty = 4, 2..3 with ty = 8);
  *   tune[3] cz:   z-chunk length in planes (1..4096, or 0 = chosen from the grid);
- *   tune[4] fuse: 1 = the fixed-point factors run two per pass over HBM (temporal
- *                 blocking on 64 x 12 tiles with z-chunks cz), 0 = one per pass,
+ *   tune[4] fuse: 1 = the fixed-point factors run several per pass over HBM (temporal
+ *                 blocking): with kern 0 or 1, and where kerns 2 and 3 do not run, up to four
+ *                 (HFCI_F32) or three (HFCI_F64), planes in registers, tiles chosen from the
+ *                 grid and the systems still iterating, z-chunks cz; with kern 2 or 3 two, on
+ *                 64 x 12 tiles with z-chunks cz.  0 = one per pass,
  *                 2 (kern 3 only) = as 1, with the middle factors of a step (those
  *                 between its first and last pair: q - 4 of them, or of step one's
  *                 run of pairs) three per pass where they split into threes and at
@@ -225,14 +228,15 @@ hfci_status hfci_op_info(const hfci_op* op, double* out7);
  *                 tiles after another's).
  * Shapes change launch geometry only: every grid point gets the same arithmetic,
  * while reductions (residual norms, the step size d) sum their block partials in a
- * different order.  New operators start at {1, 8, 2, 0, 0, 1}.  Errors: HFCI_E_ARG. */
+ * different order.  New operators start at {1, 8, 2, 0, 0, 1}, with the fixed-point factors
+ * several per pass as for fuse 1 until a shape is set or tuned.  Errors: HFCI_E_ARG. */
 hfci_status hfci_op_set_tune(hfci_op* op, int prec, const int* tune6);
 hfci_status hfci_op_get_tune(const hfci_op* op, int prec, int* tune6);
 
 /* Launch-shape autotuner: times the middle factors of the fixed-point iteration
  * (the dominant launches) over nsys systems (1..64, e.g. the number of shifted
- * systems that usually iterate together) for every valid shape, one, two and
- * (HFCI_F32) three factors per pass, keeps the fastest per factor for this operator and precision and writes
+ * systems that usually iterate together) for every valid shape, one to
+ * four factors per pass, keeps the fastest per factor for this operator and precision and writes
  * it to best6 (HOST, may be NULL).  timings (HOST, may be NULL if cap = 0) receives
  * up to cap rows of {kern, ty, pd, cz, fuse, sg, milliseconds per factor}; *count
  * (may be NULL) the number of shapes timed.  Uses the context's workspace (2 nsys

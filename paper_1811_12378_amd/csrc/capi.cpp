@@ -478,6 +478,7 @@ hfci_status hfci_op_set_tune(hfci_op* op, int prec, const int* t3) {
   t.cz = t3[3];
   t.fuse = t3[4];
   t.sg = t3[5];
+  t.chosen = true;
   HFCI_REQUIRE(tune_valid(t), "tune must be {0, ty in {4, 8}, pd in {1, 2}, cz, fuse, sg} or {1, 4, pd in 1..3, cz, "
                               "fuse, sg} or {1, 8, pd in {2, 3}, cz, fuse, sg} or {2, 8, pd in {2, 3}, cz, 1, sg} or "
                               "{3, 8, 2, cz, 1, sg}, cz in [0, 4096], fuse in {0, 1}, sg in [1, 16]");
@@ -658,6 +659,9 @@ hfci_status hfci_contour_create(const hfci_op* op, int J, double t, double eps, 
         if (!std::isfinite(cj[k].a_re) || !std::isfinite(cj[k].a_im) || !std::isfinite(cj[k].b_re) ||
             !std::isfinite(cj[k].b_im))
           throw Error(HFCI_E_NUMERIC, "non-finite factor coefficient");
+      // the eigenvalue nearest the pole: the real axis, or the band's lower edge, below or above it
+      complete_coefficients(cj, q, c->z0[j], op->s_h2,
+                            cd(std::min(std::max(zj.real(), op->b1), op->b2), zj.imag() > 0.0 ? 0.0 : -op->rho2));
       const cd zz = zj - c->z0[j];
       c->pdev[j] = PoleDev{c->z0[j].real(), c->z0[j].imag(), zz.real(), zz.imag()};
     }

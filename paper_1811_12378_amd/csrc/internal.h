@@ -37,6 +37,10 @@ struct Error : public std::runtime_error {
     if (!(cond)) throw Error(HFCI_E_ARG, msg);                    \
   } while (0)
 
+// c, g and al of a pole's factor coefficients from their a and b: the q factors of a step, then
+// those of step one.  lambda: where on the spectrum the pole's iteration is slowest.
+void complete_coefficients(FactorCoef* k, int q, cd z0, double s_h2, cd lambda);
+
 // Device workspace owned by a context: named buffers that only grow.
 class Workspace {
  public:
@@ -51,6 +55,7 @@ class Workspace {
   void set_arena(void* base, size_t cap);
   void clear_arena();
   size_t arena_used() const { return arena_used_; }
+  bool arena_set() const { return arena_ != nullptr; }
 
  private:
   struct Buf {

@@ -6,6 +6,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cstddef>
+#include <vector>
 
 namespace hfci {
 
@@ -20,7 +21,25 @@ struct KernelTune {
   // they split so; sg: with several factors per pass, the systems of a launch are taken sg
   // at a time, tile by tile, inside each XCD's slab of tiles (1 = system after system)
   int kern = 1, ty = 8, pd = 2, cz = 0, fuse = 0, sg = 1;
+  // false until a shape is set or tuned: the fixed-point factors then run several per pass
+  // (Launch::factor_rows) as with fuse 1
+  bool chosen = false;
 };
+
+// Tile geometry of a multi-factor pass in registers (zrows.h): gx x gy x nzc blocks of w
+// waves per system, tiles sx (sy) points apart, z-chunks of czlen planes.
+struct RowsShape {
+  int gx = 0, gy = 0, nzc = 0, czlen = 0, sx = 0, sy = 0;
+  int w = 0, per_sys = 0, xcd_slab = 0;
+  int small = 0;                   // the variant with fewer rows per lane
+  double inv_sh2 = 0, damp_sh2 = 0;  // 1 / s_h2, damp_scale / s_h2
+};
+constexpr int kRowsMax32 = 4, kRowsMax64 = 3;  // most factors per pass, complex64 / complex128
+// Widths of the passes of `count` factors with at most `most` each, in order: the fewest
+// passes (at least two when the first one forms the residual and the last one adds y1), as
+// even as they split, the wider ones in the middle and then last (the first and last passes of
+// a step read an extra stream).
+std::vector<int> rows_plan(int count, int most, bool step);
 
 // Geometry and operator scalars of the normalised A = (s/h^2) L7 - kappa - i D, plus
 // the launch shapes used for complex64 and complex128 vectors.
@@ -32,11 +51,20 @@ struct GridDesc {
   KernelTune tune32, tune64;
 };
 bool tune_valid(const KernelTune& t);
+// whether the complex64 kernels that stream planes into LDS (kerns 2 and 3) run on this grid:
+// an even nx and vectors under 2 GiB
+bool streams_fit(const GridDesc& g);
 
 // One linear factor of the product-form fixed-point step, per pole:
 //   w_out = a * (A - z0) w_in + b * w_in   (+ y1 on the last factor of a step).
 struct FactorCoef {
   double a_re, a_im, b_re, b_im;
+  // for the multi-factor passes in registers: g = a s_h2 and c = 6 - z0 / s_h2 + b / g, so that
+  // a (A - z0) w + b w = g ((c - kappa / s_h2 - i D / s_h2) w - sum of the six neighbours)
+  double c_re, c_im, g_re, g_im;
+  // at the first factor of a multi-factor pass in complex64: the scalar of the pass's output,
+  // the product of its g corrected for the rounding of its c (complete_coefficients)
+  double al_re, al_im;
 };
 
 // Per-pole constants used inside the stage kernels.
@@ -159,6 +187,20 @@ struct Launch {
   // nrhs, at most 64 poles): each point forms the stencil of f once for all poles; false
   // (nothing launched) when those conditions do not hold
   static bool factor_fanout(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<T2>& a);
+  // nf (2..4; complex128: 2, 3) consecutive factors from a.k in one pass, kind as for
+  // factor_pair, with the geometry rows_shape gave for the kind and a.count systems (its
+  // per_sys is the number of residual partials per system); false for an unsupported kind or
+  // nf.  The output must not alias the input.
+  static bool factor_rows(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<T2>& a, int kind,
+                          int nf, const RowsShape& sh);
+  // max_blocks > 0 bounds per_sys where some geometry allows it
+  static RowsShape rows_shape(const GridDesc& g, int nf, int kind, int count, int max_blocks = 0);
+  // upper bound of per_sys of the kinds that form residuals, for any count
+  static int rows_max_blocks(const GridDesc& g, int nf);
+  // whether factor_rows runs on this grid (32-bit offsets within a z-chunk)
+  static bool rows_fits(const GridDesc& g);
+  // whether the fixed-point factors run through factor_rows with the current launch shape
+  static bool rows_run(const GridDesc& g);
   static int pair_blocks(const GridDesc& g);  // residual partials per system of a pair launch
   // whether factor_pair runs on this grid (32-bit byte offsets: each vector under 4 GiB)
   static bool pair_fits(const GridDesc& g);

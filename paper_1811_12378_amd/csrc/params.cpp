@@ -395,12 +395,12 @@ void factor_coefficients(cd z, cd z0, double delta, int q, FactorCoef* out_L, Fa
   const cd sL = std::pow(1.0 / (fact[q] * pz), 1.0 / q);
   for (int k = 0; k < q; ++k) {
     const cd a = sL * mid, b = -sL * rho[k];
-    out_L[k] = FactorCoef{a.real(), a.imag(), b.real(), b.imag()};
+    out_L[k] = FactorCoef{a.real(), a.imag(), b.real(), b.imag(), 0, 0, 0, 0, 0, 0};
   }
   const cd g_scale = cd(0.0, delta) / pz;  // y1 = P2(B) (i delta f) / p~(z)
   if (q == 1) {
     // P2 = e_0 = 1
-    out_P[0] = FactorCoef{0.0, 0.0, g_scale.real(), g_scale.imag()};
+    out_P[0] = FactorCoef{0.0, 0.0, g_scale.real(), g_scale.imag(), 0, 0, 0, 0, 0, 0};
     return;
   }
   std::vector<cd> ce(q);
@@ -416,7 +416,65 @@ void factor_coefficients(cd z, cd z0, double delta, int q, FactorCoef* out_L, Fa
   const cd s2 = std::pow(g_scale * ce[q - 1], 1.0 / (q - 1));
   for (int k = 0; k < q - 1; ++k) {
     const cd a = s2 * mid, b = -s2 * mu[k];
-    out_P[k] = FactorCoef{a.real(), a.imag(), b.real(), b.imag()};
+    out_P[k] = FactorCoef{a.real(), a.imag(), b.real(), b.imag(), 0, 0, 0, 0, 0, 0};
+  }
+}
+
+std::vector<int> rows_plan(int count, int most, bool step) {
+  int np = (count + most - 1) / most;
+  if (np < 2 && step && count >= 2) np = 2;
+  std::vector<int> w(np, count / np);
+  int extra = count % np;
+  for (int i = 1; i + 1 < np && extra > 0; ++i, --extra) ++w[i];
+  if (extra > 0) {  // (three factors of a step: 2 + 1, so that the residual's pass has two)
+    ++w[step && count == 3 ? 0 : np - 1];
+    --extra;
+  }
+  if (extra > 0) ++w[0];
+  return w;
+}
+
+// A pass of the register kernels evaluates al prod_f (c_f - kappa / s_h2 - i D / s_h2 - nb) with
+// c_f and al rounded to the vectors' precision.  In complex64 the rounding of the c_f shifts
+// every eigenvalue's multiplier by the same few 1e-7 at every step, which a pole near the real
+// axis repeats over some hundred steps: al takes it back at the eigenvalue where the iteration
+// is slowest (the shift hardly varies along the slow part of the spectrum), and each pass's al
+// also takes back the rounding of the ones before it.
+void complete_coefficients(FactorCoef* k, int q, cd z0, double s_h2, cd lambda) {
+  const int n = q + std::max(q - 1, 1);
+  const double inv = 1.0 / s_h2;
+  for (int i = 0; i < n; ++i) {
+    const cd g = cd(k[i].a_re, k[i].a_im) * s_h2;
+    // (a lone constant factor, a = 0 for q = 1, is never in a multi-factor pass)
+    const cd c = g == cd(0.0, 0.0) ? cd(0.0, 0.0) : 6.0 - z0 * inv + cd(k[i].b_re, k[i].b_im) / g;
+    k[i].c_re = c.real();
+    k[i].c_im = c.imag();
+    k[i].g_re = g.real();
+    k[i].g_im = g.imag();
+    k[i].al_re = k[i].al_im = 0.0;
+  }
+  auto single = [](cd v) { return cd((float)v.real(), (float)v.imag()); };
+  for (int part = 0; part < 2; ++part) {
+    const bool step = part == 0;
+    const int count = step ? q : q - 1, k0 = step ? 0 : q;
+    if (count < 2) continue;
+    cd want(1.0, 0.0), have(1.0, 0.0);
+    int f = k0;
+    for (int w : rows_plan(count, kRowsMax32, step)) {
+      const int first = f;
+      for (; f < first + w; ++f) {
+        const cd c(k[f].c_re, k[f].c_im), zc(6.0 - z0.real() * inv, -z0.imag() * inv);
+        // the residual's pass adds the first factor's share to the residual's own diagonal
+        const cd rounded = step && f == 0 ? single(zc) + single(c - zc) : single(c);
+        const cd at = lambda * inv - 6.0;
+        want *= cd(k[f].g_re, k[f].g_im);
+        if (std::abs(rounded + at) > 1e-2) want *= (c + at) / (rounded + at);
+      }
+      const cd al = want / have;
+      k[first].al_re = al.real();
+      k[first].al_im = al.imag();
+      have *= single(al);
+    }
   }
 }
 

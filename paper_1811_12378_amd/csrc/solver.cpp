@@ -83,11 +83,37 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
     T2* wA = (T2*)ctx.ws.get("fp_wA", (size_t)nsys * vbytes);
     T2* wB = (q >= 3) ? (T2*)ctx.ws.get("fp_wB", (size_t)nsys * vbytes) : nullptr;
     const KernelTune& tn = (sizeof(T2) == 8) ? op.g.tune32 : op.g.tune64;
-    const bool fuse = tn.fuse != 0 && Launch<T2>::pair_fits(op.g);
-    const bool triples = fuse && Launch<T2>::triple_runs(op.g);
-    // residual partials come from the first launch of a step: a pair launch when fusing
-    const int nblk = (fuse && q >= 3) ? Launch<T2>::pair_blocks(op.g) : Launch<T2>::partial_blocks(op.g);
-    double* partial = (double*)ctx.ws.get("fp_partial", (size_t)nsys * nblk * sizeof(double));
+    // factors per pass: up to rows_max in registers (rows), else pairs and threes in LDS
+    const bool rows = Launch<T2>::rows_run(op.g);
+    const int rows_max = sizeof(T2) == 8 ? kRowsMax32 : kRowsMax64;
+    const bool fuse = rows || (tn.fuse != 0 && Launch<T2>::pair_fits(op.g));
+    const bool triples = fuse && !rows && Launch<T2>::triple_runs(op.g);
+    // residual partials come from the first launch of a step: a multi-factor launch when
+    // fusing.  Its geometry, and so the partials per system, depends on the systems still
+    // iterating; in a fixed arena it keeps to the partials of the tile kernels.
+    const int tile_blk = (tn.fuse != 0 && Launch<T2>::pair_fits(op.g) && q >= 3) ? Launch<T2>::pair_blocks(op.g)
+                                                                                  : Launch<T2>::partial_blocks(op.g);
+    const int max_blk = (rows && q >= 3 && ctx.ws.arena_set()) ? tile_blk : 0;
+    int nblk = tile_blk, nblk_cap = tile_blk;
+    struct Part {
+      int k, width, kind;
+    };
+    // launches of `count` factors from coefficient k0, several per pass in registers
+    auto plan_rows = [&](int k0, int count, int kind_first, int kind_last) {
+      const std::vector<int> w = rows_plan(count, rows_max, (kind_first & kFacResid) != 0);
+      std::vector<Part> v;
+      int k = k0;
+      for (size_t i = 0; i < w.size(); k += w[i++])
+        v.push_back(Part{k, w[i], (i == 0 ? kind_first : 0) | (i + 1 == w.size() ? kind_last : 0)});
+      return v;
+    };
+    std::vector<Part> step_rows;
+    if (rows && q >= 3) {
+      step_rows = plan_rows(0, q, kFacResid, kFacAdd);
+      nblk_cap = Launch<T2>::rows_max_blocks(op.g, step_rows[0].width);
+      if (max_blk > 0) nblk_cap = std::min(nblk_cap, std::max(max_blk, 1));
+    }
+    double* partial = (double*)ctx.ws.get("fp_partial", (size_t)nsys * nblk_cap * sizeof(double));
     int* active = (int*)ctx.ws.get("fp_active", (size_t)nsys * sizeof(int));
     int* list = (int*)ctx.ws.get("fp_list", (size_t)nsys * sizeof(int));
     double* rnorm2 = (double*)ctx.ws.get("fp_rnorm2", (size_t)nsys * sizeof(double));
@@ -98,8 +124,21 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
       launch_norm2_partial(s, f + (size_t)r * n, sizeof(T2) == 8, n, fpart + (size_t)r * nb);
     launch_reduce(s, fpart, nb, nrhs, fnorm2);
     launch_fp_start(s, nsys, sys0, nrhs, fnorm2, fixed, active, steps, list);
-
     FactorArgs<T2> a{};
+    // geometries already worked out, by (width, extra stream, systems)
+    struct Geometry {
+      int width, extra, count;
+      RowsShape s;
+    };
+    std::vector<Geometry> geometries;
+    auto rows_shape = [&](int width, int kind) -> const RowsShape& {
+      const int extra = kind & (kFacResid | kFacAdd) ? 1 : 0;
+      for (const Geometry& x : geometries)
+        if (x.width == width && x.extra == extra && x.count == a.count) return x.s;
+      geometries.push_back(Geometry{width, extra, a.count, Launch<T2>::rows_shape(op.g, width, kind, a.count, max_blk)});
+      return geometries.back().s;
+    };
+
     a.f = f;
     a.y1 = y1;
     a.coef = c.d_coef;
@@ -135,8 +174,9 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
       bool reads_f;
     };
     std::vector<Fixup>* fixups = nullptr;
-    // One launch of `width` (1, 2 or 3) consecutive factors starting at coefficient k.  kind:
-    // kFacInF / kFacResid on its first factor, kFacAdd / kFacDual on its last (none with 3).
+    // One launch of `width` (1 to 4) consecutive factors starting at coefficient k.  kind:
+    // kFacInF / kFacResid on its first factor, kFacAdd / kFacDual on its last (none with
+    // factor_triple).
     auto launch = [&](int kind, int k, int width, const T2* win, T2* wout, T2* wout2, bool fan = false) {
       a.k = k;
       a.win = win;
@@ -146,12 +186,21 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
       const int cls = resid                  ? HFCI_PROF_FP_FIRST
                        : (inf || dual)       ? HFCI_PROF_FP_INIT
                        : add                 ? HFCI_PROF_FP_LAST
-                       : width == 3          ? HFCI_PROF_FP_TRIPLE
+                       : width >= 3          ? HFCI_PROF_FP_TRIPLE
                                              : HFCI_PROF_FP_STAGE;
       const double vecs = (inf ? 0.0 : 1.0) + 1.0 + (add ? 1.0 : 0.0) + (dual ? 1.0 : 0.0);
       const bool timed = pr.sample(cls);
       if (timed) pr.begin(s);
-      const bool ok = width == 3   ? kind == 0 && Launch<T2>::factor_triple(s, op.g, kap, a)
+      bool ok;
+      if (rows && width >= 2) {
+        const RowsShape& sh = rows_shape(width, kind);
+        ok = Launch<T2>::factor_rows(s, op.g, kap, a, kind, width, sh);
+        if (resid) {
+          nblk = sh.per_sys;
+          HFCI_REQUIRE(nblk <= nblk_cap, "internal: more residual partials than allocated");
+        }
+      } else
+        ok = width == 3   ? kind == 0 && Launch<T2>::factor_triple(s, op.g, kap, a)
                       : width == 2 ? Launch<T2>::factor_pair(s, op.g, kap, a, kind)
                                    : (fan && Launch<T2>::factor_fanout(s, op.g, kap, a)) ||
                                          Launch<T2>::factor(s, op.g, kap, a, kind);
@@ -160,9 +209,6 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
         if (fixups) fixups->push_back(Fixup{pr.mark(), vecs, inf || resid});
         pr.end(s, cls, launch_bytes(vecs, inf || resid));
       }
-    };
-    struct Part {
-      int k, width, kind;
     };
     // launches of `count` factors from coefficient k0, two per pass when fusing; an odd
     // count leaves one single launch, at the end or (single_first) at the start.  With
@@ -206,7 +252,8 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
     const int nP = std::max(q - 1, 1);
     const bool dual = (graphs && !pr.on) || (fixed && cap <= 1);
     {
-      const std::vector<Part> pl = plan(q, nP, kFacInF, dual ? kFacDual : 0, fuse, true);
+      const std::vector<Part> pl = rows && nP >= 2 ? plan_rows(q, nP, kFacInF, dual ? kFacDual : 0)
+                                                   : plan(q, nP, kFacInF, dual ? kFacDual : 0, fuse, true);
       const T2* cur = nullptr;
       for (size_t i = 0; i < pl.size(); ++i) {
         const bool last = i + 1 == pl.size();
@@ -224,7 +271,7 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
 
     // ---- steps two and on: y <- L y + y1 ----
     // (a launch never writes its own input: a step made of a single launch goes through wA)
-    const std::vector<Part> pl = plan(0, q, kFacResid, kFacAdd, fuse && q >= 3, false);
+    const std::vector<Part> pl = step_rows.empty() ? plan(0, q, kFacResid, kFacAdd, fuse && q >= 3, false) : step_rows;
     const bool single = pl.size() == 1;
     // first launch of a step from y, with the ||f - (A - z) y||^2 partials of the current
     // iterate, the stopping test, and in adaptive mode the compacted list and the flags
@@ -413,11 +460,13 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   const size_t vbytes = n * sizeof(T2);
   T2* win = (T2*)ctx.ws.get("fp_wA", (size_t)nsys * vbytes);
   T2* wout = (T2*)ctx.ws.get("fp_wB", (size_t)nsys * vbytes);
-  FactorCoef* coef = (FactorCoef*)ctx.ws.get("tune_coef", 3 * sizeof(FactorCoef));
+  FactorCoef* coef = (FactorCoef*)ctx.ws.get("tune_coef", 7 * sizeof(FactorCoef));
   PoleDev* pole = (PoleDev*)ctx.ws.get("tune_pole", sizeof(PoleDev));
   int* list = (int*)ctx.ws.get("tune_list", (size_t)nsys * sizeof(int));
-  const FactorCoef c0[3] = {{1e-3, 0.0, 0.5, 0.0}, {1e-3, 0.0, 0.5, 0.0}, {1e-3, 0.0, 0.5, 0.0}};
   const PoleDev p0{0.5 * (op.b1 + op.b2), 0.5, 0.0, 0.0};
+  FactorCoef c0[4 + 3];
+  for (FactorCoef& c : c0) c = FactorCoef{1e-3, 0.0, 0.5, 0.0, 0, 0, 0, 0, 0, 0};
+  complete_coefficients(c0, 4, cd(p0.z0_re, p0.z0_im), op.s_h2, cd(0.0, 0.0));
   std::vector<int> ids(nsys);
   for (int k = 0; k < nsys; ++k) ids[k] = k;
   HFCI_HIP(hipMemcpyAsync(coef, c0, sizeof(c0), hipMemcpyHostToDevice, s));
@@ -433,12 +482,13 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   a.count = nsys;
   a.sys0 = 0;
   a.nrhs = 1;
-  a.cstride = 3;
+  a.cstride = 7;
   a.k = 0;
   KernelTune& cur = (sizeof(T2) == 8) ? op.g.tune32 : op.g.tune64;
   const KernelTune saved = cur;
   const void* kap = Prec<T2>::kappa(op);
   std::vector<KernelTune> cands;
+  // (every candidate is a shape set on purpose)
   for (int cz : {0, 16, 64}) {
     for (int ty : {4, 8})
       for (int pd : {1, 2}) cands.push_back(KernelTune{0, ty, pd, cz, 0});
@@ -455,7 +505,8 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
       for (int cz : {0, 16, 64})
         for (int pd : {2, 3})
           for (int sg : {1, 2, 4})
-            if ((sg == 1 || sg <= nsys) && !(kern == 3 && pd != 2)) cands.push_back(KernelTune{kern, 8, pd, cz, 1, sg});
+            if ((sg == 1 || sg <= nsys) && !((kern == 3 || kern == 1) && pd != 2))
+              cands.push_back(KernelTune{kern, 8, pd, cz, 1, sg});
     }
   // three middle factors per pass (kern 3, fuse 2; per-factor time = a third of a launch)
   if (sizeof(T2) == 8 && Launch<T2>::pair_fits(op.g))
@@ -472,9 +523,13 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
     for (const KernelTune& t : cands) {
       if (t.cz > 0 && t.cz >= op.g.nz) continue;  // same as one chunk per column: covered by cz = 0 or larger
       cur = t;
+      cur.chosen = true;
+      const int rows = Launch<T2>::rows_run(op.g) ? (sizeof(T2) == 8 ? kRowsMax32 : kRowsMax64) : 0;
       if (t.fuse == 2 && !Launch<T2>::triple_runs(op.g)) continue;  // (an odd nx: the pairs' shape covers it)
+      const RowsShape sh = rows ? Launch<T2>::rows_shape(op.g, rows, 0, nsys) : RowsShape{};
       auto one = [&] {
-        if (t.fuse == 2) Launch<T2>::factor_triple(s, op.g, kap, a);
+        if (rows) Launch<T2>::factor_rows(s, op.g, kap, a, 0, rows, sh);
+        else if (t.fuse == 2) Launch<T2>::factor_triple(s, op.g, kap, a);
         else if (t.fuse) Launch<T2>::factor_pair(s, op.g, kap, a, 0);
         else Launch<T2>::factor(s, op.g, kap, a, 0);
       };
@@ -486,11 +541,11 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
       HFCI_HIP(hipEventSynchronize(e1));
       float ms = 0.f;
       HFCI_HIP(hipEventElapsedTime(&ms, e0, e1));
-      const double avg = ms / reps / (t.fuse == 2 ? 3.0 : t.fuse ? 2.0 : 1.0);  // per factor
+      const double avg = ms / reps / (rows ? (double)rows : t.fuse == 2 ? 3.0 : t.fuse ? 2.0 : 1.0);  // per factor
       timings.emplace_back(t, avg);
       if (avg < best_ms) {
         best_ms = avg;
-        best = t;
+        best = cur;
       }
     }
   } catch (...) {

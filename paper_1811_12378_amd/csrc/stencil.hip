@@ -1967,9 +1967,7 @@ struct PairShape {
   int gx, gy, nzc, czlen, per_sys, xcd_slab;
 };
 
-bool dma_pair_fits(const GridDesc& g) {
-  return g.nx % 2 == 0 && (size_t)g.nx * g.ny * g.nz * sizeof(float2) < ((size_t)1 << 31);
-}
+bool dma_pair_fits(const GridDesc& g) { return streams_fit(g); }
 
 template <typename T>
 PairShape pair_shape(const GridDesc& g) {
@@ -2068,6 +2066,10 @@ void run_pair(hipStream_t st, const GridDesc& g, const void* kappa, const Factor
 }
 
 }  // namespace
+
+bool streams_fit(const GridDesc& g) {
+  return g.nx % 2 == 0 && (size_t)g.nx * g.ny * g.nz * sizeof(float2) < ((size_t)1 << 31);
+}
 
 bool tune_valid(const KernelTune& t) {
   if (t.cz < 0 || t.cz > 4096 || !(t.ty == 4 || t.ty == 8) || t.fuse < 0 || t.fuse > 2) return false;

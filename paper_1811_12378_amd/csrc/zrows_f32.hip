@@ -1,0 +1,11 @@
+// Multi-factor passes with planes in registers (zrows.h), complex64.
+#include "zrows_launch.h"
+
+namespace hfci {
+template bool Launch<float2>::factor_rows(hipStream_t, const GridDesc&, const void*, const FactorArgs<float2>&, int, int,
+                                          const RowsShape&);
+template RowsShape Launch<float2>::rows_shape(const GridDesc&, int, int, int, int);
+template int Launch<float2>::rows_max_blocks(const GridDesc&, int);
+template bool Launch<float2>::rows_fits(const GridDesc&);
+template bool Launch<float2>::rows_run(const GridDesc&);
+}  // namespace hfci

@@ -1,0 +1,233 @@
+// Kernels and launches of zrows.h for one precision (included by zrows_f32.hip and
+// zrows_f64.hip, which compile in parallel).
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+#include "zrows.h"
+
+namespace hfci {
+namespace zrows {
+
+// Rows per lane and the largest block, by precision, factors and extra stream (f or y1): the
+// most rows whose planes of state stay in registers without spills, at three waves per SIMD
+// (168 registers, blocks of up to 12 waves), or two where three would leave a lane one row.
+// SM: few rows per lane, for launches that cannot fill the chip: a plane then costs the
+// barrier and the LDS exchange more than the arithmetic.
+template <typename T, int NF, bool EXTRA, bool SM>
+struct Cfg {
+  static constexpr bool kF32 = sizeof(T) == 4;
+  static constexpr int R = SM     ? (kF32 ? 2 : 1)
+                           : kF32 ? (NF == 2 ? 4 : NF == 3 ? (EXTRA ? 3 : 4) : (EXTRA ? 2 : 3))
+                                  : (NF == 2 ? (EXTRA ? 2 : 3) : (EXTRA ? 3 : 2));
+  static constexpr int WPE = SM ? (NF == 4 ? 3 : 4) : (!kF32 && NF == 3 && EXTRA) ? 2 : 3;  // waves per SIMD
+  static constexpr int WMAX = 4 * WPE;
+};
+
+template <typename T, int KIND, int NF, bool SM>
+struct KindCfg : Cfg<T, NF, (KIND & (kFacResid | kFacAdd)) != 0, SM> {};
+
+template <typename T, int KIND, int NF, bool SM>
+__global__ __launch_bounds__((64 * KindCfg<T, KIND, NF, SM>::WMAX))
+    __attribute__((amdgpu_waves_per_eu((KindCfg<T, KIND, NF, SM>::WPE)))) void zrows_kernel(
+        GridDesc g, RowsShape q, int sgrp, FactorArgs<typename V2<T>::t> a, const T* __restrict__ K) {
+  extern __shared__ __align__(16) char lds[];
+  // block order: see pair_block in stencil.hip
+  const int per_sys = q.per_sys, xcd_slab = q.xcd_slab;
+  int li, b;
+  if (xcd_slab > 0 && sgrp > 1) {
+    const int xcd = blockIdx.x % 8, k = blockIdx.x / 8;
+    const int gsz = sgrp * xcd_slab;
+    const int s0 = (k / gsz) * sgrp, r = k % gsz;
+    const int gs = min(sgrp, a.count - s0);
+    li = s0 + r % gs;
+    b = xcd * xcd_slab + r / gs;
+  } else {
+    li = blockIdx.x / per_sys;
+    b = blockIdx.x % per_sys;
+    if (xcd_slab > 0) b = (b % 8) * xcd_slab + b / 8;
+  }
+  const int s = __builtin_amdgcn_readfirstlane(a.list[li]);
+  if (s < 0) return;  // a stopped system past the end of the active list (uniform)
+  rows_tile<T, KIND, NF, KindCfg<T, KIND, NF, SM>::R>(g, q, s, b, a, K, lds);
+}
+
+// The longest z-chunk whose planes (with the halo) 32-bit offsets reach
+template <typename T>
+int chunk_limit(const GridDesc& g) {
+  const double planes = 2147483647.0 / ((double)g.nx * g.ny * 2 * sizeof(T));
+  return (int)std::min(planes, 1e6) - 10;
+}
+
+// The largest number of blocks per system a geometry may have: enough to fill the chip eight
+// times over with one system, or what the longest chunks and largest blocks give
+template <typename T, int NF, bool EXTRA>
+int rows_cap(const GridDesc& g) {
+  using C = Cfg<T, NF, EXTRA, false>;
+  const KernelTune& t = sizeof(T) == 4 ? g.tune32 : g.tune64;
+  auto tiles = [](int n, int len) { return n <= len ? 1 : 1 + (n - len + len - 2 * NF - 1) / (len - 2 * NF); };
+  const int cz = std::min(t.cz > 0 ? t.cz : 126, chunk_limit<T>(g));
+  return std::max(2048, tiles(g.nx, 64) * tiles(g.ny, C::WMAX * C::R) * ((g.nz + cz - 1) / cz));
+}
+
+// Geometry of a pass over `count` systems.  Candidates: blocks of 2 .. WMAX waves and z-chunks
+// of 2 .. 128 planes (those for which a chunk's iterations fill whole trips of four), or the
+// launch shape's chunk.  A block's planes cost its vector instructions or, with few waves on
+// a CU, the latency of a barrier and the LDS exchange; short chunks repeat 2 (NF - 1) planes,
+// small blocks 2 NF rows; long chunks and large blocks leave CUs idle where systems are few.
+// The constants are fitted to 5000 measured launches (32^3 to 256^3, 1 to 24 systems, both
+// precisions, every kind): the geometry chosen costs 4 % more than the best measured one on
+// average (33 % at worst), where one fixed geometry per grid costs 30 % and more at either end.
+template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
+void shape_try(const GridDesc& g, int count, int max_blocks, RowsShape& best, double& best_t, RowsShape& any) {
+  using C = Cfg<T, NF, EXTRA, SM>;
+  const KernelTune& t = sizeof(T) == 4 ? g.tune32 : g.tune64;
+  auto tiles = [](int n, int len, int& step) {
+    step = 0;
+    if (n <= len) return 1;
+    const int k = 1 + (n - len + len - 2 * NF - 1) / (len - 2 * NF);
+    step = (n - len + k - 2) / (k - 1);
+    return k;
+  };
+  const int climit = chunk_limit<T>(g);
+  const int cap = rows_cap<T, NF, EXTRA>(g);
+  for (int w = C::WMAX; w >= 2; --w) {
+    const int rb = w * C::R;
+    if (g.ny > rb && rb <= 2 * NF) break;
+    if (w > 2 && rb - C::R >= g.ny) continue;  // a smaller block covers every row
+    if (lds_bytes(NF, w, 2 * sizeof(T)) > 160 * 1024) continue;
+    RowsShape s;
+    s.w = w;
+    s.small = SM ? 1 : 0;
+    s.gx = tiles(g.nx, 64, s.sx);
+    if (s.sx > 0) s.sx = std::min((s.sx + 7) / 8 * 8, 64 - 2 * NF);  // rows start on 64-byte lines where they can
+    s.gy = tiles(g.ny, rb, s.sy);
+    const int bpc = std::max(1, C::WMAX / w);  // blocks per CU (registers; LDS allows as many)
+    for (const int m : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
+      int cz = 4 * m - 2 * (NF - 1) % 4;
+      if (t.cz > 0) cz = t.cz;
+      s.czlen = std::min(std::min(cz, g.nz), climit);
+      s.nzc = (g.nz + s.czlen - 1) / s.czlen;
+      s.per_sys = s.gx * s.gy * s.nzc;
+      // CU cycles of the launch (2.4 GHz): rounds of blocks over the CUs, `conc` of them on a
+      // CU at once; memory time overlaps with all but a quarter of the shorter of the two
+      const double blocks = (double)s.per_sys * count;
+      const double v = C::R * (NF * (sizeof(T) == 4 ? 83.0 : 137.0) + (RESID ? 72.0 : 0.0));
+      const double iters = (s.czlen + 2 * (NF - 1) + 3) / 4 * 4;
+      auto round = [&](double conc) {
+        return iters * std::max(std::ceil(w * conc / 4) * v * 1.19, 820.0 + v * 1.02) + 6100.0;
+      };
+      const double conc = std::max(1.0, std::min((double)bpc, std::ceil(blocks / 256.0)));
+      const double full = std::floor(blocks / (256.0 * conc)), rest = blocks - full * 256.0 * conc;
+      const double comp = full * round(conc) + (rest > 0 ? round(std::ceil(rest / 256.0)) : 0.0);
+      const double e = 2 * sizeof(T), pts = (double)g.nx * g.ny * g.nz * count;
+      const double hbm = pts * (2.5 * e + (RESID ? e / count : EXTRA ? e : 0.0));
+      const double l2 = (double)s.gx * 64 * s.gy * rb * s.nzc * (s.czlen + 2 * NF) * count * 1.5 * e +
+                        pts * (EXTRA ? 2.0 : 1.0) * e;
+      const double mem = 2400.0 * std::max(hbm / 5.16e6, l2 / 9.34e6);
+      const double tm = std::max(comp, mem) + 0.25 * std::min(comp, mem);
+      if (s.per_sys <= cap && (max_blocks <= 0 || s.per_sys <= max_blocks) && tm < best_t) {
+        best_t = tm;
+        best = s;
+      }
+      if (any.w == 0 || s.per_sys < any.per_sys) any = s;
+      if (t.cz > 0 || cz >= g.nz || cz >= climit) break;
+    }
+  }
+}
+
+template <typename T, int NF, bool EXTRA, bool RESID>
+RowsShape shape_for(const GridDesc& g, int count, int max_blocks) {
+  RowsShape best{}, any{};
+  double best_t = 1e300;
+  shape_try<T, NF, EXTRA, RESID, false>(g, count, max_blocks, best, best_t, any);
+  shape_try<T, NF, EXTRA, RESID, true>(g, count, max_blocks, best, best_t, any);
+  if (best.w == 0) best = any;
+  best.xcd_slab = (best.per_sys % 8 == 0 && best.per_sys >= 64) ? best.per_sys / 8 : 0;
+  best.inv_sh2 = 1.0 / g.s_h2;
+  best.damp_sh2 = g.damp_scale / g.s_h2;
+  return best;
+}
+
+template <typename T, int KIND, int NF>
+void run(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<typename V2<T>::t>& a,
+         const RowsShape& s) {
+  const int sg = sizeof(T) == 4 ? g.tune32.sg : g.tune64.sg;
+  const dim3 grid((unsigned)s.per_sys * (unsigned)a.count), block(64 * s.w);
+  const size_t lds = lds_bytes(NF, s.w, 2 * sizeof(T));
+  if (s.small)
+    hipLaunchKernelGGL((zrows_kernel<T, KIND, NF, true>), grid, block, lds, st, g, s, sg, a, (const T*)kappa);
+  else
+    hipLaunchKernelGGL((zrows_kernel<T, KIND, NF, false>), grid, block, lds, st, g, s, sg, a, (const T*)kappa);
+}
+
+template <typename T, int NF>
+bool run_kind(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<typename V2<T>::t>& a, int kind,
+              const RowsShape& s) {
+  switch (kind) {
+    case 0: run<T, 0, NF>(st, g, kappa, a, s); return true;
+    case kFacResid: run<T, kFacResid, NF>(st, g, kappa, a, s); return true;
+    case kFacAdd: run<T, kFacAdd, NF>(st, g, kappa, a, s); return true;
+    case kFacDual: run<T, kFacDual, NF>(st, g, kappa, a, s); return true;
+    case kFacInF: run<T, kFacInF, NF>(st, g, kappa, a, s); return true;
+    case kFacInF | kFacDual: run<T, kFacInF | kFacDual, NF>(st, g, kappa, a, s); return true;
+    default: return false;
+  }
+}
+
+}  // namespace zrows
+
+template <typename T2>
+bool Launch<T2>::factor_rows(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<T2>& a, int kind,
+                             int nf, const RowsShape& sh) {
+  using T = typename zrows::Elem<T2>::t;
+  if (a.count <= 0) return true;
+  if (nf == 2) return zrows::run_kind<T, 2>(st, g, kappa, a, kind, sh);
+  if (nf == 3) return zrows::run_kind<T, 3>(st, g, kappa, a, kind, sh);
+  if constexpr (sizeof(T2) == 8)
+    if (nf == 4) return zrows::run_kind<T, 4>(st, g, kappa, a, kind, sh);
+  return false;
+}
+
+template <typename T2>
+RowsShape Launch<T2>::rows_shape(const GridDesc& g, int nf, int kind, int count, int max_blocks) {
+  using T = typename zrows::Elem<T2>::t;
+  auto of = [&](auto nfc) {
+    constexpr int NF = decltype(nfc)::value;
+    return (kind & kFacResid) ? zrows::shape_for<T, NF, true, true>(g, count, max_blocks)
+           : (kind & kFacAdd) ? zrows::shape_for<T, NF, true, false>(g, count, max_blocks)
+                              : zrows::shape_for<T, NF, false, false>(g, count, max_blocks);
+  };
+  if (nf == 2) return of(std::integral_constant<int, 2>{});
+  if (nf == 3) return of(std::integral_constant<int, 3>{});
+  if constexpr (sizeof(T2) == 8)
+    if (nf == 4) return of(std::integral_constant<int, 4>{});
+  return RowsShape{};
+}
+
+template <typename T2>
+int Launch<T2>::rows_max_blocks(const GridDesc& g, int nf) {
+  using T = typename zrows::Elem<T2>::t;
+  if (nf == 2) return zrows::rows_cap<T, 2, true>(g);
+  if (nf == 3) return zrows::rows_cap<T, 3, true>(g);
+  if constexpr (sizeof(T2) == 8)
+    if (nf == 4) return zrows::rows_cap<T, 4, true>(g);
+  return 0;
+}
+
+template <typename T2>
+bool Launch<T2>::rows_fits(const GridDesc& g) {
+  return zrows::chunk_limit<typename zrows::Elem<T2>::t>(g) >= 4;
+}
+
+template <typename T2>
+bool Launch<T2>::rows_run(const GridDesc& g) {
+  const KernelTune& t = sizeof(T2) == 8 ? g.tune32 : g.tune64;
+  // kerns 2 and 3 are the complex64 kernels that stream into LDS; where the grid does not
+  // suit them (an odd nx, vectors of 2 GiB or more) their shapes run these passes too
+  return (!t.chosen || (t.fuse != 0 && (t.kern <= 1 || !streams_fit(g)))) && rows_fits(g);
+}
+
+}  // namespace hfci
