@@ -31,30 +31,47 @@ template <> void copy_vec<double2>(hipStream_t s, double2* dst, const double2* s
 std::string tag(const char* base, int i) { return std::string(base) + "_" + std::to_string(i); }
 
 // Device tables and per-system vectors of a batch in precision T2.
+//
+// Work tables: table 0 maps blocks of the single-factor launches.  With several factors per
+// pass (rows) every class of launch has a table and a geometry per instance of its own: the
+// classes of the later steps once per level of work left (a level's geometry is made for all
+// systems iterating, or a 4th, 16th or 64th of them), then those of step one, which runs once
+// over all live systems.  The stopping test rebuilds the tables of the later steps on the device.
 template <typename T2>
 struct MultiFp {
+  static constexpr int kLevels = 4;
   Ctx* ctx = nullptr;
   int count = 0, q = 0, cstride = 0, nsys = 0;
   std::vector<const Op*> ops;
   std::vector<const Contour*> cons;
-  std::vector<int> sys0, J, per_sys, per_sys_p;  // per instance (single-factor and pair tiles)
-  bool pairs = false;                 // factors two per pass (every instance supports it)
+  std::vector<int> sys0, J;           // per instance
+  bool rows = false;                  // several factors per pass (every instance supports it)
+  int levels = 1;
+  std::vector<RowsClass> classes;     // per table from 1 on
+  int nlater = 0;                     // classes of the later steps (per level)
+  int ntab = 1, ntest = 1;            // tables in all, and of the later steps (with table 0)
+  std::vector<int> bps;               // [ntab][count]: blocks per system of each instance
   std::vector<size_t> n;
   std::vector<int> slot_of;           // per system
   std::vector<T2*> f, y;              // per instance: f (n), y (J n)
   std::vector<MultiSys<T2>> h_sys;
-  std::vector<int2> h_seg, h_segp;
-  std::vector<int> h_init;  // host sources of asynchronous copies live as long as the batch
+  std::vector<int2> h_seg;
+  std::vector<int> h_init, h_bps;  // host sources of asynchronous copies live as long as the batch
+  std::vector<RowsShape> h_shapes;    // [ntab - 1][count]
   MultiInst* d_inst = nullptr;
   MultiSys<T2>* d_sys = nullptr;
-  int2* d_seg = nullptr;
-  int2* d_segp = nullptr;
-  int2* d_bps = nullptr;              // per system: {single-factor, pair} blocks
+  RowsShape* d_shapes = nullptr;
+  int2* d_seg = nullptr;              // [ntab][nsys + 1]
+  int* d_bps = nullptr;               // [ntab][nsys]
   int *active = nullptr, *steps = nullptr;
   double *rnorm2 = nullptr, *fnorm2 = nullptr, *fpart = nullptr, *dpart = nullptr;
   std::vector<double*> cc;            // per instance: sigma_j / z_j (device)
   std::vector<T2*> w;                 // per instance: the quadrature sum (n)
   int nb_max = 0, nd_max = 0;
+  struct Part {
+    int k, width, kind;
+  };
+  std::vector<Part> first_plan, step_plan;
 
   MultiFp(Ctx* c, const std::vector<const Op*>& o, const std::vector<const Contour*>& k) : ctx(c), ops(o), cons(k) {
     hipStream_t s = ctx->stream;
@@ -62,30 +79,39 @@ struct MultiFp {
     q = cons[0]->q;
     cstride = cons[0]->cstride;
     std::vector<MultiInst> h_inst(count);
-    size_t npart = 0;
-    pairs = q >= 3;
+    std::vector<GridDesc> grids;
+    rows = q >= 3;
     for (int i = 0; i < count; ++i) {
       h_inst[i] = MultiLaunch<T2>::describe(ops[i]->g, kappa_of<T2>(*ops[i]));
-      pairs = pairs && h_inst[i].pper_sys > 0;
-    }
-    for (int i = 0; i < count; ++i) {
+      grids.push_back(h_inst[i].g);
+      rows = rows && Launch<T2>::rows_fits(h_inst[i].g);
       sys0.push_back(nsys);
       J.push_back(cons[i]->J);
       n.push_back(ops[i]->n);
-      per_sys.push_back(h_inst[i].per_sys);
-      per_sys_p.push_back(h_inst[i].pper_sys);
       nsys += cons[i]->J;
-      // residual partials: one per block of the launch that forms them (a pair when fusing)
-      npart += (size_t)cons[i]->J * (pairs ? h_inst[i].pper_sys : h_inst[i].per_sys);
       nb_max = std::max(nb_max, blas_blocks(ops[i]->n));
       nd_max = std::max(nd_max, Launch<T2>::partial_blocks(ops[i]->g));
+    }
+    if (rows) rows = make_classes(grids);
+    const int nP = std::max(q - 1, 1);
+    first_plan = plan(q, nP, kFacInF, kFacDual);
+    step_plan = plan(0, q, kFacResid, kFacAdd);
+    for (int t = 0; t < ntab; ++t)
+      for (int i = 0; i < count; ++i)
+        bps.push_back(t == 0 ? h_inst[i].per_sys : h_shapes[(size_t)(t - 1) * count + i].per_sys);
+    // residual partials: one per block of the launch that forms them, at the level with most
+    std::vector<int> npart_of(count, 0);
+    size_t npart = 0;
+    for (int i = 0; i < count; ++i) {
+      for (int l = 0; l < levels; ++l) npart_of[i] = std::max(npart_of[i], bps[(size_t)table_of(0, l) * count + i]);
+      npart += (size_t)J[i] * npart_of[i];
     }
     Workspace& ws = ctx->ws;
     d_inst = (MultiInst*)ws.get("mb_inst", count * sizeof(MultiInst));
     d_sys = (MultiSys<T2>*)ws.get("mb_sys", nsys * sizeof(MultiSys<T2>));
-    d_seg = (int2*)ws.get("mb_seg", (nsys + 1) * sizeof(int2));
-    d_segp = (int2*)ws.get("mb_segp", (nsys + 1) * sizeof(int2));
-    d_bps = (int2*)ws.get("mb_bps", nsys * sizeof(int2));
+    d_shapes = (RowsShape*)ws.get("mb_shapes", h_shapes.size() * sizeof(RowsShape));
+    d_seg = (int2*)ws.get("mb_seg", (size_t)ntab * (nsys + 1) * sizeof(int2));
+    d_bps = (int*)ws.get("mb_bps", (size_t)ntab * nsys * sizeof(int));
     active = (int*)ws.get("mb_active", nsys * sizeof(int));
     steps = (int*)ws.get("mb_steps", nsys * sizeof(int));
     rnorm2 = (double*)ws.get("mb_rnorm2", nsys * sizeof(double));
@@ -127,55 +153,125 @@ struct MultiFp {
         d.pole = cons[i]->d_poles + p;
         d.partial = part + poff;
         d.inst = i;
-        d.nblk = pairs ? per_sys_p[i] : per_sys[i];
         d.slot = i;
-        d.pad = 0;
-        poff += d.nblk;
+        poff += npart_of[i];
         slot_of[G] = i;
       }
     }
     HFCI_HIP(hipMemcpyAsync(d_inst, h_inst.data(), count * sizeof(MultiInst), hipMemcpyHostToDevice, s));
     HFCI_HIP(hipMemcpyAsync(d_sys, h_sys.data(), nsys * sizeof(MultiSys<T2>), hipMemcpyHostToDevice, s));
-    std::vector<int2> h_bps(nsys);
-    for (int G = 0; G < nsys; ++G)
-      h_bps[G] = int2{per_sys[slot_of[G]], pairs ? per_sys_p[slot_of[G]] : 0};
-    HFCI_HIP(hipMemcpyAsync(d_bps, h_bps.data(), nsys * sizeof(int2), hipMemcpyHostToDevice, s));
+    if (!h_shapes.empty())
+      HFCI_HIP(hipMemcpyAsync(d_shapes, h_shapes.data(), h_shapes.size() * sizeof(RowsShape), hipMemcpyHostToDevice, s));
+    for (int t = 0; t < ntab; ++t)
+      for (int G = 0; G < nsys; ++G) h_bps.push_back(bps[(size_t)t * count + slot_of[G]]);
+    HFCI_HIP(hipMemcpyAsync(d_bps, h_bps.data(), h_bps.size() * sizeof(int), hipMemcpyHostToDevice, s));
     HFCI_HIP(hipStreamSynchronize(s));
   }
 
-  // Launch bounds of the systems with hact[G] != 0: rows to search (the live rows and
-  // the sentinel) and blocks of single-factor and pair launches.
+  // launches of cnt factors from coefficient k0: several per pass with rows, else one each
+  std::vector<Part> plan(int k0, int cnt, int kind_first, int kind_last) const {
+    const int most = rows ? (sizeof(T2) == 8 ? kRowsMax32 : kRowsMax64) : 1;
+    const std::vector<int> w = most > 1 && cnt >= 2 ? rows_plan(cnt, most, (kind_first & kFacResid) != 0)
+                                                    : std::vector<int>(cnt, 1);
+    std::vector<Part> v;
+    int k = k0;
+    for (size_t i = 0; i < w.size(); k += w[i++])
+      v.push_back(Part{k, w[i], (i == 0 ? kind_first : 0) | (i + 1 == w.size() ? kind_last : 0)});
+    return v;
+  }
+
+  // The classes of multi-factor launches and their geometries; false if one has none.
+  bool make_classes(const std::vector<GridDesc>& grids) {
+    auto add = [&](std::vector<RowsClass>& v, const Part& p) {
+      const int kind = p.kind & (kFacResid | kFacAdd);
+      if (p.width < 2) return;
+      for (const RowsClass& x : v)
+        if (x.width == p.width && x.kind == kind) return;
+      RowsClass x;
+      x.width = p.width;
+      x.kind = kind;
+      v.push_back(x);
+    };
+    std::vector<RowsClass> later, first;
+    for (const Part& p : plan(0, q, kFacResid, kFacAdd)) add(later, p);  // the residual's class comes first
+    for (const Part& p : plan(q, std::max(q - 1, 1), kFacInF, kFacDual)) add(first, p);
+    levels = nsys <= 4096 ? kLevels : 1;
+    nlater = (int)later.size();
+    auto geometry = [&](const RowsClass& x, double part) {
+      std::vector<double> systems(J.begin(), J.end());
+      for (double& v : systems) v *= part;
+      std::vector<RowsShape> sh(count);
+      const RowsClass c = MultiLaunch<T2>::rows_class(grids, systems, x.width, x.kind, sh);
+      classes.push_back(c);
+      h_shapes.insert(h_shapes.end(), sh.begin(), sh.end());
+      return c.w > 0;
+    };
+    bool ok = true;
+    for (int l = 0; l < levels; ++l)
+      for (const RowsClass& x : later) ok = geometry(x, std::pow(0.25, l)) && ok;
+    for (const RowsClass& x : first) ok = geometry(x, 1.0) && ok;
+    if (!ok) {
+      classes.clear();
+      h_shapes.clear();
+      nlater = 0;
+      levels = 1;
+      return false;
+    }
+    ntest = 1 + levels * nlater;
+    ntab = 1 + (int)classes.size();
+    return true;
+  }
+
+  // the table of class c of the later steps at a level (table 0 without rows)
+  int table_of(int c, int level) const { return rows ? 1 + level * nlater + c : 0; }
+  // the table of a launch: its width's and kind's class at the level, or of step one
+  int table_for(const Part& p, int level) const {
+    if (p.width < 2) return 0;
+    const bool step = p.k < q;
+    const int lo = step ? 1 + level * nlater : ntest, hi = step ? lo + nlater : ntab;
+    for (int t = lo; t < hi; ++t)
+      if (classes[t - 1].width == p.width && classes[t - 1].kind == (p.kind & (kFacResid | kFacAdd))) return t;
+    throw Error(HFCI_E_ARG, "internal: no geometry for a launch");
+  }
+
+  // Launch bounds of the systems with hact[G] != 0: rows to search (the live rows and the
+  // sentinel), blocks per table, and the level of the work they are.
   struct Tables {
-    int nseg, blocks, blocks_p;
+    int nseg = 1, level = 0;
+    std::vector<int> blocks;
   };
   Tables bounds(const std::vector<int>& hact) const {
-    Tables t{1, 0, 0};
-    for (int G = 0; G < nsys; ++G)
-      if (hact[G]) {
-        ++t.nseg;
-        t.blocks += per_sys[slot_of[G]];
-        if (pairs) t.blocks_p += per_sys_p[slot_of[G]];
-      }
+    Tables t;
+    t.blocks.assign(ntab, 0);
+    std::vector<int> per(count, 0);
+    double all = 0.0, left = 0.0;
+    for (int G = 0; G < nsys; ++G) {
+      all += (double)n[slot_of[G]];
+      if (!hact[G]) continue;
+      ++t.nseg;
+      ++per[slot_of[G]];
+      left += (double)n[slot_of[G]];
+    }
+    for (int k = 0; k < ntab; ++k)
+      for (int i = 0; i < count; ++i) t.blocks[k] += per[i] * bps[(size_t)k * count + i];
+    while (t.level + 1 < levels && left < 0.5 * std::pow(0.25, t.level) * all) ++t.level;
     return t;
   }
   // the work tables of those systems, each ending in its sentinel {total blocks, -1}
   Tables upload_segments(const std::vector<int>& hact) {
-    h_seg.clear();
-    h_segp.clear();
-    int blocks = 0, blocks_p = 0;
-    for (int G = 0; G < nsys; ++G)
-      if (hact[G]) {
-        h_seg.push_back(int2{blocks, G});
-        h_segp.push_back(int2{blocks_p, G});
-        blocks += per_sys[slot_of[G]];
-        if (pairs) blocks_p += per_sys_p[slot_of[G]];
-      }
-    h_seg.push_back(int2{blocks, -1});
-    h_segp.push_back(int2{blocks_p, -1});
+    h_seg.assign((size_t)ntab * (nsys + 1), int2{0, -1});
+    for (int t = 0; t < ntab; ++t) {
+      int2* row = &h_seg[(size_t)t * (nsys + 1)];
+      int blocks = 0;
+      for (int G = 0; G < nsys; ++G)
+        if (hact[G]) {
+          *row++ = int2{blocks, G};
+          blocks += bps[(size_t)t * count + slot_of[G]];
+        }
+      *row = int2{blocks, -1};
+    }
     HFCI_HIP(hipMemcpyAsync(d_seg, h_seg.data(), h_seg.size() * sizeof(int2), hipMemcpyHostToDevice, ctx->stream));
-    HFCI_HIP(hipMemcpyAsync(d_segp, h_segp.data(), h_segp.size() * sizeof(int2), hipMemcpyHostToDevice,
-                            ctx->stream));
-    return Tables{(int)h_seg.size(), blocks, blocks_p};
+    return bounds(hact);
   }
 
   // The fixed-point iteration of every system of the live instances (live[i] != 0) on
@@ -205,43 +301,32 @@ struct MultiFp {
     HFCI_HIP(hipMemcpyAsync(steps, h_init.data(), nsys * sizeof(int), hipMemcpyHostToDevice, s));
     auto sg = upload_segments(hact);
     const bool f64 = sizeof(T2) == 16;
-    // one launch of `width` factors from coefficient k over the listed systems
-    auto launch = [&](int kind, int k, int width, int rin, int rout, int rout2) {
-      if (width == 2) {
-        const bool ok = MultiLaunch<T2>::factor_pair(s, d_inst, d_sys, d_segp, sg.nseg, sg.blocks_p, kind, rin, rout,
-                                                     rout2, k, cstride);
+    // one launch of a plan over the listed systems, at the level of `sg`
+    auto launch = [&](const Part& p, int rin, int rout, int rout2) {
+      const int t = table_for(p, sg.level);
+      const int2* seg = d_seg + (size_t)t * (nsys + 1);
+      if (p.width >= 2) {
+        const bool ok = MultiLaunch<T2>::factor_rows(s, classes[t - 1], d_inst, d_shapes + (size_t)(t - 1) * count, d_sys,
+                                                     seg, sg.nseg, sg.blocks[t], p.kind, rin, rout, rout2, p.k, cstride);
         HFCI_REQUIRE(ok, "internal: unsupported factor kind");
       } else {
-        MultiLaunch<T2>::factor(s, d_inst, d_sys, d_seg, sg.nseg, sg.blocks, kind, rin, rout, rout2, k, cstride, f64);
+        MultiLaunch<T2>::factor(s, d_inst, d_sys, seg, sg.nseg, sg.blocks[t], p.kind, rin, rout, rout2, p.k, cstride,
+                                f64);
       }
     };
-    struct Part {
-      int k, width, kind;
-    };
-    // launches of cnt factors from coefficient k0, two per pass when fusing; an odd count
-    // leaves one single launch, at the end or (single_first) at the start
-    auto plan = [&](int k0, int cnt, int kind_first, int kind_last, bool single_first) {
-      std::vector<Part> v;
-      for (int j = 0; j < cnt;) {
-        const bool lone = single_first && j == 0 && cnt % 2 == 1;
-        const int w = (pairs && j + 1 < cnt && !lone) ? 2 : 1;
-        int kind = 0;
-        if (j == 0) kind |= kind_first;
-        if (j + w == cnt) kind |= kind_last;
-        v.push_back(Part{k0 + j, w, kind});
-        j += w;
-      }
-      return v;
+    // blocks per system of the launch that last formed residuals
+    const int* nblk = nullptr;
+    auto head = [&]() {
+      launch(step_plan[0], kRoleY, kRoleWA, kRoleNone);
+      nblk = d_bps + (size_t)table_for(step_plan[0], sg.level) * nsys;
     };
     // step one: the max(q-1, 1) factors of P2 from f into y1 (and y)
-    const int nP = std::max(q - 1, 1);
     {
-      const std::vector<Part> pl = plan(q, nP, kFacInF, kFacDual, true);
       int cur = kRoleF;
-      for (size_t i = 0; i < pl.size(); ++i) {
-        const bool last = i + 1 == pl.size();
+      for (size_t i = 0; i < first_plan.size(); ++i) {
+        const bool last = i + 1 == first_plan.size();
         const int dst = last ? kRoleY1 : (cur == kRoleWA ? kRoleWB : kRoleWA);
-        launch(pl[i].kind, pl[i].k, pl[i].width, cur, dst, last ? kRoleY : kRoleNone);
+        launch(first_plan[i], cur, dst, last ? kRoleY : kRoleNone);
         cur = dst;
       }
       st.matvecs += (long long)(q - 1) * nact;
@@ -249,13 +334,13 @@ struct MultiFp {
     }
     // later steps: the first launch reads y and forms the residual partials, the last adds
     // y1 into y; the launches in between ping-pong between wA and wB
-    const std::vector<Part> pl = plan(0, q, kFacResid, kFacAdd, false);
+    const std::vector<Part>& pl = step_plan;
     auto rest = [&]() {
       int cur = kRoleWA;
       for (size_t i = 1; i < pl.size(); ++i) {
         const bool last = i + 1 == pl.size();
         const int dst = last ? kRoleY : (cur == kRoleWA ? kRoleWB : kRoleWA);
-        launch(pl[i].kind, pl[i].k, pl[i].width, cur, dst, kRoleNone);
+        launch(pl[i], cur, dst, kRoleNone);
         cur = dst;
       }
     };
@@ -269,9 +354,9 @@ struct MultiFp {
       int* flags[2] = {ctx->pinned_int, ctx->pinned_int + kPinnedIntHalf};
       int* flags_dev[2] = {ctx->pinned_int_dev, ctx->pinned_int_dev + kPinnedIntHalf};
       auto head_to = [&](int slot) {
-        launch(pl[0].kind, pl[0].k, pl[0].width, kRoleY, kRoleWA, kRoleNone);
-        launch_fp_test_multi<T2>(s, d_sys, nsys, d_bps, fnorm2, reduce, max_steps, active, steps, rnorm2, d_seg,
-                                 d_segp, flags_dev[slot]);
+        head();
+        launch_fp_test_multi<T2>(s, d_sys, nsys, nblk, ntest, d_bps, fnorm2, reduce, max_steps, active, steps, rnorm2,
+                                 d_seg, flags_dev[slot]);
         HFCI_HIP(hipEventRecord(ev[slot], s));
       };
       head_to(0);
@@ -296,9 +381,9 @@ struct MultiFp {
     }
     for (int it = 1; it <= cap; ++it) {
       if (fixed && it == cap) break;
-      launch(pl[0].kind, pl[0].k, pl[0].width, kRoleY, kRoleWA, kRoleNone);
+      head();
       st.matvecs += nact;
-      launch_fp_check_multi<T2>(s, d_sys, nsys, fnorm2, fixed_steps, reduce, max_steps, active, steps, rnorm2);
+      launch_fp_check_multi<T2>(s, d_sys, nsys, nblk, fnorm2, fixed_steps, reduce, max_steps, active, steps, rnorm2);
       if (!fixed) {
         HFCI_HIP(hipMemcpyAsync(ctx->pinned_int, active, nsys * sizeof(int), hipMemcpyDeviceToHost, s));
         HFCI_HIP(hipStreamSynchronize(s));

@@ -433,6 +433,7 @@ __global__ __launch_bounds__(NT) void build_list_kernel(const int* __restrict__ 
 // system s reduces its own partial row against the norm of its slot's right-hand side.
 template <typename T2>
 __global__ __launch_bounds__(NT) void fp_check_multi_kernel(const MultiSys<T2>* __restrict__ sys,
+                                                            const int* __restrict__ nblk,
                                                             const double* __restrict__ fnorm2, int fixed_steps,
                                                             double inv_reduce2, int max_steps, int* __restrict__ active,
                                                             int* __restrict__ steps, double* __restrict__ rnorm2) {
@@ -441,7 +442,8 @@ __global__ __launch_bounds__(NT) void fp_check_multi_kernel(const MultiSys<T2>* 
   if (active[s] == 0) return;
   const MultiSys<T2> sd = sys[s];
   double v[1] = {0.0};
-  for (int i = threadIdx.x; i < sd.nblk; i += NT) v[0] += sd.partial[i];
+  const int nb = nblk[s];
+  for (int i = threadIdx.x; i < nb; i += NT) v[0] += sd.partial[i];
   block_sum_n<1>(v, sh);
   if (threadIdx.x == 0) {
     const double r2 = v[0];
@@ -458,29 +460,28 @@ __global__ __launch_bounds__(NT) void fp_check_multi_kernel(const MultiSys<T2>* 
 }
 
 // Adaptive stopping test of a batch with the work tables rebuilt on the device (one
-// block): wave w decides systems w, w + 16, ... as fp_check_multi_kernel does; then the
-// active systems, in increasing order, get their rows {first block, system} of the
-// single-factor table (seg, bps[s].x blocks each) and of the pair table (segp, bps[s].y
-// blocks).  Exclusive prefix sums run per chunk of FTT systems: ballots give the row,
-// shuffle scans the first blocks, LDS carries the wave totals.  Row `count` of each table
-// is the sentinel {total blocks, -1}, the rows after it {INT_MAX, -1}: a launch sized for
-// an earlier, larger set of systems searches past the live rows and its surplus blocks
-// land on the sentinel and exit.  The flags also go to host_flags (pinned host memory).
+// block): wave w decides systems w, w + 16, ... as fp_check_multi_kernel does; then wave w
+// writes tables w, w + 16, ...: the active systems, in increasing order, get their rows {first
+// block, system} (bps[t][s] blocks each), 64 systems at a time (a ballot gives the row, a
+// shuffle scan the first block).  The row after them is the sentinel {total blocks, -1}, the
+// rows after it {INT_MAX, -1}: a launch sized for an earlier, larger set of systems searches
+// past the live rows and its surplus blocks land on the sentinel and exit.  The flags also go
+// to host_flags (pinned host memory).
 template <typename T2>
 __global__ __launch_bounds__(FTT) void fp_test_multi_kernel(const MultiSys<T2>* __restrict__ sys, int nsys,
-                                                            const int2* __restrict__ bps,
+                                                            const int* __restrict__ nblk, int ntab,
+                                                            const int* __restrict__ bps,
                                                             const double* __restrict__ fnorm2, double inv_reduce2,
-                                                            int max_steps, int* __restrict__ active,
-                                                            int* __restrict__ steps, double* __restrict__ rnorm2,
-                                                            int2* __restrict__ seg, int2* __restrict__ segp,
+                                                            int max_steps, int* active, int* __restrict__ steps,
+                                                            double* __restrict__ rnorm2, int2* __restrict__ seg,
                                                             int* __restrict__ host_flags) {
-  __shared__ int wtot[3][FTT / 64];
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   for (int s = wid; s < nsys; s += FTT / 64) {
     if (active[s] == 0) continue;  // stopped earlier: its partial row was not written
     const MultiSys<T2>& sd = sys[s];
+    const int nb = nblk[s];
     double v = 0.0;
-    for (int i = lane; i < sd.nblk; i += 64) v += sd.partial[i];
+    for (int i = lane; i < nb; i += 64) v += sd.partial[i];
     v = wave_sum(v);
     if (lane == 0) {
       const double r2 = v;
@@ -492,49 +493,28 @@ __global__ __launch_bounds__(FTT) void fp_test_multi_kernel(const MultiSys<T2>* 
     }
   }
   __syncthreads();
-  int base = 0, bbase = 0, pbase = 0;
-  for (int c0 = 0; c0 < nsys; c0 += FTT) {
-    const int s = c0 + threadIdx.x;
-    const bool a = s < nsys && active[s] != 0;
-    if (s < nsys) host_flags[s] = a ? 1 : 0;
-    const int2 w = a ? bps[s] : make_int2(0, 0);
-    const unsigned long long m = __ballot(a);
-    const int below = __popcll(m & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
-    int ib = w.x, ip = w.y;  // inclusive scans within the wave
+  for (int s = threadIdx.x; s < nsys; s += FTT) host_flags[s] = active[s] != 0 ? 1 : 0;
+  for (int t = wid; t < ntab; t += FTT / 64) {
+    int2* row = seg + (size_t)t * (nsys + 1);
+    const int* blocks = bps + (size_t)t * nsys;
+    int base = 0, first = 0;
+    for (int c0 = 0; c0 < nsys; c0 += 64) {
+      const int s = c0 + lane;
+      const bool a = s < nsys && active[s] != 0;
+      const int w = a ? blocks[s] : 0;
+      const unsigned long long m = __ballot(a);
+      const int below = __popcll(m & ((lane == 0) ? 0ull : (~0ull >> (64 - lane))));
+      int inc = w;  // inclusive scan within the wave
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int tb = __shfl_up(ib, o, 64), tp = __shfl_up(ip, o, 64);
-      if (lane >= o) {
-        ib += tb;
-        ip += tp;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += up;
       }
+      if (a) row[base + below] = make_int2(first + inc - w, s);
+      base += __popcll(m);
+      first += __shfl(inc, 63, 64);
     }
-    if (lane == 63) {
-      wtot[0][wid] = __popcll(m);
-      wtot[1][wid] = ib;
-      wtot[2][wid] = ip;
-    }
-    __syncthreads();
-    int off = base, boff = bbase, poff = pbase;
-    for (int v = 0; v < wid; ++v) {
-      off += wtot[0][v];
-      boff += wtot[1][v];
-      poff += wtot[2][v];
-    }
-    if (a) {
-      seg[off + below] = make_int2(boff + ib - w.x, s);
-      segp[off + below] = make_int2(poff + ip - w.y, s);
-    }
-    for (int v = 0; v < FTT / 64; ++v) {
-      base += wtot[0][v];
-      bbase += wtot[1][v];
-      pbase += wtot[2][v];
-    }
-    __syncthreads();
-  }
-  for (int r = base + threadIdx.x; r <= nsys; r += FTT) {
-    seg[r] = make_int2(r == base ? bbase : INT_MAX, -1);
-    segp[r] = make_int2(r == base ? pbase : INT_MAX, -1);
+    for (int r = base + lane; r <= nsys; r += 64) row[r] = make_int2(r == base ? first : INT_MAX, -1);
   }
 }
 
@@ -710,29 +690,29 @@ void launch_fp_check(hipStream_t st, const double* partial, int nblk, int nsys, 
 }
 
 template <typename T2>
-void launch_fp_check_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const double* fnorm2, int fixed_steps,
-                           double reduce, int max_steps, int* active, int* steps, double* rnorm2) {
+void launch_fp_check_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const int* nblk, const double* fnorm2,
+                           int fixed_steps, double reduce, int max_steps, int* active, int* steps, double* rnorm2) {
   if (nsys > 0)
-    hipLaunchKernelGGL(fp_check_multi_kernel<T2>, dim3(nsys), dim3(NT), 0, st, sys, fnorm2, fixed_steps,
+    hipLaunchKernelGGL(fp_check_multi_kernel<T2>, dim3(nsys), dim3(NT), 0, st, sys, nblk, fnorm2, fixed_steps,
                        1.0 / (reduce * reduce), max_steps, active, steps, rnorm2);
 }
-template void launch_fp_check_multi<float2>(hipStream_t, const MultiSys<float2>*, int, const double*, int, double, int,
-                                            int*, int*, double*);
-template void launch_fp_check_multi<double2>(hipStream_t, const MultiSys<double2>*, int, const double*, int, double,
-                                             int, int*, int*, double*);
+template void launch_fp_check_multi<float2>(hipStream_t, const MultiSys<float2>*, int, const int*, const double*, int,
+                                            double, int, int*, int*, double*);
+template void launch_fp_check_multi<double2>(hipStream_t, const MultiSys<double2>*, int, const int*, const double*, int,
+                                             double, int, int*, int*, double*);
 
 template <typename T2>
-void launch_fp_test_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const int2* bps, const double* fnorm2,
-                          double reduce, int max_steps, int* active, int* steps, double* rnorm2, int2* seg,
-                          int2* segp, int* host_flags) {
+void launch_fp_test_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const int* nblk, int ntab, const int* bps,
+                          const double* fnorm2, double reduce, int max_steps, int* active, int* steps, double* rnorm2,
+                          int2* seg, int* host_flags) {
   if (nsys > 0)
-    hipLaunchKernelGGL(fp_test_multi_kernel<T2>, dim3(1), dim3(FTT), 0, st, sys, nsys, bps, fnorm2,
-                       1.0 / (reduce * reduce), max_steps, active, steps, rnorm2, seg, segp, host_flags);
+    hipLaunchKernelGGL(fp_test_multi_kernel<T2>, dim3(1), dim3(FTT), 0, st, sys, nsys, nblk, ntab, bps, fnorm2,
+                       1.0 / (reduce * reduce), max_steps, active, steps, rnorm2, seg, host_flags);
 }
-template void launch_fp_test_multi<float2>(hipStream_t, const MultiSys<float2>*, int, const int2*, const double*,
-                                           double, int, int*, int*, double*, int2*, int2*, int*);
-template void launch_fp_test_multi<double2>(hipStream_t, const MultiSys<double2>*, int, const int2*, const double*,
-                                            double, int, int*, int*, double*, int2*, int2*, int*);
+template void launch_fp_test_multi<float2>(hipStream_t, const MultiSys<float2>*, int, const int*, int, const int*,
+                                           const double*, double, int, int*, int*, double*, int2*, int*);
+template void launch_fp_test_multi<double2>(hipStream_t, const MultiSys<double2>*, int, const int*, int, const int*,
+                                            const double*, double, int, int*, int*, double*, int2*, int*);
 
 void launch_dfinish(hipStream_t st, const double* sums, int nrhs, double* d) {
   hipLaunchKernelGGL(dfinish_kernel, dim3((nrhs + 63) / 64), dim3(64), 0, st, sums, nrhs, d);

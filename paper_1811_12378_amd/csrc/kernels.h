@@ -13,8 +13,8 @@ namespace hfci {
 // Launch shape of the z-marching stencil kernels: kern 0 keeps the in-plane neighbours
 // as cached global loads, kern 1 stages each plane through LDS; a 64 x ty thread tile,
 // HBM streams prefetched pd planes ahead, z-chunks of cz planes (0: from the grid size);
-// fuse 1 applies the fixed-point factors two per pass (64 x 12 tiles, z-chunks cz; loads
-// one plane ahead, two when pd is 3).
+// fuse 1 applies the fixed-point factors several per pass (kern 0 and 1 in registers, kern 2
+// and 3 two per pass on tiles in LDS).
 struct KernelTune {
   // fuse: 0 one factor per pass, 1 two (the later steps' first and last factors and the
   // middle ones in pairs), 2 (kern 3 only) as 1 with the middle factors in threes where
@@ -202,7 +202,7 @@ struct Launch {
   // whether the fixed-point factors run through factor_rows with the current launch shape
   static bool rows_run(const GridDesc& g);
   static int pair_blocks(const GridDesc& g);  // residual partials per system of a pair launch
-  // whether factor_pair runs on this grid (32-bit byte offsets: each vector under 4 GiB)
+  // whether factor_pair runs: complex64, launch shape kern 2 or 3, a grid that suits them
   static bool pair_fits(const GridDesc& g);
   // partial sums for the step size d: conj(A w).f and |A w|^2, per rhs.
   static void dstep_partials(hipStream_t st, const GridDesc& g, const void* kappa, int nrhs,
@@ -216,8 +216,12 @@ struct MultiInst {
   GridDesc g;
   const void* kappa;  // float* or double*
   int gx, gy, nzc, czlen, xcd_slab, per_sys;
-  // the same for two factors per pass (64 x 12 tiles); pper_sys = 0 where it does not run
-  int pgx, pgy, pnzc, pczlen, pxcd_slab, pper_sys;
+};
+// A multi-factor pass over the systems of many operators: `width` factors in blocks of w waves,
+// the same for every instance (its RowsShape has the tiles and z-chunks), and the kind of the
+// passes it is for: kFacResid, kFacAdd or 0 (neither).
+struct RowsClass {
+  int width = 0, kind = 0, w = 0, small = 0;
 };
 // Per shifted system (instance, pole): its vectors by role (0 f, 1 y, 2 y1, 3 wA, 4 wB),
 // the pole's factor coefficients and constants, its residual-partial row.
@@ -227,8 +231,8 @@ struct MultiSys {
   T2* vec[5];
   const FactorCoef* coef;  // this pole's cstride coefficients
   const PoleDev* pole;
-  double* partial;         // nblk doubles
-  int inst, nblk, slot, pad;
+  double* partial;         // room for the blocks of any launch that forms residuals
+  int inst, slot;
 };
 // One factor launch over the systems listed in the work table seg[i] = {first block,
 // system}, ascending in the first block; a block finds its system by binary search over
@@ -239,26 +243,31 @@ struct MultiLaunch {
   static void factor(hipStream_t st, const MultiInst* inst, const MultiSys<T2>* sys, const int2* seg, int nseg,
                      int nblocks, int kind, int role_in, int role_out, int role_out2, int k, int cstride,
                      bool f64);
-  // factors k and k + 1 in one pass over the work table of pair tiles (kind as for
-  // Launch::factor_pair); false for an unsupported kind
-  static bool factor_pair(hipStream_t st, const MultiInst* inst, const MultiSys<T2>* sys, const int2* seg, int nseg,
-                          int nblocks, int kind, int role_in, int role_out, int role_out2, int k, int cstride);
+  // c.width factors from k in one pass (kind as for Launch::factor_rows), shapes (device): the
+  // geometry of each instance; false for an unsupported kind or width
+  static bool factor_rows(hipStream_t st, const RowsClass& c, const MultiInst* inst, const RowsShape* shapes,
+                          const MultiSys<T2>* sys, const int2* seg, int nseg, int nblocks, int kind, int role_in,
+                          int role_out, int role_out2, int k, int cstride);
+  // the block size, and the geometry per instance, of a pass over systems[i] systems (an
+  // expected number, not necessarily whole) of grid g[i]
+  static RowsClass rows_class(const std::vector<GridDesc>& g, const std::vector<double>& systems, int width, int kind,
+                              std::vector<RowsShape>& shapes);
   // geometry of one instance for this launch shape (host)
   static MultiInst describe(const GridDesc& g, const void* kappa);
 };
 // fixed-point bookkeeping of a batch: per system s, its partial row (sys[s].partial,
-// sys[s].nblk) against fnorm2[sys[s].slot]
+// nblk[s] entries) against fnorm2[sys[s].slot]
 template <typename T2>
-void launch_fp_check_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const double* fnorm2,
+void launch_fp_check_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const int* nblk, const double* fnorm2,
                            int fixed_steps, double reduce, int max_steps, int* active, int* steps, double* rnorm2);
-// adaptive test of a batch that also rebuilds the work tables on the device: rows
-// {first block, system} of the active systems in seg (bps[s].x blocks each) and segp
-// (bps[s].y), then the sentinel {total, -1} and {INT_MAX, -1} up to row nsys; the flags
-// also go to host_flags (device-visible pinned host memory, nsys ints)
+// adaptive test of a batch that also rebuilds the work tables on the device: table t < ntab
+// (rows seg + t (nsys + 1), bps[t nsys + s] blocks of system s) gets rows {first block, system}
+// of the active systems, then the sentinel {total, -1} and {INT_MAX, -1} up to row nsys; the
+// flags also go to host_flags (device-visible pinned host memory, nsys ints)
 template <typename T2>
-void launch_fp_test_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const int2* bps, const double* fnorm2,
-                          double reduce, int max_steps, int* active, int* steps, double* rnorm2, int2* seg,
-                          int2* segp, int* host_flags);
+void launch_fp_test_multi(hipStream_t st, const MultiSys<T2>* sys, int nsys, const int* nblk, int ntab, const int* bps,
+                          const double* fnorm2, double reduce, int max_steps, int* active, int* steps, double* rnorm2,
+                          int2* seg, int* host_flags);
 
 // FP64 residual r = b - A u (shift 0) with partial sums of |r|^2.
 void launch_residual64(hipStream_t st, const GridDesc& g, const double* kappa, const double2* b,

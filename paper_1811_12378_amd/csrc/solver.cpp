@@ -91,8 +91,8 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
     // residual partials come from the first launch of a step: a multi-factor launch when
     // fusing.  Its geometry, and so the partials per system, depends on the systems still
     // iterating; in a fixed arena it keeps to the partials of the tile kernels.
-    const int tile_blk = (tn.fuse != 0 && Launch<T2>::pair_fits(op.g) && q >= 3) ? Launch<T2>::pair_blocks(op.g)
-                                                                                  : Launch<T2>::partial_blocks(op.g);
+    const int tile_blk = (tn.fuse != 0 && fuse && q >= 3) ? Launch<T2>::pair_blocks(op.g)
+                                                          : Launch<T2>::partial_blocks(op.g);
     const int max_blk = (rows && q >= 3 && ctx.ws.arena_set()) ? tile_blk : 0;
     int nblk = tile_blk, nblk_cap = tile_blk;
     struct Part {
@@ -495,21 +495,20 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
     for (int pd : {1, 2, 3}) cands.push_back(KernelTune{1, 4, pd, cz, 0});
     for (int pd : {2, 3}) cands.push_back(KernelTune{1, 8, pd, cz, 0});
   }
-  // two factors per pass (its own 64 x 12 tiles; per-factor time = half a launch), with
-  // the systems of a launch taken one, two or four at a time tile by tile
-  // (kern 2: the complex64 pair kernel whose streams are loaded straight into LDS; kern 3:
-  // the same with 64 x 28 tiles for the middle pairs, two planes ahead only)
-  if (Launch<T2>::pair_fits(op.g))
-    for (int kern : {1, 2, 3}) {
-      if (kern >= 2 && sizeof(T2) != 8) continue;
-      for (int cz : {0, 16, 64})
-        for (int pd : {2, 3})
-          for (int sg : {1, 2, 4})
-            if ((sg == 1 || sg <= nsys) && !((kern == 3 || kern == 1) && pd != 2))
-              cands.push_back(KernelTune{kern, 8, pd, cz, 1, sg});
-    }
+  // several factors per pass (per-factor time = a launch over its factors), with the systems
+  // of a launch taken one, two or four at a time tile by tile: kern 1 in registers; kern 2 the
+  // complex64 pairs whose streams are loaded straight into LDS; kern 3 the same with 64 x 28
+  // tiles for the middle pairs, two planes ahead only
+  for (int kern : {1, 2, 3}) {
+    if (kern >= 2 ? sizeof(T2) != 8 || !streams_fit(op.g) : !Launch<T2>::rows_fits(op.g)) continue;
+    for (int cz : {0, 16, 64})
+      for (int pd : {2, 3})
+        for (int sg : {1, 2, 4})
+          if ((sg == 1 || sg <= nsys) && !((kern == 3 || kern == 1) && pd != 2))
+            cands.push_back(KernelTune{kern, 8, pd, cz, 1, sg});
+  }
   // three middle factors per pass (kern 3, fuse 2; per-factor time = a third of a launch)
-  if (sizeof(T2) == 8 && Launch<T2>::pair_fits(op.g))
+  if (sizeof(T2) == 8 && streams_fit(op.g))
     for (int cz : {0, 16, 64})
       for (int sg : {1, 2, 4})
         if (sg == 1 || sg <= nsys) cands.push_back(KernelTune{3, 8, 2, cz, 2, sg});

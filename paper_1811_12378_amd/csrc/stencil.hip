@@ -330,331 +330,26 @@ __global__ __launch_bounds__(TX * TY) void zlds_kernel(GridDesc g, int nzc, int 
 // in an SGPR.  Callers keep every access inside the buffer.
 using BufRsrc = __amdgpu_buffer_rsrc_t;
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ BufRsrc buf_rsrc(const void* p) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)0xffffffff, 0x00020000);
-}
-template <typename V>
-__device__ __forceinline__ V buf_load(const BufRsrc& r, uint32_t voff, uint32_t soff);
-template <>
-__device__ __forceinline__ float buf_load<float>(const BufRsrc& r, uint32_t voff, uint32_t soff) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
-}
-template <>
-__device__ __forceinline__ double buf_load<double>(const BufRsrc& r, uint32_t voff, uint32_t soff) {
-  const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
-  return __hiloint2double((int)v.y, (int)v.x);
-}
-template <>
-__device__ __forceinline__ float2 buf_load<float2>(const BufRsrc& r, uint32_t voff, uint32_t soff) {
-  const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
-  return float2{__uint_as_float(v.x), __uint_as_float(v.y)};
-}
-template <>
-__device__ __forceinline__ double2 buf_load<double2>(const BufRsrc& r, uint32_t voff, uint32_t soff) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0);
-  return double2{__hiloint2double((int)v.y, (int)v.x), __hiloint2double((int)v.w, (int)v.z)};
-}
-template <typename V>
-__device__ __forceinline__ void buf_store(const BufRsrc& r, uint32_t voff, uint32_t soff, const V& x);
-template <>
-__device__ __forceinline__ void buf_store<float2>(const BufRsrc& r, uint32_t voff, uint32_t soff, const float2& x) {
+__device__ __forceinline__ void buf_store(const BufRsrc& r, uint32_t voff, uint32_t soff, const float2& x) {
   const u32x2 v = {__float_as_uint(x.x), __float_as_uint(x.y)};
   __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, 0);
-}
-template <>
-__device__ __forceinline__ void buf_store<double2>(const BufRsrc& r, uint32_t voff, uint32_t soff, const double2& x) {
-  const unsigned long long lx = (unsigned long long)__double_as_longlong(x.x);
-  const unsigned long long ly = (unsigned long long)__double_as_longlong(x.y);
-  const u32x4 v = {(unsigned)lx, (unsigned)(lx >> 32), (unsigned)ly, (unsigned)(ly >> 32)};
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, soff, 0);
 }
 
 // Two consecutive factors of the fixed-point step in one pass (temporal blocking):
 //   t = a1 (A - z0) w + b1 w,   out = a2 (A - z0) t + b2 t  [+ y1].
-// A block owns a 64 x 12 output tile and a z-chunk.  Per plane k it stages the input
-// plane k+1 on the 68 x 16 tile (two-point halo) in a 4-plane LDS ring and, after one
-// barrier, computes the second factor at plane k-2 on the 64 x 12 core from the
-// first-factor ring, then the first factor at plane k on the 66 x 14 tile (one-point
-// halo; zeros outside the grid, the Dirichlet ghosts of the intermediate vector) into
-// that 4-plane ring.  Four slots per ring let one barrier per plane order every write
-// against every read of the same slot.  One thread per first-factor point (924 of
-// 960); global loads run D planes ahead (D = 2 when the shape's prefetch depth pd is
-// 3, else 1).
 // kFacResid / kFacInF select the first factor's input (y with the residual partials,
-// or f); kFacAdd / kFacDual the second factor's epilogue.
-//
-// The loop body is written for the scalar unit as much as for the vector unit (one
-// scalar ALU serves the four SIMDs of a CU): the plane loop is unrolled four times and
-// the ring slots count from the chunk's first plane, so every slot is a compile-time
-// constant; the first factor and the residual are computed by every lane and masked
-// (no divergent branch), and lanes without a tile entry of their own write to LDS
-// padding; every global load is issued unconditionally from an in-bounds address and
-// masked where it is consumed, so no load sits under a divergent branch (which would
-// make the compiler's wait counts assume it might not have been issued, and wait for
-// every load in flight).
+// or f); kFacAdd / kFacDual the second factor's epilogue.  The tiles of kern 2:
 constexpr int PX = 64, PY = 12;                 // output tile
 constexpr int PEX = PX + 2, PEY = PY + 2;       // first-factor tile
 constexpr int PIX = PX + 4, PIY = PY + 4;       // input tile
 constexpr int PNT = 960;                        // 15 waves >= PEX * PEY = 924
 constexpr int NIN = PIX * PIY;                  // 1088 input-tile entries
-constexpr int NINP = NIN + 64;                  // plus a write-only pad for lanes without an entry
-
-template <typename T2, typename T>
-struct PairRec {
-  T2 in[2];  // the thread's two entries of the 68 x 16 input tile
-  T kap;
-  T2 fv, y1;
-};
-
-// Two blocks per CU need eight waves per SIMD, i.e. at most 64 VGPRs: asked of the
-// complex64 kernels whose registers fit without spilling (not the residual or the y1
-// epilogue, which keep more per-point values in flight).
-template <typename T, int KIND>
-constexpr int pair_waves_per_eu() {
-  return (sizeof(T) == 4 && (KIND & (kFacResid | kFacAdd)) == 0) ? 8 : 1;
-}
-
-// The work of one block: tile b (of the gx x gy x nzc pair tiles of a system, per_sys in
-// all) of system s of the factor arguments.
-template <typename T, int KIND, int D>
-__device__ __forceinline__ void pair_tile(const GridDesc& g, int czlen, int gx, int gy, int per_sys, int s, int b,
-                                          const FactorArgs<typename V2<T>::t>& a, const T* __restrict__ K) {
-  using T2 = typename V2<T>::t;
-  constexpr bool RESID = (KIND & kFacResid) != 0, ADD = (KIND & kFacAdd) != 0, DUAL = (KIND & kFacDual) != 0,
-                 INF = (KIND & kFacInF) != 0;
-  static_assert(D == 1 || D == 2, "prefetch depth 1 or 2");
-  __shared__ T2 inr[4][NINP];  // input planes, [row][col] flattened as row * PIX + col
-  __shared__ T2 tr[4][PNT];    // first-factor planes, [row][col] as row * PEX + col (= tid)
-  __shared__ double sh[PNT / 64];
-  const int tid = threadIdx.x;
-  const int bx = b % gx, by = (b / gx) % gy, zc = b / (gx * gy);
-  const int x0 = bx * PX, y0 = by * PY;
-  const int zb = zc * czlen, ze = min(g.nz, zb + czlen);
-  const size_t n = (size_t)g.nx * g.ny * g.nz;
-  const size_t plane = (size_t)g.nx * (size_t)g.ny;
-  const int gs = a.sys0 + s;
-  const int pole = gs / a.nrhs, rhs = gs % a.nrhs;
-  const FactorCoef c1 = a.coef[pole * a.cstride + a.k], c2 = a.coef[pole * a.cstride + a.k + 1];
-  const PoleDev pd = a.poles[pole];
-  const T a1r = (T)c1.a_re, a1i = (T)c1.a_im, b1r = (T)c1.b_re, b1i = (T)c1.b_im;
-  const T a2r = (T)c2.a_re, a2i = (T)c2.a_im, b2r = (T)c2.b_re, b2i = (T)c2.b_im;
-  const T2* __restrict__ X = INF ? a.f + (size_t)rhs * n : a.win + (size_t)s * n;
-  const T2* __restrict__ F = a.f + (size_t)rhs * n;
-  const T2* __restrict__ Y1 = a.y1 + (size_t)s * n;
-  T2* __restrict__ O = a.wout + (size_t)s * n;
-  T2* __restrict__ O2 = DUAL ? a.wout2 + (size_t)s * n : nullptr;
-  const T sh2 = (T)g.s_h2, dsc = (T)g.damp_scale;
-  const T diag0 = (T)6 * sh2 - (T)pd.z0_re, sim = (T)pd.z0_im;
-  const double zzr = pd.zz_re, zzi = pd.zz_im;
-
-  // Addresses: raw buffer accesses with a uniform plane offset (scalar) and a 32-bit
-  // per-lane byte offset (every vector is under 4 GiB when this kernel runs), so each
-  // lane keeps one 32-bit offset per stream and the plane advance is scalar work.
-  const uint32_t pb = (uint32_t)(plane * sizeof(T2)), pbk = (uint32_t)(plane * sizeof(T));
-  auto clampz = [&](int kp) { return (uint32_t)min(max(kp, 0), g.nz - 1); };
-  const BufRsrc rX = buf_rsrc(X), rK = buf_rsrc(K), rF = buf_rsrc(F), rY1 = buf_rsrc(Y1), rO = buf_rsrc(O),
-                rO2 = buf_rsrc(O2);
-  auto ld = [](const BufRsrc& r, uint32_t uoff, uint32_t loff) { return buf_load<T2>(r, loff, uoff); };
-
-  // input-tile duty: entries tid and tid + PNT of the 68 x 16 tile (the second only for
-  // the first 128 lanes; the others write it to the pad)
-  bool in_ok[2];
-  uint32_t in_b[2];
-  int in_idx[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = tid + h * PNT;
-    const int ix = x0 - 2 + i % PIX, iy = y0 - 2 + i / PIX;
-    in_ok[h] = i < NIN && ix >= 0 && ix < g.nx && iy >= 0 && iy < g.ny;
-    in_b[h] = in_ok[h] ? (uint32_t)((ix + g.nx * iy) * sizeof(T2)) : 0u;
-    in_idx[h] = i < NIN ? i : NIN + (tid & 63);
-  }
-  // first-factor point of this thread (66 x 14 tile) and whether it is an output point;
-  // lanes past the tile read the tile's last row and are masked
-  const bool tthr = tid < PEX * PEY;
-  const int ex = tid % PEX, ey = min(tid / PEX, PEY - 1);
-  const int xe = x0 - 1 + ex, ye = y0 - 1 + ey;
-  const bool ine = tthr && xe >= 0 && xe < g.nx && ye >= 0 && ye < g.ny;
-  const bool core = ine && ex >= 1 && ex <= PX && ey >= 1 && ey <= PY;
-  const uint32_t oe = ine ? (uint32_t)(xe + g.nx * ye) : 0u;
-  const uint32_t oe_b = oe * (uint32_t)sizeof(T2), oe_k = oe * (uint32_t)sizeof(T);
-  // per-point vectors (f, y1) are read at the nearest output point of the tile, so the
-  // lanes of the halo ring fetch no cache line the core does not
-  const int xc = min(max(xe, x0), min(x0 + PX, g.nx) - 1), yc = min(max(ye, y0), min(y0 + PY, g.ny) - 1);
-  const uint32_t oc_b = (uint32_t)((xc + g.nx * yc) * sizeof(T2));
-  // second-factor neighbours in the first-factor ring, clamped into the tile for the
-  // lanes that are not output points (their result is not stored)
-  const int fx = min(max(ex, 1), PX), fy = min(max(ey, 1), PY);
-  const int fc = fy * PEX + fx;
-  // damping: dsc * max(dxy, dz)^2 = max(dsc dxy^2, dsc dz^2) (both depths >= 0)
-  const int dxy = max(layer_depth(xe, g.nx, g.damp_cells), layer_depth(ye, g.ny, g.damp_cells));
-  const T dampxy = (T)(dxy * dxy) * dsc;
-  auto dampz = [&](int k) {
-    const int dz = layer_depth(k, g.nz, g.damp_cells);
-    return (T)(dz * dz) * dsc;
-  };
-
-  auto load_in = [&](int kp, T2 (&r)[2]) {
-    const uint32_t off = pb * clampz(kp);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) r[h] = ld(rX, off, in_b[h]);
-  };
-  // ring slot of input plane kp is (kp - zb + 2) mod 4, of first-factor plane kp is
-  // (kp - zb + 1) mod 4: compile-time constants in the four-times unrolled loop
-  auto store_in = [&](int kp, int slot, const T2 (&r)[2]) {
-    const bool kin = kp >= 0 && kp < g.nz;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) inr[slot][in_idx[h]] = (kin && in_ok[h]) ? r[h] : T2{(T)0, (T)0};
-  };
-  // record of iteration k: input plane k+1, kappa at plane k (first factor), f at plane
-  // k (residual of the first factor), y1 at plane k-2 (second factor's epilogue); kappa,
-  // f and y1 are used only at points and planes where they were read in bounds
-  auto load_rec = [&](int k, PairRec<T2, T>& r) {
-    load_in(k + 1, r.in);
-    const uint32_t ck = clampz(k);
-    r.kap = buf_load<T>(rK, oe_k, pbk * ck);
-    if constexpr (RESID) r.fv = ld(rF, pb * ck, oc_b);
-    if constexpr (ADD) r.y1 = ld(rY1, pb * clampz(k - 2), oc_b);
-  };
-
-  double acc = 0.0;
-  if (zb < ze) {
-    {
-      T2 r[2];
-      load_in(zb - 2, r);
-      store_in(zb - 2, 0, r);
-      load_in(zb - 1, r);
-      store_in(zb - 1, 1, r);
-    }
-    // records are issued D iterations ahead into a queue of four register slots indexed
-    // by the iteration modulo 4: the queue rotates by renaming, so no register with a
-    // load in flight is ever copied and the loads stay in flight across the plane's
-    // barrier and stores
-    PairRec<T2, T> q[4];
-#pragma unroll
-    for (int d = 0; d < D; ++d) load_rec(zb - 1 + d, q[d]);
-    T k1 = (T)0, k2 = (T)0;  // kappa at planes k-1, k-2 (kept when two records are in flight)
-    const int len = ze - zb + 3;  // iterations k = zb-1 .. ze+1
-    for (int r0 = 0; r0 < len; r0 += 4) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (r0 + u < len) {
-          const int k = zb - 1 + r0 + u;
-          load_rec(k + D, q[(u + D) % 4]);
-          const PairRec<T2, T>& rc = q[u];
-          // input slots: plane k-1 -> u, k -> u+1, k+1 -> u+2; first-factor slots:
-          // plane k-3 -> u+1, k-2 -> u+2, k-1 -> u+3, k -> u (all mod 4).  The one barrier
-          // publishes input plane k+1 and first-factor plane k-1.  The input slot u+2
-          // written before it is not one the previous iteration's first factor reads
-          // (u-1, u, u+1), and the first-factor slot u written after it is not one this
-          // iteration's second factor reads (u+1, u+2, u+3): a barrier separates every
-          // write from every read of the same slot.
-          store_in(k + 1, (u + 2) % 4, rc.in);
-          __syncthreads();
-          // second factor at plane k-2 on the 64 x 12 core
-          {
-            const int km = k - 2;
-            const T2* cq = tr[(u + 2) % 4];
-            const T2 cen2 = cq[fc];
-            const T2 xm2 = cq[fc - 1], xp2 = cq[fc + 1], ym2 = cq[fc - PEX], yp2 = cq[fc + PEX];
-            const T2 zm2 = tr[(u + 1) % 4][fc], zp2 = tr[(u + 3) % 4][fc];
-            // kappa at plane k-2: with one record in flight its slot is still intact
-            const T dre2 = diag0 - (D == 1 ? q[(u + 2) % 4].kap : k2);
-            const T dim2 = -(max(dampxy, dampz(km)) + sim);
-            const T nbr2 = ((zm2.x + zp2.x) + (xm2.x + xp2.x)) + (ym2.x + yp2.x);
-            const T nbi2 = ((zm2.y + zp2.y) + (xm2.y + xp2.y)) + (ym2.y + yp2.y);
-            T2 S2;
-            S2.x = dre2 * cen2.x - dim2 * cen2.y - sh2 * nbr2;
-            S2.y = dre2 * cen2.y + dim2 * cen2.x - sh2 * nbi2;
-            T2 o;
-            o.x = a2r * S2.x - a2i * S2.y + b2r * cen2.x - b2i * cen2.y;
-            o.y = a2r * S2.y + a2i * S2.x + b2r * cen2.y + b2i * cen2.x;
-            if constexpr (ADD) {
-              o.x += rc.y1.x;
-              o.y += rc.y1.y;
-            }
-            if (core && km >= zb && km < ze) {
-              const uint32_t po = pb * (uint32_t)km;
-              buf_store<T2>(rO, oe_b, po, o);
-              if constexpr (DUAL) buf_store<T2>(rO2, oe_b, po, o);
-            }
-          }
-          // first factor at plane k on the 66 x 14 tile (every lane; masked)
-          {
-            const T2* cp = inr[(u + 1) % 4];
-            const int c0 = (ey + 1) * PIX + ex + 1;
-            const T2 cen = cp[c0];
-            const T2 xm = cp[c0 - 1], xp = cp[c0 + 1], ym = cp[c0 - PIX], yp = cp[c0 + PIX];
-            const T2 zm = inr[u][c0], zp = inr[(u + 2) % 4][c0];
-            const T dre = diag0 - rc.kap;
-            const T dim = -(max(dampxy, dampz(k)) + sim);
-            const T nbr = ((zm.x + zp.x) + (xm.x + xp.x)) + (ym.x + yp.x);
-            const T nbi = ((zm.y + zp.y) + (xm.y + xp.y)) + (ym.y + yp.y);
-            T2 Sx;
-            Sx.x = dre * cen.x - dim * cen.y - sh2 * nbr;
-            Sx.y = dre * cen.y + dim * cen.x - sh2 * nbi;
-            const bool live = ine && k >= 0 && k < g.nz;
-            T2 tv;
-            tv.x = live ? a1r * Sx.x - a1i * Sx.y + b1r * cen.x - b1i * cen.y : (T)0;
-            tv.y = live ? a1r * Sx.y + a1i * Sx.x + b1r * cen.y + b1i * cen.x : (T)0;
-            if constexpr (RESID) {
-              const double rr = (double)rc.fv.x - (double)Sx.x + zzr * (double)cen.x - zzi * (double)cen.y;
-              const double ri = (double)rc.fv.y - (double)Sx.y + zzr * (double)cen.y + zzi * (double)cen.x;
-              acc += (core && k >= zb && k < ze) ? rr * rr + ri * ri : 0.0;
-            }
-            tr[u][tid] = tv;
-            k2 = k1;
-            k1 = rc.kap;
-          }
-        }
-      }
-    }
-  }
-  if constexpr (RESID) {
-    double v[1] = {acc};
-    block_sum<PNT, 1>(v, sh);
-    if (tid == 0) a.partial[(size_t)s * per_sys + (bx + gx * (by + gy * zc))] = v[0];
-  }
-}
-
-// Block order.  Workgroups are dispatched round-robin over the 8 XCDs, so workgroup w
-// runs on XCD w % 8 as the (w / 8)-th of that XCD.  With XCD slabs (xcd_slab > 0: a
-// system's tiles split into 8 contiguous slabs, one per XCD) each XCD walks its slab of
-// every listed system, and y/z neighbours of a tile meet in that XCD's L2.  With
-// sgrp > 1 the listed systems go sgrp at a time, tile by tile: an XCD runs tile t of
-// systems s0 .. s0+sgrp-1 back to back, then tile t+1, so kappa of a tile comes from
-// HBM once per group instead of once per system, while neighbouring tiles of one
-// system still run close together.  The last group may hold fewer systems.
-template <typename T, int KIND, int D>
-__global__ __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(pair_waves_per_eu<T, KIND>()))) void zpair_kernel(GridDesc g, int nzc, int czlen, int xcd_slab,
-                                                    int sgrp, FactorArgs<typename V2<T>::t> a, const T* __restrict__ K) {
-  const int gx = (g.nx + PX - 1) / PX, gy = (g.ny + PY - 1) / PY;
-  const int per_sys = gx * gy * nzc;
-  int li, b;  // index into the active list, tile of that system
-  if (xcd_slab > 0 && sgrp > 1) {
-    const int xcd = blockIdx.x % 8, k = blockIdx.x / 8;  // k < count * xcd_slab
-    const int gsz = sgrp * xcd_slab;
-    const int s0 = (k / gsz) * sgrp, r = k % gsz;
-    const int gs = min(sgrp, a.count - s0);
-    li = s0 + r % gs;
-    b = xcd * xcd_slab + r / gs;
-  } else {
-    li = blockIdx.x / per_sys;
-    b = blockIdx.x % per_sys;
-    if (xcd_slab > 0) b = (b % 8) * xcd_slab + b / 8;
-  }
-  const int s = a.list[li];
-  if (s < 0) return;  // a stopped system past the end of the active list (uniform)
-  pair_tile<T, KIND, D>(g, czlen, gx, gy, per_sys, s, b, a, K);
-}
 
 // ---- Two factors per pass with the HBM streams loaded straight into LDS (kern 2) ----
 //
-// The same two factors and the same 64 x 12 tiles, 66 x 14 first-factor tile and 68 x 16
-// input tile as zpair_kernel, with the same arithmetic per point (results equal
-// zpair_kernel's bit for bit), but every stream reaches LDS without passing through
-// registers:
+// 64 x 12 output tiles, the first factor on 66 x 14 and the input on 68 x 16 (zeros outside
+// the grid, the Dirichlet ghosts of the intermediate vector), one thread per first-factor
+// point (924 of 960); every stream reaches LDS without passing through registers:
 //   * each input plane goes to LDS by buffer-to-LDS loads, two complex values (16 bytes)
 //     per lane, 37 pairs per wave; kappa of the first-factor tile likewise, one value per
 //     lane (lane = tile entry); f (the residual kind) or y1 (the kind that adds it) at the
@@ -814,8 +509,8 @@ __device__ __forceinline__ void dma_step(const DmaTile& d, int k, unsigned char*
     }
     const uint32_t voff = (km >= d.zb && km < d.ze) ? d.ost : kOOB;
     const uint32_t po = __builtin_amdgcn_readfirstlane(d.pb * clampz(km));
-    buf_store<T2>(d.rO, voff, po, o);
-    if constexpr (DUAL) buf_store<T2>(d.rO2, voff, po, o);
+    buf_store(d.rO, voff, po, o);
+    if constexpr (DUAL) buf_store(d.rO2, voff, po, o);
   }
   cm = cen;
   cc = zp;
@@ -907,7 +602,7 @@ __device__ __forceinline__ void pair_tile_dma(const GridDesc& g, int czlen, int 
     if (d.elane && cy < PY && x0 + cx < g.nx && y0 + cy < g.ny)
       d.dex = (uint32_t)((x0 + cx + g.nx * (y0 + cy)) * sizeof(T2));
   }
-  // the thread's first-factor point (66 x 14 tile, as in zpair_kernel), also its kappa entry
+  // the thread's first-factor point (66 x 14 tile), also its kappa entry
   const bool tthr = tid < PEX * PEY;
   const int ex = tid % PEX, ey = min(tid / PEX, PEY - 1);
   const int xe = x0 - 1 + ex, ye = y0 - 1 + ey;
@@ -978,7 +673,8 @@ __device__ __forceinline__ void pair_tile_dma(const GridDesc& g, int czlen, int 
   }
 }
 
-// Block order shared by both pair kernels (see zpair_kernel).
+// Block order of the multi-factor kernels: each XCD walks a contiguous slab of a system's
+// tiles, sgrp systems at a time tile by tile.
 __device__ __forceinline__ bool pair_block(int xcd_slab, int sgrp, int per_sys, const int* list, int count, int& s,
                                            int& b) {
   int li;
@@ -1145,8 +841,8 @@ __device__ __forceinline__ void qstep(const QTile& d, int k, unsigned char* __re
     o.x = d.a2r * S2.x - d.a2i * S2.y + d.b2r * cen2.x - d.b2i * cen2.y;
     o.y = d.a2r * S2.y + d.a2i * S2.x + d.b2r * cen2.y + d.b2i * cen2.x;
     const uint32_t voff = zok ? d.ost[h] : kOOB;
-    buf_store<T2>(d.rO, voff, po, o);
-    if constexpr (DUAL) buf_store<T2>(d.rO2, voff, po, o);
+    buf_store(d.rO, voff, po, o);
+    if constexpr (DUAL) buf_store(d.rO2, voff, po, o);
     tm[h] = t0[h];
     t0[h] = tv[h];
   }
@@ -1451,7 +1147,7 @@ __device__ __forceinline__ void tstep(const TTile& d, int k, unsigned char* __re
       o = tfactor(d.f3, ka2[h], da2[h], u0[h], um[h], uv[h], r2[e - 1], r2[e + 1], r2[e - G::EX], r2[e + G::EX]);
     // the store is issued by every wave (out of range where skipped or outside the core):
     // the plane's wait counts V memory instructions per wave
-    buf_store<T2>(d.rO, (zok && !d.skip3[h]) ? d.ost[h] : kOOB, po, o);
+    buf_store(d.rO, (zok && !d.skip3[h]) ? d.ost[h] : kOOB, po, o);
     um[h] = u0[h];
     u0[h] = uv[h];
     ka2[h] = ka1[h];
@@ -1608,44 +1304,6 @@ __global__ __launch_bounds__(Trip<kTripQH>::NT) __attribute__((amdgpu_waves_per_
   int s, b;
   if (!pair_block(xcd_slab, sgrp, per_sys, a.list, a.count, s, b)) return;  // uniform
   trip_tile<kTripQH>(g, czlen, gx, gy, s, b, a, K);
-}
-
-// Uneven batches, two factors per pass: as zmulti_kernel, with the pair tile of the
-// block's system on its operator's pair geometry (pgx x pgy x pnzc tiles).
-template <typename T, int KIND>
-__global__ __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(pair_waves_per_eu<T, KIND>()))) void zmulti_pair_kernel(
-    const MultiInst* __restrict__ inst, const MultiSys<typename V2<T>::t>* __restrict__ sys,
-    const int2* __restrict__ seg, int nseg, int rin, int rout, int rout2, int k, int cstride) {
-  using T2 = typename V2<T>::t;
-  const int blk = blockIdx.x;
-  int lo = 0, hi = nseg - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (seg[mid].x <= blk) lo = mid;
-    else hi = mid - 1;
-  }
-  const int G = seg[lo].y;
-  if (G < 0) return;  // past the live rows of a table rebuilt since the launch was sized
-  int local = blk - seg[lo].x;
-  const MultiSys<T2>* __restrict__ sd = sys + G;
-  const MultiInst id = inst[sd->inst];
-  if (id.pxcd_slab > 0) local = (local % 8) * id.pxcd_slab + local / 8;
-  FactorArgs<T2> a{};
-  a.win = sd->vec[rin];
-  a.f = sd->vec[kRoleF];
-  a.y1 = sd->vec[kRoleY1];
-  a.wout = sd->vec[rout];
-  a.wout2 = rout2 >= 0 ? sd->vec[rout2] : nullptr;
-  a.coef = sd->coef;
-  a.poles = sd->pole;
-  a.list = nullptr;
-  a.partial = sd->partial;
-  a.count = 1;
-  a.sys0 = 0;
-  a.nrhs = 1;
-  a.cstride = cstride;
-  a.k = k;
-  pair_tile<T, KIND, 1>(id.g, id.pczlen, id.pgx, id.pgy, id.pper_sys, 0, local, a, (const T*)id.kappa);
 }
 
 struct NoAux {};
@@ -1967,8 +1625,6 @@ struct PairShape {
   int gx, gy, nzc, czlen, per_sys, xcd_slab;
 };
 
-bool dma_pair_fits(const GridDesc& g) { return streams_fit(g); }
-
 template <typename T>
 PairShape pair_shape(const GridDesc& g) {
   const KernelTune& t = tune_of<T>(g);
@@ -2023,46 +1679,30 @@ PairShape trip_shape(const GridDesc& g, int cz) {
   return p;
 }
 
-template <typename T, int KIND, typename T2>
-void run_pair(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<T2>& a) {
+template <int KIND>
+void run_pair(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<float2>& a) {
   if (a.count <= 0) return;
-  const int sgrp = tune_of<T>(g).sg;
-  if constexpr (sizeof(T) == 4) {
-    // kern 3: the pairs without an extra stream on tall tiles (complex64, an even nx,
-    // vectors under 2 GiB); the residual and y1 pairs as kern 2
-    if constexpr ((KIND & (kFacResid | kFacAdd)) == 0) {
-      if (tune_of<T>(g).kern == 3 && dma_pair_fits(g)) {
-        const PairShape q = tall_shape<kTallQH>(g, tune_of<T>(g).cz);
-        hipLaunchKernelGGL((zpair_tall_kernel<KIND>), dim3((unsigned)q.per_sys * (unsigned)a.count),
-                           dim3(Tall<kTallQH>::NT), 0, st, g, q.nzc, q.czlen, q.xcd_slab, sgrp, a,
-                           (const float*)kappa);
-        return;
-      }
-    }
-  }
-  const PairShape p = pair_shape<T>(g);
-  const dim3 grid((unsigned)p.per_sys * (unsigned)a.count);
-  if constexpr (sizeof(T) == 4) {
-    // the streams-into-LDS pair kernel: complex64, an even nx, vectors under 2 GiB (with
-    // kern 3, the residual and y1 pairs)
-    if ((tune_of<T>(g).kern == 2 || tune_of<T>(g).kern == 3) && dma_pair_fits(g)) {
-      // prefetch depth P (planes ahead): pd 2 -> 2 (the kinds without an extra stream then
-      // fit two blocks per CU), pd 3 -> 4 (one block per CU)
-      if (tune_of<T>(g).pd >= 3)
-        hipLaunchKernelGGL((zpair_dma_kernel<KIND, 4>), grid, dim3(PNT), 0, st, g, p.nzc, p.czlen, p.xcd_slab,
-                           sgrp, a, (const float*)kappa);
-      else
-        hipLaunchKernelGGL((zpair_dma_kernel<KIND, 2>), grid, dim3(PNT), 0, st, g, p.nzc, p.czlen, p.xcd_slab,
-                           sgrp, a, (const float*)kappa);
+  const KernelTune& t = g.tune32;
+  // kern 3: the pairs without an extra stream on tall tiles; the residual and y1 pairs as
+  // kern 2
+  if constexpr ((KIND & (kFacResid | kFacAdd)) == 0) {
+    if (t.kern == 3) {
+      const PairShape q = tall_shape<kTallQH>(g, t.cz);
+      hipLaunchKernelGGL((zpair_tall_kernel<KIND>), dim3((unsigned)q.per_sys * (unsigned)a.count),
+                         dim3(Tall<kTallQH>::NT), 0, st, g, q.nzc, q.czlen, q.xcd_slab, t.sg, a, (const float*)kappa);
       return;
     }
   }
-  if (tune_of<T>(g).pd >= 3)
-    hipLaunchKernelGGL((zpair_kernel<T, KIND, 2>), grid, dim3(PNT), 0, st, g, p.nzc, p.czlen, p.xcd_slab, sgrp,
-                       a, (const T*)kappa);
+  const PairShape p = pair_shape<float>(g);
+  const dim3 grid((unsigned)p.per_sys * (unsigned)a.count);
+  // prefetch depth P (planes ahead): pd 2 -> 2 (the kinds without an extra stream then
+  // fit two blocks per CU), pd 3 -> 4 (one block per CU)
+  if (t.pd >= 3)
+    hipLaunchKernelGGL((zpair_dma_kernel<KIND, 4>), grid, dim3(PNT), 0, st, g, p.nzc, p.czlen, p.xcd_slab, t.sg, a,
+                       (const float*)kappa);
   else
-    hipLaunchKernelGGL((zpair_kernel<T, KIND, 1>), grid, dim3(PNT), 0, st, g, p.nzc, p.czlen, p.xcd_slab, sgrp,
-                       a, (const T*)kappa);
+    hipLaunchKernelGGL((zpair_dma_kernel<KIND, 2>), grid, dim3(PNT), 0, st, g, p.nzc, p.czlen, p.xcd_slab, t.sg, a,
+                       (const float*)kappa);
 }
 
 }  // namespace
@@ -2135,29 +1775,29 @@ int Launch<T2>::pair_blocks(const GridDesc& g) {
 
 template <typename T2>
 bool Launch<T2>::pair_fits(const GridDesc& g) {
-  return (size_t)g.nx * g.ny * g.nz * sizeof(T2) < ((size_t)1 << 32);
+  return sizeof(T2) == 8 && g.tune32.kern >= 2 && streams_fit(g);
 }
 
 template <typename T2>
 bool Launch<T2>::factor_pair(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<T2>& a,
                              int kind) {
-  using T = typename Scal<T2>::t;
   if (!pair_fits(g)) return false;
-  switch (kind) {
-    case 0: run_pair<T, 0>(st, g, kappa, a); break;
-    case kFacResid: run_pair<T, kFacResid>(st, g, kappa, a); break;
-    case kFacInF: run_pair<T, kFacInF>(st, g, kappa, a); break;
-    case kFacAdd: run_pair<T, kFacAdd>(st, g, kappa, a); break;
-    case kFacDual: run_pair<T, kFacDual>(st, g, kappa, a); break;
-    case kFacInF | kFacDual: run_pair<T, kFacInF | kFacDual>(st, g, kappa, a); break;
-    default: return false;
+  if constexpr (sizeof(T2) == 8) {
+    switch (kind) {
+      case 0: run_pair<0>(st, g, kappa, a); return true;
+      case kFacResid: run_pair<kFacResid>(st, g, kappa, a); return true;
+      case kFacInF: run_pair<kFacInF>(st, g, kappa, a); return true;
+      case kFacAdd: run_pair<kFacAdd>(st, g, kappa, a); return true;
+      case kFacDual: run_pair<kFacDual>(st, g, kappa, a); return true;
+      case kFacInF | kFacDual: run_pair<kFacInF | kFacDual>(st, g, kappa, a); return true;
+    }
   }
-  return true;
+  return false;
 }
 
 template <typename T2>
 bool Launch<T2>::triple_runs(const GridDesc& g) {
-  return sizeof(T2) == 8 && g.tune32.kern == 3 && g.tune32.fuse == 2 && dma_pair_fits(g);
+  return sizeof(T2) == 8 && g.tune32.kern == 3 && g.tune32.fuse == 2 && streams_fit(g);
 }
 
 template <typename T2>
@@ -2198,17 +1838,6 @@ MultiInst MultiLaunch<T2>::describe(const GridDesc& g0, const void* kappa) {
   m.czlen = sh.czlen;
   m.xcd_slab = sh.xcd_slab;
   m.per_sys = m.gx * m.gy * m.nzc;
-  // pair geometry (64 x 12 tiles, automatic z-chunks), when the pair kernel runs on this grid
-  m.pgx = m.pgy = m.pnzc = m.pczlen = m.pxcd_slab = m.pper_sys = 0;
-  if (Launch<T2>::pair_fits(g)) {
-    const PairShape p = pair_shape<T>(g);  // g carries cz = 0: automatic chunks
-    m.pgx = p.gx;
-    m.pgy = p.gy;
-    m.pnzc = p.nzc;
-    m.pczlen = p.czlen;
-    m.pxcd_slab = p.xcd_slab;
-    m.pper_sys = p.per_sys;
-  }
   return m;
 }
 
@@ -2239,34 +1868,6 @@ void MultiLaunch<T2>::factor(hipStream_t st, const MultiInst* inst, const MultiS
       break;
     default: break;
   }
-}
-
-template <typename T, int KIND, typename T2>
-void run_multi_pair(hipStream_t st, const MultiInst* inst, const MultiSys<T2>* sys, const int2* seg, int nseg,
-                    int nblocks, int rin, int rout, int rout2, int k, int cstride) {
-  hipLaunchKernelGGL((zmulti_pair_kernel<T, KIND>), dim3((unsigned)nblocks), dim3(PNT), 0, st, inst, sys, seg, nseg,
-                     rin, rout, rout2, k, cstride);
-}
-
-template <typename T2>
-bool MultiLaunch<T2>::factor_pair(hipStream_t st, const MultiInst* inst, const MultiSys<T2>* sys, const int2* seg,
-                                  int nseg, int nblocks, int kind, int rin, int rout, int rout2, int k, int cstride) {
-  using T = typename Scal<T2>::t;
-  if (nseg <= 0 || nblocks <= 0) return true;
-  switch (kind) {
-    case 0: run_multi_pair<T, 0>(st, inst, sys, seg, nseg, nblocks, rin, rout, rout2, k, cstride); break;
-    case kFacResid:
-      run_multi_pair<T, kFacResid>(st, inst, sys, seg, nseg, nblocks, rin, rout, rout2, k, cstride);
-      break;
-    case kFacInF: run_multi_pair<T, kFacInF>(st, inst, sys, seg, nseg, nblocks, rin, rout, rout2, k, cstride); break;
-    case kFacAdd: run_multi_pair<T, kFacAdd>(st, inst, sys, seg, nseg, nblocks, rin, rout, rout2, k, cstride); break;
-    case kFacDual: run_multi_pair<T, kFacDual>(st, inst, sys, seg, nseg, nblocks, rin, rout, rout2, k, cstride); break;
-    case kFacInF | kFacDual:
-      run_multi_pair<T, kFacInF | kFacDual>(st, inst, sys, seg, nseg, nblocks, rin, rout, rout2, k, cstride);
-      break;
-    default: return false;
-  }
-  return true;
 }
 
 template <typename T2>

@@ -61,73 +61,90 @@ int chunk_limit(const GridDesc& g) {
   return (int)std::min(planes, 1e6) - 10;
 }
 
+// tiles of `len` points covering n, and the distance between them
+template <int NF>
+int tiles(int n, int len, int& step) {
+  step = 0;
+  if (n <= len) return 1;
+  const int k = 1 + (n - len + len - 2 * NF - 1) / (len - 2 * NF);
+  step = (n - len + k - 2) / (k - 1);
+  return k;
+}
+
 // The largest number of blocks per system a geometry may have: enough to fill the chip eight
 // times over with one system, or what the longest chunks and largest blocks give
 template <typename T, int NF, bool EXTRA>
 int rows_cap(const GridDesc& g) {
   using C = Cfg<T, NF, EXTRA, false>;
   const KernelTune& t = sizeof(T) == 4 ? g.tune32 : g.tune64;
-  auto tiles = [](int n, int len) { return n <= len ? 1 : 1 + (n - len + len - 2 * NF - 1) / (len - 2 * NF); };
   const int cz = std::min(t.cz > 0 ? t.cz : 126, chunk_limit<T>(g));
-  return std::max(2048, tiles(g.nx, 64) * tiles(g.ny, C::WMAX * C::R) * ((g.nz + cz - 1) / cz));
+  int step;
+  return std::max(2048, tiles<NF>(g.nx, 64, step) * tiles<NF>(g.ny, C::WMAX * C::R, step) * ((g.nz + cz - 1) / cz));
 }
 
-// Geometry of a pass over `count` systems.  Candidates: blocks of 2 .. WMAX waves and z-chunks
-// of 2 .. 128 planes (those for which a chunk's iterations fill whole trips of four), or the
-// launch shape's chunk.  A block's planes cost its vector instructions or, with few waves on
-// a CU, the latency of a barrier and the LDS exchange; short chunks repeat 2 (NF - 1) planes,
-// small blocks 2 NF rows; long chunks and large blocks leave CUs idle where systems are few.
-// The constants are fitted to 5000 measured launches (32^3 to 256^3, 1 to 24 systems, both
-// precisions, every kind): the geometry chosen costs 4 % more than the best measured one on
-// average (33 % at worst), where one fixed geometry per grid costs 30 % and more at either end.
+// the geometry with blocks of w waves and z-chunks of cz planes; false where it cannot be used
+template <typename T, int NF, bool EXTRA, bool SM>
+bool shape_of(const GridDesc& g, int w, int cz, RowsShape& s) {
+  using C = Cfg<T, NF, EXTRA, SM>;
+  const int rb = w * C::R;
+  if ((g.ny > rb && rb <= 2 * NF) || lds_bytes(NF, w, 2 * sizeof(T)) > 160 * 1024) return false;
+  s.w = w;
+  s.small = SM ? 1 : 0;
+  s.gx = tiles<NF>(g.nx, 64, s.sx);
+  if (s.sx > 0) s.sx = std::min((s.sx + 7) / 8 * 8, 64 - 2 * NF);  // rows start on 64-byte lines where they can
+  s.gy = tiles<NF>(g.ny, rb, s.sy);
+  s.czlen = std::min(std::min(cz, g.nz), chunk_limit<T>(g));
+  s.nzc = (g.nz + s.czlen - 1) / s.czlen;
+  s.per_sys = s.gx * s.gy * s.nzc;
+  s.xcd_slab = (s.per_sys % 8 == 0 && s.per_sys >= 64) ? s.per_sys / 8 : 0;
+  s.inv_sh2 = 1.0 / g.s_h2;
+  s.damp_sh2 = g.damp_scale / g.s_h2;
+  return true;
+}
+
+// CU cycles (2.4 GHz) of one block of w waves on a z-chunk, `conc` blocks on its CU at once
+template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
+double block_cycles(int w, int czlen, double conc) {
+  const double v = Cfg<T, NF, EXTRA, SM>::R * (NF * (sizeof(T) == 4 ? 83.0 : 137.0) + (RESID ? 72.0 : 0.0));
+  const double iters = (czlen + 2 * (NF - 1) + 3) / 4 * 4;
+  return iters * std::max(std::ceil(w * conc / 4) * v * 1.19, 820.0 + v * 1.02) + 6100.0;
+}
+
+// bytes of HBM, and requested of the L2s, by a launch over `count` systems
+template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
+void launch_bytes(const GridDesc& g, const RowsShape& s, double count, double& hbm, double& l2) {
+  const double e = 2 * sizeof(T), pts = (double)g.nx * g.ny * g.nz * count;
+  hbm = pts * (2.5 * e + (RESID ? e / std::max(count, 1.0) : EXTRA ? e : 0.0));
+  l2 = (double)s.gx * 64 * s.gy * s.w * Cfg<T, NF, EXTRA, SM>::R * s.nzc * (s.czlen + 2 * NF) * count * 1.5 * e +
+       pts * (EXTRA ? 2.0 : 1.0) * e;
+}
+
+// memory time (cycles) overlaps with all but a quarter of the shorter of the two
+inline double launch_cycles(double comp, double hbm, double l2) {
+  const double mem = 2400.0 * std::max(hbm / 5.16e6, l2 / 9.34e6);
+  return std::max(comp, mem) + 0.25 * std::min(comp, mem);
+}
+
 template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
 void shape_try(const GridDesc& g, int count, int max_blocks, RowsShape& best, double& best_t, RowsShape& any) {
   using C = Cfg<T, NF, EXTRA, SM>;
   const KernelTune& t = sizeof(T) == 4 ? g.tune32 : g.tune64;
-  auto tiles = [](int n, int len, int& step) {
-    step = 0;
-    if (n <= len) return 1;
-    const int k = 1 + (n - len + len - 2 * NF - 1) / (len - 2 * NF);
-    step = (n - len + k - 2) / (k - 1);
-    return k;
-  };
-  const int climit = chunk_limit<T>(g);
-  const int cap = rows_cap<T, NF, EXTRA>(g);
+  const int climit = chunk_limit<T>(g), cap = rows_cap<T, NF, EXTRA>(g);
   for (int w = C::WMAX; w >= 2; --w) {
-    const int rb = w * C::R;
-    if (g.ny > rb && rb <= 2 * NF) break;
-    if (w > 2 && rb - C::R >= g.ny) continue;  // a smaller block covers every row
-    if (lds_bytes(NF, w, 2 * sizeof(T)) > 160 * 1024) continue;
-    RowsShape s;
-    s.w = w;
-    s.small = SM ? 1 : 0;
-    s.gx = tiles(g.nx, 64, s.sx);
-    if (s.sx > 0) s.sx = std::min((s.sx + 7) / 8 * 8, 64 - 2 * NF);  // rows start on 64-byte lines where they can
-    s.gy = tiles(g.ny, rb, s.sy);
-    const int bpc = std::max(1, C::WMAX / w);  // blocks per CU (registers; LDS allows as many)
+    if (w > 2 && (w - 1) * C::R >= g.ny) continue;  // a smaller block covers every row
+    const int bpc = std::max(1, C::WMAX / w);       // blocks per CU (registers; LDS allows as many)
     for (const int m : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
-      int cz = 4 * m - 2 * (NF - 1) % 4;
-      if (t.cz > 0) cz = t.cz;
-      s.czlen = std::min(std::min(cz, g.nz), climit);
-      s.nzc = (g.nz + s.czlen - 1) / s.czlen;
-      s.per_sys = s.gx * s.gy * s.nzc;
-      // CU cycles of the launch (2.4 GHz): rounds of blocks over the CUs, `conc` of them on a
-      // CU at once; memory time overlaps with all but a quarter of the shorter of the two
+      const int cz = t.cz > 0 ? t.cz : 4 * m - 2 * (NF - 1) % 4;
+      RowsShape s;
+      if (!shape_of<T, NF, EXTRA, SM>(g, w, cz, s)) break;
       const double blocks = (double)s.per_sys * count;
-      const double v = C::R * (NF * (sizeof(T) == 4 ? 83.0 : 137.0) + (RESID ? 72.0 : 0.0));
-      const double iters = (s.czlen + 2 * (NF - 1) + 3) / 4 * 4;
-      auto round = [&](double conc) {
-        return iters * std::max(std::ceil(w * conc / 4) * v * 1.19, 820.0 + v * 1.02) + 6100.0;
-      };
       const double conc = std::max(1.0, std::min((double)bpc, std::ceil(blocks / 256.0)));
       const double full = std::floor(blocks / (256.0 * conc)), rest = blocks - full * 256.0 * conc;
-      const double comp = full * round(conc) + (rest > 0 ? round(std::ceil(rest / 256.0)) : 0.0);
-      const double e = 2 * sizeof(T), pts = (double)g.nx * g.ny * g.nz * count;
-      const double hbm = pts * (2.5 * e + (RESID ? e / count : EXTRA ? e : 0.0));
-      const double l2 = (double)s.gx * 64 * s.gy * rb * s.nzc * (s.czlen + 2 * NF) * count * 1.5 * e +
-                        pts * (EXTRA ? 2.0 : 1.0) * e;
-      const double mem = 2400.0 * std::max(hbm / 5.16e6, l2 / 9.34e6);
-      const double tm = std::max(comp, mem) + 0.25 * std::min(comp, mem);
+      const double comp = full * block_cycles<T, NF, EXTRA, RESID, SM>(w, s.czlen, conc) +
+                          (rest > 0 ? block_cycles<T, NF, EXTRA, RESID, SM>(w, s.czlen, std::ceil(rest / 256.0)) : 0.0);
+      double hbm, l2;
+      launch_bytes<T, NF, EXTRA, RESID, SM>(g, s, count, hbm, l2);
+      const double tm = launch_cycles(comp, hbm, l2);
       if (s.per_sys <= cap && (max_blocks <= 0 || s.per_sys <= max_blocks) && tm < best_t) {
         best_t = tm;
         best = s;
@@ -138,17 +155,21 @@ void shape_try(const GridDesc& g, int count, int max_blocks, RowsShape& best, do
   }
 }
 
+// Geometry of a pass over `count` systems.  Candidates: blocks of 2 .. WMAX waves and z-chunks
+// of 2 .. 128 planes (those for which a chunk's iterations fill whole trips of four), or the
+// launch shape's chunk.  A block's planes cost its vector instructions or, with few waves on
+// a CU, the latency of a barrier and the LDS exchange; short chunks repeat 2 (NF - 1) planes,
+// small blocks 2 NF rows; long chunks and large blocks leave CUs idle where systems are few.
+// The constants are fitted to 5000 measured launches (32^3 to 256^3, 1 to 24 systems, both
+// precisions, every kind): the geometry chosen costs 4 % more than the best measured one on
+// average (33 % at worst), where one fixed geometry per grid costs 30 % and more at either end.
 template <typename T, int NF, bool EXTRA, bool RESID>
 RowsShape shape_for(const GridDesc& g, int count, int max_blocks) {
   RowsShape best{}, any{};
   double best_t = 1e300;
   shape_try<T, NF, EXTRA, RESID, false>(g, count, max_blocks, best, best_t, any);
   shape_try<T, NF, EXTRA, RESID, true>(g, count, max_blocks, best, best_t, any);
-  if (best.w == 0) best = any;
-  best.xcd_slab = (best.per_sys % 8 == 0 && best.per_sys >= 64) ? best.per_sys / 8 : 0;
-  best.inv_sh2 = 1.0 / g.s_h2;
-  best.damp_sh2 = g.damp_scale / g.s_h2;
-  return best;
+  return best.w == 0 ? any : best;
 }
 
 template <typename T, int KIND, int NF>

@@ -84,3 +84,34 @@ def test_register_passes_stop_where_single_factors_do(ctx):  # noqa: F811
     assert len(set(out[0][1][:, 0].tolist())) > 1
     assert np.array_equal(out[1][0], out[2][0])
     assert np.abs(out[0][0] - out[1][0]).max() <= 1e-10 * np.abs(out[0][0]).max()
+
+
+@pytest.mark.parametrize("q", [3, 8, 10])
+@pytest.mark.parametrize("prec", [64, 32])
+def test_batch_passes_match_single_operators(ctx, prec, q):  # noqa: F811
+    # instances from one tile to several, a thin one, and one whose systems outlast the others
+    # (the geometry changes with the work left): each against its own shifted solves, same
+    # steps.  FP64 to 2e-12 of the largest value, FP32 to 1e-5: both sides are within the FP32
+    # bar, at most 40 steps of q <= 10 products with errors of a few 6e-8 each
+    shapes = [(3, 5, 70), (40, 33, 64), (1, 20, 21), (24, 60, 130)]
+    dt = torch.complex128 if prec == 64 else torch.complex64
+    ops, cons, fs = [], [], []
+    rng = np.random.default_rng(q)
+    for i, shape in enumerate(shapes):
+        c = rng.uniform(1.0, 3.0, size=shape)
+        h = 1.0 / max(shape)
+        g = hf.Operator(ctx, dev(c), h, 0.3 / h, 2, 1.0)
+        ops.append(g)
+        cons.append(hf.Contour(g, 4 + 2 * (i % 2), 1.0, 0.25 if i == 1 else 0.6, q))
+        f = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+        fs.append(dev(f).to(dt))
+    ys, st = hf.shifted_solve_batch(ops, cons, fs, reduce=5.0, max_steps=40)
+    assert max(int(s.max()) for s in st) > min(int(s.max()) for s in st)
+    for g, c, f, y, s in zip(ops, cons, fs, ys, st):
+        ref, rs = hf.shifted_solve(g, c, f[None], reduce=5.0, max_steps=40)
+        if prec == 64:
+            assert np.array_equal(s, rs[:, 0])
+        same = s == rs[:, 0]  # (an FP32 residual can land on the other side of the threshold)
+        assert same.sum() >= len(s) - 1
+        a, b = host(y)[same], host(ref)[same, 0]
+        assert np.abs(a - b).max() <= (2e-12 if prec == 64 else 1e-5) * np.abs(b).max()
