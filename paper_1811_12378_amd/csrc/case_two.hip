@@ -116,13 +116,13 @@ __device__ __forceinline__ double block_sum_nt(double v, double* sh) {
 // w), kFacInF (the input is the right-hand side); on the output: kFacAdd (adds y1),
 // kFacDual (a second output).
 //
-// z-marching: a workgroup of PTX x PTY threads takes tiles of PTX x PTY columns by PCZ
-// planes (a grid-stride loop over the tiles of its system, so the residual partials keep
+// z-marching: a workgroup of PTX x PTY threads takes tiles of PTX x PTY columns by pcz
+// planes (b2_chunk; a grid-stride loop over the tiles of its system, so the residual partials keep
 // the single factor's layout); each thread carries x1 and x2 of planes k - 1, k and k + 1
 // of its column in registers and gathers only the in-plane neighbours through the cache.
 // With a grid width that is a multiple of 8 the workgroups of one XCD (blockIdx.x % 8)
 // sweep one contiguous eighth of the tiles.
-constexpr int PTX = 64, PTY = NT / PTX, PCZ = 32;
+constexpr int PTX = 64, PTY = NT / PTX;
 
 template <typename T>
 struct Pt2 {
@@ -139,7 +139,7 @@ constexpr int b2_zm_waves() {
 
 template <typename T, int KIND, int NF>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<T, KIND, NF>()))) void b2_zm_kernel(
-    GridDesc g, const T* __restrict__ K, B2Args<typename Vec2<T>::t> a) {
+    GridDesc g, const T* __restrict__ K, B2Args<typename Vec2<T>::t> a, int pcz) {
   static_assert(NF == 1 || NF == 2, "one or two factors per pass");
   using T2 = typename Vec2<T>::t;
   constexpr bool RESID = (KIND & kFacResid) != 0, ADD = (KIND & kFacAdd) != 0, DUAL = (KIND & kFacDual) != 0,
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<
   T2* __restrict__ O = a.wout + (size_t)s * n2;
   T2* __restrict__ O2 = DUAL ? a.wout2 + (size_t)s * n2 : nullptr;
   const size_t sy = (size_t)g.nx, sz = (size_t)g.nx * g.ny;
-  const int gx = (g.nx + PTX - 1) / PTX, gy = (g.ny + PTY - 1) / PTY, gz = (g.nz + PCZ - 1) / PCZ;
+  const int gx = (g.nx + PTX - 1) / PTX, gy = (g.ny + PTY - 1) / PTY, gz = (g.nz + pcz - 1) / pcz;
   const int ntile = gx * gy * gz;
   const int nsl = gridDim.x % 8 == 0 ? 8 : 1;
   const int tps = (ntile + nsl - 1) / nsl;
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<
   double acc = 0.0;
   for (int t = t_lo + (int)(blockIdx.x / nsl); t < t_hi; t += (int)(gridDim.x / nsl)) {
     const int i = (t % gx) * PTX + tx, j = ((t / gx) % gy) * PTY + ty, zc = t / (gx * gy);
-    const int zb = zc * PCZ, ze = min(g.nz, zb + PCZ);
+    const int zb = zc * pcz, ze = min(g.nz, zb + pcz);
     if (i >= g.nx || j >= g.ny) continue;  // no barrier inside the tile loop
     const size_t col = (size_t)i + sy * (size_t)j;
     Pt2<T> xm = zb > 0 ? ld2(col + sz * (size_t)(zb - 1)) : zero;
@@ -332,16 +332,26 @@ __global__ __launch_bounds__(NT) void b2_residual64_kernel(GridDesc g, const dou
   if (threadIdx.x == 0) partial[blockIdx.x] = t;
 }
 
+// Planes per tile: 32, fewer where the workgroups of a launch would outnumber the tiles (a
+// system's tail of steps runs alone: at 128^3 256 tiles of 32 planes left three of four CUs'
+// worth of waves idle)
+int b2_chunk(const GridDesc& g) {
+  const long cols = (long)((g.nx + PTX - 1) / PTX) * ((g.ny + PTY - 1) / PTY);
+  int cz = 32;
+  while (cz > 4 && cols * ((g.nz + cz - 1) / cz) < b2_blocks(g)) cz /= 2;
+  return cz;
+}
+
 template <typename T, int KIND>
 void launch_kind(hipStream_t st, const GridDesc& g, const T* K, int nsys, int nblk,
                  const B2Args<typename Vec2<T>::t>& a) {
-  hipLaunchKernelGGL((b2_zm_kernel<T, KIND, 1>), dim3((unsigned)nblk, (unsigned)nsys), dim3(NT), 0, st, g, K, a);
+  hipLaunchKernelGGL((b2_zm_kernel<T, KIND, 1>), dim3((unsigned)nblk, (unsigned)nsys), dim3(NT), 0, st, g, K, a, b2_chunk(g));
 }
 
 template <typename T, int KIND>
 void launch_pair_kind(hipStream_t st, const GridDesc& g, const T* K, int nsys, int nblk,
                       const B2Args<typename Vec2<T>::t>& a) {
-  hipLaunchKernelGGL((b2_zm_kernel<T, KIND, 2>), dim3((unsigned)nblk, (unsigned)nsys), dim3(NT), 0, st, g, K, a);
+  hipLaunchKernelGGL((b2_zm_kernel<T, KIND, 2>), dim3((unsigned)nblk, (unsigned)nsys), dim3(NT), 0, st, g, K, a, b2_chunk(g));
 }
 
 }  // namespace
