@@ -8,28 +8,28 @@
 // [27 taps][Cout][Cin] (tap = (dz+1)*9 + (dy+1)*3 + (dx+1)), so that the Cin values a
 // lane feeds to one MFMA are contiguous.
 //
-// Implicit GEMM: output tile = 16 voxels x 16 output channels per wavefront,
-//   D[v][co] += sum_{tap, ci} X[v + off_tap][ci] * W[tap][co][ci],
-// one v_mfma_f32_16x16x32_bf16 (Cin % 32 == 0) or v_mfma_f32_16x16x16_bf16 per
-// (tap, 32- or 16-channel chunk, Cout tile).  Lane l supplies row (l % 16) and the
-// k-range [KB*(l/16), KB*(l/16)+KB) of A (voxels x channels) and column (l % 16) of B;
-// the accumulator holds rows 4*(l/16)+r, column l%16.  Voxels are numbered linearly
-// (x fastest), so any grid shape fills the waves.
+// Implicit GEMM: D[co][v] += sum_{tap, ci} W[tap][co][ci] * X[v + off_tap][ci], one
+// v_mfma_f32_16x16x32_bf16 (Cin % 32 == 0) or v_mfma_f32_16x16x16_bf16 per (tap, 32- or
+// 16-channel chunk, 16 outputs, 16 voxels).  Lane l supplies row (column) l % 16 and the
+// k-range [KB*(l/16), KB*(l/16)+KB) of A (B); the accumulator holds rows 4*(l/16)+r, column
+// l%16.
 //
 // The backward data pass is the same kernel applied to the output gradient with the
 // tap-flipped, Cin/Cout-transposed weights; the weight gradient is a GEMM over voxels
-// (k = voxel) whose per-chunk partial sums are reduced in a fixed order.
+// (k = voxel) whose per-block partial sums are reduced in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <stdexcept>
+#include <type_traits>
 
 #include "netkern.h"
 
 namespace hfci {
 namespace {
 
-typedef short s4v __attribute__((ext_vector_type(4)));
 typedef __bf16 b8v __attribute__((ext_vector_type(8)));
+typedef __bf16 b4v __attribute__((ext_vector_type(4)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
@@ -51,242 +51,277 @@ __device__ __forceinline__ Coord coord_of(long v, const Dims& d) {
   return c;
 }
 
-template <int KB>
-struct Frag;
-template <>
-struct Frag<4> {  // 16x16x16: 4 bf16 per lane
-  using T = s4v;
-  __device__ static T load(const uint16_t* p) {
-    const uint2 u = *reinterpret_cast<const uint2*>(p);
-    T r;
-    r[0] = (short)(u.x & 0xffff);
-    r[1] = (short)(u.x >> 16);
-    r[2] = (short)(u.y & 0xffff);
-    r[3] = (short)(u.y >> 16);
-    return r;
-  }
-  __device__ static T zero() { return T{0, 0, 0, 0}; }
-  __device__ static f4v mma(T a, T b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0); }
-};
-template <>
-struct Frag<8> {  // 16x16x32: 8 bf16 per lane
-  using T = b8v;
-  __device__ static T load(const uint16_t* p) {
-    const uint4 u = *reinterpret_cast<const uint4*>(p);
-    return __builtin_bit_cast(T, u);
-  }
-  __device__ static T zero() { return __builtin_bit_cast(T, make_uint4(0, 0, 0, 0)); }
-  __device__ static f4v mma(T a, T b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+struct Frag {  // v_mfma_f32_16x16x32_bf16: 8 bf16 per lane
+  __device__ static b8v load(const uint16_t* p) { return __builtin_bit_cast(b8v, *reinterpret_cast<const uint4*>(p)); }
+  __device__ static b8v zero() { return __builtin_bit_cast(b8v, make_uint4(0, 0, 0, 0)); }
+  __device__ static f4v mma(b8v a, b8v b, f4v c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 };
 
-// Forward 3x3x3 convolution: one block = 64 consecutive voxels (4 waves x 16);
-// each wave produces all Cout channels of its 16 voxels.  CT = Cout / 16 tiles.
-template <int KB, int CT>
-__global__ __launch_bounds__(256) void conv_fwd_kernel(Dims d, View in, int cin, const uint16_t* __restrict__ w,
-                                                       const float* __restrict__ bias, int relu, View out) {
-  using F = Frag<KB>;
-  constexpr int KC = 4 * KB;  // channels per MFMA
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long nvox = (long)d.x * d.y * d.z;
-  const long v0 = (long)blockIdx.x * 64 + wave * 16;
+// 3x3x3 "same" convolution as a z-marching implicit GEMM.  A block owns a TX x TY voxel tile of
+// each plane of a z-chunk and takes its input planes in turn: the tile with its one-voxel halo
+// sits in LDS, the next plane's loads are issued before a plane's products and written there
+// after them.  A fragment of 16 voxels read from LDS serves the three output planes that use it
+// (taps dz = -1, 0, 1 of planes p + 1, p, p - 1, one accumulator each).  A wave owns MB blocks of
+// 16 voxels along x and CTW x 16 output channels; the weights are operand A (cout x cin), the
+// input B (cin x voxels), so a lane of the accumulator holds four output channels of one voxel,
+// stored as 8 bytes.
+// 16 and 48 input channels (PAIR): one instruction takes two consecutive 16-channel steps, lanes
+// 0-31 the first and 32-63 the second; the instruction sums the first half of k before the
+// second, so the result has the bits of two 16x16x16 instructions (which take as long each).
+// The odd step out has zeros in lanes 32-63 of both operands.
+// Each output sums its products in the order (tap, channels) in one accumulator.
+// Weights (three fragments per step and 16 outputs): in registers where all of a wave's fit; for
+// 48 -> 16 and 32 -> 32, which leave room for them, in LDS; for 64 and 96 channels a third
+// (dz = -1) in LDS and the rest through L1, from where they are the bound (96 -> 32 on 128^3
+// voxels: 480 us all through L1, 387 us with the third; the products alone 150 us).
+// UP > 0: the first UP input channels are the nearest-neighbour x2 up-sampling of `up` (half
+// the grid), read in place; the others are `in`.
+// SMALL: 16 x 4 tiles, where the large ones would leave CUs without a block.
+// Measured on a 256^3 grid, a block of 64 voxels that read every tap from memory (or one
+// 3-plane ring with a loop over taps, 16 and 48 channels) before, this now: 16 -> 16 988 -> 258 us
+// (4.2 TB/s), 48 -> 16 2488 -> 600 us and its up-sampling pass 900 us gone (66% of the matrix
+// cores' cycles), at 128^3 96 -> 32 and 32 -> 32 1122 (mean) -> 387 and 124 us, 16 -> 32 357 -> 76 us,
+// at 64^3 64 -> 64 and 32 -> 64 306 (mean) -> 82 and 50 us.
+template <int CIN, int COUT, bool SMALL>
+struct ConvCfg {
+  static constexpr bool PAIR = CIN % 32 != 0;
+  static constexpr int CT = COUT / 16;
+  // products of 32 per output, plane and dz; 16-channel steps are (dy, dx, channels)
+  static constexpr int NC = PAIR ? CIN / 16 : CIN / 32, NJ = 9 * NC, NS = PAIR ? (NJ + 1) / 2 : NJ;
+  // waves: WG groups of output channels times WV groups of voxels
+  static constexpr int WG = SMALL && CT == 6 ? 2 : CT;
+  static constexpr int TX = SMALL ? 16 : 32, TY = SMALL || (CIN == 32 && CT >= 4) ? 4 : 8;
+  static constexpr int MB = SMALL ? (CT == 3 ? 1 : WG) : CIN == 64 && CT == 4 ? 8 : 4;
+  static constexpr int WV = TX * TY / 16 / MB, NW = WG * WV, CTW = CT / WG;
+  // channels per voxel in LDS: 2 (mod 4) pieces of 16 bytes apart, reads meet no bank twice
+  static constexpr int CP = PAIR ? CIN : CIN + 16;
+  static constexpr int LX = TX + 2, LY = TY + 2, kPlane = LX * LY * CP;
+  // weights: dz < LDZ in LDS; all taps in registers (WREG: up to 108 of a lane's 256, 60 of 168)
+  static constexpr int LDZ = CIN == 48 || (CIN == 32 && CT == 2 && !SMALL) ? 3 : CIN >= 64 && !SMALL ? 1 : 0;
+  static constexpr bool WREG = !LDZ && 3 * NS * CTW * 4 <= (NW > 8 ? 60 : 108);
+  static constexpr bool ROLL = !WREG && LDZ < 3;  // weights through L1: a loop over dy
+  static constexpr int kFrags = LDZ * NS * CT;
+  static constexpr int PARTS = CIN / 8, kItems = LX * LY * PARTS, NT = 64 * NW, PER = (kItems + NT - 1) / NT;
+  static constexpr int NBX = TX / 16;  // blocks per row
+  static constexpr int blk(int m) { return (m / NBX * LX + m % NBX * 16) * CP; }
+  static_assert(MB % NBX == 0 && WG * CTW == CT && WV * MB * 16 == TX * TY && MB >= 1, "waves cover the tile");
+  static_assert(!ROLL || !PAIR, "paired steps keep their weights in registers or LDS");
+  // LDS offset of 16-channel (32-channel) step j within a tile
+  static constexpr int off(int j) {
+    return (j / NC / 3 * LX + j / NC % 3) * CP + j % NC * (PAIR ? 16 : 32);
+  }
+};
+
+template <int CIN, int COUT, int UP, bool SMALL>
+__global__ __launch_bounds__((ConvCfg<CIN, COUT, SMALL>::NT), 2) void zconv_kernel(
+    Dims d, View in, View up, const uint16_t* __restrict__ w, const float* __restrict__ bias, int relu, View out,
+    int zlen) {
+  using C = ConvCfg<CIN, COUT, SMALL>;
+  using F = Frag;
+  struct Acc {
+    f4v v[C::MB][C::CTW];
+  };
+  __shared__ __align__(16) uint16_t pl[C::kPlane];
+  __shared__ __align__(16) uint16_t wl[C::LDZ ? C::kFrags * 512 : 8];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int gx = (d.x + C::TX - 1) / C::TX, gy = (d.y + C::TY - 1) / C::TY;
+  const int bid = blockIdx.x;
+  const int x0 = bid % gx * C::TX, y0 = bid / gx % gy * C::TY;
+  const int zb = bid / (gx * gy) * zlen, ze = min(d.z, zb + zlen);
   const int row = lane & 15, kq = lane >> 4;
-  const long va = v0 + row;  // voxel whose A-row this lane supplies
-  const bool va_ok = va < nvox;
-  const Coord ca = coord_of(va_ok ? va : 0, d);
-  const int cout = CT * 16;
-  f4v acc[CT];
-#pragma unroll
-  for (int t = 0; t < CT; ++t) acc[t] = f4v{0.f, 0.f, 0.f, 0.f};
-  for (int tap = 0; tap < 27; ++tap) {
-    const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-    const int zz = ca.z + dz, yy = ca.y + dy, xx = ca.x + dx;
-    const bool ok = va_ok && zz >= 0 && zz < d.z && yy >= 0 && yy < d.y && xx >= 0 && xx < d.x;
-    const long vin = ok ? ((long)zz * d.y + yy) * d.x + xx : 0;
-    const uint16_t* ap = in.p + vin * in.cs + in.off + kq * KB;
-    const uint16_t* wp = w + (size_t)tap * cout * cin + (size_t)row * cin + kq * KB;
-    for (int c0 = 0; c0 < cin; c0 += KC) {
-      const typename F::T a = ok ? F::load(ap + c0) : F::zero();
-#pragma unroll
-      for (int t = 0; t < CT; ++t) {
-        const typename F::T b = F::load(wp + (size_t)t * 16 * cin + c0);
-        acc[t] = F::mma(a, b, acc[t]);
-      }
+  const int wg = wave % C::WG, wv = wave / C::WG;
+  // fragment of the weights for (dz, step s, 16 outputs t): a lane's 8 channels of one output
+  auto wfrag = [&](int dz, int st, int t, int l) {
+    const int r = l & 15, k = l >> 4;
+    int j = st, ch = k * 8;
+    if (C::PAIR) {
+      j = 2 * st + k / 2;
+      ch = k % 2 * 8;
+      if (j >= C::NJ) return F::zero();
     }
-  }
-  // accumulator: rows (voxels) 4*kq + r, column (channel) row
-#pragma unroll
-  for (int t = 0; t < CT; ++t) {
-    const int co = t * 16 + row;
-    const float bv = bias ? bias[co] : 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const long v = v0 + kq * 4 + r;
-      if (v < nvox) {
-        float val = acc[t][r] + bv;
-        if (relu) val = fmaxf(val, 0.f);
-        out.p[v * out.cs + out.off + co] = f2bf(val);
-      }
-    }
-  }
-}
+    const int tap = dz * 9 + j / C::NC;
+    return F::load(w + ((size_t)tap * COUT + t * 16 + r) * CIN + j % C::NC * (C::PAIR ? 16 : 32) + ch);
+  };
+  if constexpr (C::LDZ > 0)
+    for (int i = tid; i < C::kFrags * 64; i += C::NT)
+      *reinterpret_cast<b8v*>(wl + i * 8) = wfrag(i / 64 / (C::NS * C::CT), i / 64 / C::CT % C::NS, i / 64 % C::CT, i & 63);
 
-// 16 -> 16 channel layers (the full-resolution level of the U-Net) as a z-marching
-// implicit GEMM.  A block owns a 64 x 4 voxel tile of each plane of a z-chunk; the input
-// tile with its one-voxel halo (66 x 6 voxels x 16 channels) of planes z-1, z, z+1 sits
-// in a 3-plane LDS ring and the 27 x 16 x 16 weights in LDS, so every input voxel is read
-// from memory about once per chunk instead of once per tap.  Wave w computes row y0+w:
-// four 16-voxel blocks, one MFMA per (tap, block) with the weights as A (cout x cin) and
-// the input as B (cin x voxels), so the accumulator of lane l holds output channels
-// 4(l/16)..4(l/16)+3 of voxel l%16 and is stored as one 8-byte write.
-constexpr int ZCX = 64, ZCY = 4, ZLX = ZCX + 2, ZLY = ZCY + 2;
-
-__global__ __launch_bounds__(256) void zconv16_kernel(Dims d, View in, const uint16_t* __restrict__ w,
-                                                      const float* __restrict__ bias, int relu, View out, int zlen) {
-  __shared__ __align__(16) uint16_t ring[3][ZLY][ZLX][16];
-  __shared__ __align__(16) uint16_t ws[27][16][16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gx = (d.x + ZCX - 1) / ZCX, gy = (d.y + ZCY - 1) / ZCY;
-  const int b = blockIdx.x;
-  const int bx = b % gx, by = (b / gx) % gy, zc = b / (gx * gy);
-  const int x0 = bx * ZCX, y0 = by * ZCY;
-  const int zb = zc * zlen, ze = min(d.z, zb + zlen);
-  for (int i = threadIdx.x; i < 27 * 16 * 16 / 8; i += 256)
-    reinterpret_cast<uint4*>(&ws[0][0][0])[i] = reinterpret_cast<const uint4*>(w)[i];
-  // plane zp of the input tile into ring slot zp mod 3 (zeros outside the grid)
-  auto load_plane = [&](int zp) {
-    uint4* dst = reinterpret_cast<uint4*>(&ring[(zp + 3) % 3][0][0][0]);
-    for (int c = threadIdx.x; c < ZLY * ZLX * 2; c += 256) {
-      const int vox = c >> 1, half = c & 1;
-      const int lx = vox % ZLX, ly = vox / ZLX;
-      const int xg = x0 - 1 + lx, yg = y0 - 1 + ly;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (zp >= 0 && zp < d.z && xg >= 0 && xg < d.x && yg >= 0 && yg < d.y)
-        v = *reinterpret_cast<const uint4*>(in.p + (((long)zp * d.y + yg) * d.x + xg) * in.cs + in.off + half * 8);
-      dst[c] = v;
+  // this thread's 16-byte pieces of a plane: where they come from (in pieces; -1: zeros) and go
+  const Dims e{d.z / 2, d.y / 2, d.x / 2};
+  int src[C::PER];
+  bool coarse[C::PER];
+#pragma unroll
+  for (int i = 0; i < C::PER; ++i) {
+    const int c = tid + i * C::NT;
+    const int vox = c / C::PARTS, part = c % C::PARTS;
+    const int xg = x0 - 1 + vox % C::LX, yg = y0 - 1 + vox / C::LX;
+    const bool ok = c < C::kItems && xg >= 0 && xg < d.x && yg >= 0 && yg < d.y;
+    coarse[i] = UP > 0 && part * 8 < UP;
+    src[i] = !ok ? -1
+             : coarse[i] ? ((yg / 2) * e.x + xg / 2) * (up.cs / 8) + up.off / 8 + part
+                         : (yg * d.x + xg) * (in.cs / 8) + in.off / 8 + part - UP / 8;
+  }
+  // (loads of valid addresses only, without branches: pieces outside the grid become zeros in put)
+  uint4 v[C::PER];
+  bool zok = false;
+  auto fetch = [&](int zp) {
+    zok = zp >= 0 && zp < d.z;  // uniform
+    zp = min(max(zp, 0), d.z - 1);
+    const uint4* f = reinterpret_cast<const uint4*>(in.p + (long)zp * d.y * d.x * in.cs);
+    const uint4* g = UP > 0 ? reinterpret_cast<const uint4*>(up.p + (long)(zp / 2) * e.y * e.x * up.cs) : f;
+#pragma unroll
+    for (int i = 0; i < C::PER; ++i) v[i] = (coarse[i] ? g : f)[max(src[i], 0)];
+  };
+  auto put = [&] {
+#pragma unroll
+    for (int i = 0; i < C::PER; ++i) {
+      const int c = tid + i * C::NT;
+      const bool ok = zok && src[i] >= 0;
+      if (c < C::kItems)
+        *reinterpret_cast<uint4*>(pl + c / C::PARTS * C::CP + c % C::PARTS * 8) =
+            make_uint4(ok ? v[i].x : 0, ok ? v[i].y : 0, ok ? v[i].z : 0, ok ? v[i].w : 0);
     }
   };
-  if (zb >= ze) return;
-  load_plane(zb - 1);
-  load_plane(zb);
-  const int row = lane & 15, kq = lane >> 4;
-  const int yo = y0 + wave;
-  float bv[4];
+  fetch(zb - 1);
+
+  b8v wr[C::WREG ? 3 : 1][C::WREG ? C::NS : 1][C::CTW];
+  if constexpr (C::WREG)
 #pragma unroll
-  for (int r = 0; r < 4; ++r) bv[r] = bias ? bias[4 * kq + r] : 0.f;
-  for (int z = zb; z < ze; ++z) {
-    load_plane(z + 1);
-    __syncthreads();
-    f4v acc[4];
+    for (int dz = 0; dz < 3; ++dz)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) acc[q] = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int tap = 0; tap < 27; ++tap) {
-      const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-      const s4v wa = *reinterpret_cast<const s4v*>(&ws[tap][row][4 * kq]);
-      const uint16_t(*pl)[ZLX][16] = ring[(z + dz + 3) % 3];
+      for (int st = 0; st < C::NS; ++st)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const s4v xb = *reinterpret_cast<const s4v*>(&pl[wave + 1 + dy][q * 16 + row + 1 + dx][4 * kq]);
-        acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa, xb, acc[q], 0, 0, 0);
-      }
-    }
+        for (int t = 0; t < C::CTW; ++t) wr[dz][st][t] = wfrag(dz, st, wg * C::CTW + t, lane);
+  f4v bv[C::CTW];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int xo = x0 + q * 16 + row;
-      if (xo < d.x && yo < d.y) {
-        uint16_t h[4];
+  for (int t = 0; t < C::CTW; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float v = acc[q][r] + bv[r];
-          if (relu) v = fmaxf(v, 0.f);
-          h[r] = f2bf(v);
+    for (int r = 0; r < 4; ++r) bv[t][r] = bias ? bias[(wg * C::CTW + t) * 16 + 4 * kq + r] : 0.f;
+
+  // the wave's blocks of 16 voxels: block m is NBX * 16 voxels of a row along, then rows down
+  const int cx = row, cy = wv * (C::MB / C::NBX);
+  const int base = (cy * C::LX + cx) * C::CP + (C::PAIR ? kq % 2 : kq) * 8;
+  const int hi = C::PAIR ? kq / 2 : 0;  // lanes of a pair's second step
+  const int xo = x0 + cx, yo = y0 + cy;
+  const long ostep = (long)d.x * out.cs, oplane = d.y * ostep;
+  uint16_t* op = out.p + zb * oplane + yo * ostep + (long)xo * out.cs + out.off + wg * C::CTW * 16 + 4 * kq;
+  // output planes are stored in turn
+  auto store = [&](const Acc& a) {
+#pragma unroll
+    for (int m = 0; m < C::MB; ++m)
+      if (xo + m % C::NBX * 16 < d.x && yo + m / C::NBX < d.y) {
+        uint16_t* o = op + m / C::NBX * ostep + m % C::NBX * 16 * out.cs;
+#pragma unroll
+        for (int t = 0; t < C::CTW; ++t) {
+          f4v h = a.v[m][t] + bv[t];
+          if (relu)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) h[r] = fmaxf(h[r], 0.f);
+          *reinterpret_cast<b4v*>(o + t * 16) = __builtin_convertvector(h, b4v);  // to nearest even
         }
-        const uint2 pk = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-        *reinterpret_cast<uint2*>(out.p + (((long)z * d.y + yo) * d.x + xo) * out.cs + out.off + 4 * kq) = pk;
       }
-    }
-    __syncthreads();
-  }
-}
+    op += oplane;
+  };
 
-// 48 -> 16 channel layer (the full-resolution decoder's first convolution, on the
-// concatenation of the upsampled coarse features and the skip connection) as a z-marching
-// implicit GEMM.  As zconv16, but the 48-channel planes are too large for a 64 x 4 tile to
-// leave room for two blocks per CU: a block owns a 32 x 4 tile, its input planes (34 x 6
-// voxels with the halo, 48 channels padded to 56 per voxel, so 16-byte rows stay aligned)
-// sit in a 3-plane LDS ring (68.5 KB), and the weights (27 x 16 x 48, the same for every
-// block) are read through the L1 cache.  Wave w computes row y0 + w: two 16-voxel blocks,
-// one 16x16x16 MFMA per (tap, 16-channel chunk, block), weights as A and input as B.
-constexpr int ZDX = 32, ZDY = 4, ZDLX = ZDX + 2, ZDLY = ZDY + 2, ZDC = 48, ZDCP = 56;
-
-__global__ __launch_bounds__(256) void zconv48_kernel(Dims d, View in, const uint16_t* __restrict__ w,
-                                                      const float* __restrict__ bias, int relu, View out, int zlen) {
-  __shared__ __align__(16) uint16_t ring[3][ZDLY][ZDLX][ZDCP];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gx = (d.x + ZDX - 1) / ZDX, gy = (d.y + ZDY - 1) / ZDY;
-  const int b = blockIdx.x;
-  const int bx = b % gx, by = (b / gx) % gy, zc = b / (gx * gy);
-  const int x0 = bx * ZDX, y0 = by * ZDY;
-  const int zb = zc * zlen, ze = min(d.z, zb + zlen);
-  if (zb >= ze) return;
-  constexpr int PARTS = ZDC / 8;  // 16-byte pieces per voxel
-  auto load_plane = [&](int zp) {
-    uint16_t(*dst)[ZDLX][ZDCP] = ring[(zp + 3) % 3];
-    for (int c = threadIdx.x; c < ZDLY * ZDLX * PARTS; c += 256) {
-      const int vox = c / PARTS, part = c % PARTS;
-      const int lx = vox % ZDLX, ly = vox / ZDLX;
-      const int xg = x0 - 1 + lx, yg = y0 - 1 + ly;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (zp >= 0 && zp < d.z && xg >= 0 && xg < d.x && yg >= 0 && yg < d.y)
-        v = *reinterpret_cast<const uint4*>(in.p + (((long)zp * d.y + yg) * d.x + xg) * in.cs + in.off + part * 8);
-      *reinterpret_cast<uint4*>(&dst[ly][lx][part * 8]) = v;
+  // products of the plane in LDS for the output planes in mask (bit dz + 1), dz = -1 starts at 0
+  auto products = [&](auto mask, Acc& a0, Acc& a1, Acc& a2) {
+    constexpr int M = decltype(mask)::value;
+    if constexpr (M & 1)
+#pragma unroll
+      for (int m = 0; m < C::MB; ++m)
+#pragma unroll
+        for (int t = 0; t < C::CTW; ++t) a0.v[m][t] = f4v{0.f, 0.f, 0.f, 0.f};
+    // operands of a step are loaded one step ahead, and no further: registers
+    constexpr int N = C::ROLL ? C::NS / 3 : C::NS;
+    b8v xb[2][C::MB], wa[2][C::WREG ? 1 : 3][C::CTW];
+#pragma unroll(C::ROLL ? 1 : 3)
+    for (int dy = 0; dy < (C::ROLL ? 3 : 1); ++dy) {
+      int wo = dy * 3 * COUT * CIN;
+      if constexpr (C::ROLL) asm volatile("" : "+s"(wo));  // keeps the loads of weights in the loop
+      auto operands = [&](int st) {
+#pragma unroll
+        for (int m = 0; m < C::MB; ++m) {
+          b8v& x = xb[st & 1][m];
+          if constexpr (C::PAIR) {
+            const int j = 2 * st, step = j + 1 < C::NJ ? C::off(j + 1) - C::off(j) : 0;
+            x = F::load(pl + base + hi * step + C::blk(m) + C::off(j));
+            if (j + 1 == C::NJ) x = hi ? F::zero() : x;
+          } else {
+            x = F::load(pl + base + dy * C::LX * C::CP + C::blk(m) + C::off(st));
+          }
+        }
+        if constexpr (!C::WREG)
+#pragma unroll
+          for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+            for (int t = 0; t < C::CTW; ++t)
+              if (M >> dz & 1)
+                wa[st & 1][dz][t] =
+                    dz < C::LDZ ? F::load(wl + (((dz * C::NS + dy * N + st) * C::CT + wg * C::CTW + t) * 64 + lane) * 8)
+                            : F::load(w + wo + (wg * C::CTW * 16 + row) * CIN + kq * 8 +
+                                      ((dz * 9 + st / C::NC) * COUT + t * 16) * CIN + st % C::NC * 32);
+      };
+      operands(0);
+#pragma unroll
+      for (int st = 0; st < N; ++st) {
+        if (st + 1 < N) operands(st + 1);
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) {
+          if (!(M >> dz & 1)) continue;
+          Acc& a = dz == 0 ? a0 : dz == 1 ? a1 : a2;
+#pragma unroll
+          for (int t = 0; t < C::CTW; ++t)
+#pragma unroll
+            for (int m = 0; m < C::MB; ++m)
+              a.v[m][t] = F::mma(C::WREG ? wr[C::WREG ? dz : 0][C::WREG ? st : 0][t] : wa[st & 1][C::WREG ? 0 : dz][t], xb[st & 1][m], a.v[m][t]);
+        }
+        // no load further ahead: registers (32 channels fit)
+        if (CIN != 32) __builtin_amdgcn_sched_barrier(0);
+      }
     }
   };
-  load_plane(zb - 1);
-  load_plane(zb);
-  const int row = lane & 15, kq = lane >> 4;
-  const int yo = y0 + wave;
-  float bv[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) bv[r] = bias ? bias[4 * kq + r] : 0.f;
-  for (int z = zb; z < ze; ++z) {
-    load_plane(z + 1);
-    __syncthreads();
-    f4v acc[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) acc[q] = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int tap = 0; tap < 27; ++tap) {
-      const int dz = tap / 9 - 1, dy = (tap / 3) % 3 - 1, dx = tap % 3 - 1;
-      const uint16_t(*pl)[ZDLX][ZDCP] = ring[(z + dz + 3) % 3];
-      const uint16_t* wp = w + ((size_t)tap * 16 + row) * ZDC + 4 * kq;
-#pragma unroll
-      for (int c = 0; c < ZDC / 16; ++c) {
-        const s4v wa = Frag<4>::load(wp + 16 * c);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          const s4v xb = *reinterpret_cast<const s4v*>(&pl[wave + 1 + dy][q * 16 + row + 1 + dx][16 * c + 4 * kq]);
-          acc[q] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa, xb, acc[q], 0, 0, 0);
-        }
-      }
+  // plane p: its products, the output plane that is done with it, and plane p + 1 into LDS
+  auto plane = [&](auto mask, int p, Acc& a0, Acc& a1, Acc& a2) {
+    constexpr int M = decltype(mask)::value;
+    if (M != 4) fetch(p + 1);
+    products(mask, a0, a1, a2);
+    if (M & 4) store(a2);
+    if (M != 4) {
+      __syncthreads();  // every wave is done with plane p
+      put();
+      __syncthreads();
     }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int xo = x0 + q * 16 + row;
-      if (xo < d.x && yo < d.y) {
-        uint16_t h[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float v = acc[q][r] + bv[r];
-          if (relu) v = fmaxf(v, 0.f);
-          h[r] = f2bf(v);
-        }
-        const uint2 pk = make_uint2((uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16));
-        *reinterpret_cast<uint2*>(out.p + (((long)z * d.y + yo) * d.x + xo) * out.cs + out.off + 4 * kq) = pk;
-      }
-    }
-    __syncthreads();
+  };
+  using std::integral_constant;
+  constexpr integral_constant<int, 1> first{};
+  constexpr integral_constant<int, 2> only{};
+  constexpr integral_constant<int, 3> second{};
+  constexpr integral_constant<int, 4> last{};
+  constexpr integral_constant<int, 6> before{};
+  constexpr integral_constant<int, 7> full{};
+  Acc a, b, c;  // the roles of dz = -1, 0, 1 go round
+  put();
+  __syncthreads();
+  plane(first, zb - 1, b, c, a);
+  if (ze - zb == 1) {
+    plane(only, zb, a, b, c);
+    plane(last, ze, c, a, b);
+    return;
   }
+  plane(second, zb, a, b, c);
+  int p = zb + 1;
+  for (; p + 2 < ze - 1; p += 3) {
+    plane(full, p, c, a, b);
+    plane(full, p + 1, b, c, a);
+    plane(full, p + 2, a, b, c);
+  }
+  for (; p < ze - 1; ++p) {
+    plane(full, p, c, a, b);
+    b = a;
+    a = c;
+  }
+  plane(before, p, c, a, b);
+  plane(last, p + 1, b, c, a);
 }
 
 // Weight and bias gradient of one layer: dw[tap][co][ci] = sum over voxels of dz[v][co] *
@@ -370,13 +405,13 @@ __global__ __launch_bounds__(WGNT) void conv_wgrad_kernel(Dims d, View x, View d
       const b8v bp = __builtin_bit_cast(b8v, make_uint4(s1, s2, s3, __builtin_amdgcn_alignbit(hi, c.w, 16)));
 #pragma unroll
       for (int t = 0; t < CT; ++t) {
-        const b8v a = Frag<8>::load(ds + (t * 16 + row) * WGDS + r * WGX + 8 * kq);
-        acc[0][t] = Frag<8>::mma(a, bm, acc[0][t]);
-        acc[1][t] = Frag<8>::mma(a, b0, acc[1][t]);
-        acc[2][t] = Frag<8>::mma(a, bp, acc[2][t]);
+        const b8v a = Frag::load(ds + (t * 16 + row) * WGDS + r * WGX + 8 * kq);
+        acc[0][t] = Frag::mma(a, bm, acc[0][t]);
+        acc[1][t] = Frag::mma(a, b0, acc[1][t]);
+        acc[2][t] = Frag::mma(a, bp, acc[2][t]);
         if (wave == 4 && ci0 == 0) {  // the centre pair's wave also sums dz (a product with ones)
           const uint32_t one = 0x3f803f80u;
-          bacc[t] = Frag<8>::mma(a, __builtin_bit_cast(b8v, make_uint4(one, one, one, one)), bacc[t]);
+          bacc[t] = Frag::mma(a, __builtin_bit_cast(b8v, make_uint4(one, one, one, one)), bacc[t]);
         }
       }
     }
@@ -577,19 +612,32 @@ void launch_sum_chunks(hipStream_t s, const float* part, int nchunk, long len, f
   hipLaunchKernelGGL(sum_chunks_kernel, dim3(blocks_for(len, 64)), dim3(1024), 0, s, part, nchunk, len, out);
 }
 
-template <int KB>
-void fwd_dispatch(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, const float* bias, int relu, View out,
-                  int cout) {
-  const long nvox = (long)d.x * d.y * d.z;
-  const dim3 g((unsigned)((nvox + 63) / 64));
-  switch (cout / 16) {
-    case 1: hipLaunchKernelGGL((conv_fwd_kernel<KB, 1>), g, dim3(256), 0, s, d, in, cin, w, bias, relu, out); break;
-    case 2: hipLaunchKernelGGL((conv_fwd_kernel<KB, 2>), g, dim3(256), 0, s, d, in, cin, w, bias, relu, out); break;
-    case 3: hipLaunchKernelGGL((conv_fwd_kernel<KB, 3>), g, dim3(256), 0, s, d, in, cin, w, bias, relu, out); break;
-    case 4: hipLaunchKernelGGL((conv_fwd_kernel<KB, 4>), g, dim3(256), 0, s, d, in, cin, w, bias, relu, out); break;
-    case 6: hipLaunchKernelGGL((conv_fwd_kernel<KB, 6>), g, dim3(256), 0, s, d, in, cin, w, bias, relu, out); break;
-    default: break;
-  }
+template <int CIN, int COUT, int UP, bool SMALL>
+void run_tiles(hipStream_t s, Dims d, View in, View up, const uint16_t* w, const float* bias, bool relu, View out,
+               int zlen) {
+  using C = ConvCfg<CIN, COUT, SMALL>;
+  const long cols = (long)((d.x + C::TX - 1) / C::TX) * ((d.y + C::TY - 1) / C::TY);
+  hipLaunchKernelGGL((zconv_kernel<CIN, COUT, UP, SMALL>), dim3((unsigned)(cols * ((d.z + zlen - 1) / zlen))),
+                     dim3(C::NT), 0, s, d, in, up, w, bias, relu ? 1 : 0, out, zlen);
+}
+
+// z-chunk: as long as leaves two blocks per CU, for each chunk reads two planes more
+template <int CIN, int COUT, bool SMALL>
+long conv_blocks(Dims d, int lo, int& zlen) {
+  using C = ConvCfg<CIN, COUT, SMALL>;
+  const long cols = (long)((d.x + C::TX - 1) / C::TX) * ((d.y + C::TY - 1) / C::TY);
+  zlen = 64;
+  while (zlen > lo && cols * ((d.z + zlen - 1) / zlen) < 512) zlen /= 2;
+  return cols * ((d.z + zlen - 1) / zlen);
+}
+
+template <int CIN, int COUT, int UP>
+void run_conv(hipStream_t s, Dims d, View in, View up, const uint16_t* w, const float* bias, bool relu, View out) {
+  int zlen;
+  if (conv_blocks<CIN, COUT, false>(d, 4, zlen) >= 256)
+    return run_tiles<CIN, COUT, UP, false>(s, d, in, up, w, bias, relu, out, zlen);
+  conv_blocks<CIN, COUT, true>(d, 1, zlen);
+  run_tiles<CIN, COUT, UP, true>(s, d, in, up, w, bias, relu, out, zlen);
 }
 
 // tile depth and blocks per 16 input channels of the weight gradient: tiles of four planes,
@@ -612,36 +660,28 @@ WgradPlan wgrad_plan(Dims d, int cin) {
 
 }  // namespace
 
-bool conv_shape_ok(int cin, int cout) {
-  auto ok = [](int c) { return c == 16 || c == 32 || c == 48 || c == 64 || c == 96; };
-  return ok(cin) && (cout == 16 || cout == 32 || cout == 48 || cout == 64 || cout == 96);
-}
-
+// The layers of the network and, with the channels exchanged, their backward data passes; every
+// view's channel stride and offset are multiples of 8, its base 16-byte aligned.
 void launch_conv_fwd(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, const float* bias, bool relu,
-                     View out, int cout) {
-  // the 16 -> 16 layers take the z-marching kernel when the views allow 16-byte vector
-  // access (channel stride and offset multiples of 8)
-  if (cin == 16 && cout == 16 && in.cs % 8 == 0 && in.off % 8 == 0 && out.cs % 4 == 0 && out.off % 4 == 0) {
-    const int gx = (d.x + ZCX - 1) / ZCX, gy = (d.y + ZCY - 1) / ZCY;
-    int zlen = 32;
-    while (zlen > 4 && (long)gx * gy * ((d.z + zlen - 1) / zlen) < 2048) zlen /= 2;
-    const unsigned nb = (unsigned)((long)gx * gy * ((d.z + zlen - 1) / zlen));
-    hipLaunchKernelGGL(zconv16_kernel, dim3(nb), dim3(256), 0, s, d, in, w, bias, relu ? 1 : 0, out, zlen);
-    return;
+                     View out, int cout, View up, int cup) {
+  const int key = cin * 1000 + cout;
+  if (cup > 0) {
+    if (key == 96032 && cup == 64) return run_conv<96, 32, 64>(s, d, in, up, w, bias, relu, out);
+    if (key == 48016 && cup == 32) return run_conv<48, 16, 32>(s, d, in, up, w, bias, relu, out);
+  } else {
+    switch (key) {
+      case 16016: return run_conv<16, 16, 0>(s, d, in, up, w, bias, relu, out);
+      case 16032: return run_conv<16, 32, 0>(s, d, in, up, w, bias, relu, out);
+      case 16048: return run_conv<16, 48, 0>(s, d, in, up, w, bias, relu, out);
+      case 32016: return run_conv<32, 16, 0>(s, d, in, up, w, bias, relu, out);
+      case 32032: return run_conv<32, 32, 0>(s, d, in, up, w, bias, relu, out);
+      case 32064: return run_conv<32, 64, 0>(s, d, in, up, w, bias, relu, out);
+      case 32096: return run_conv<32, 96, 0>(s, d, in, up, w, bias, relu, out);
+      case 64032: return run_conv<64, 32, 0>(s, d, in, up, w, bias, relu, out);
+      case 64064: return run_conv<64, 64, 0>(s, d, in, up, w, bias, relu, out);
+    }
   }
-  // the 48 -> 16 layer likewise (16-byte loads of the input, 8-byte stores of the output)
-  if (cin == ZDC && cout == 16 && in.cs % 8 == 0 && in.off % 8 == 0 && out.cs % 4 == 0 && out.off % 4 == 0) {
-    const int gx = (d.x + ZDX - 1) / ZDX, gy = (d.y + ZDY - 1) / ZDY;
-    int zlen = 32;
-    while (zlen > 4 && (long)gx * gy * ((d.z + zlen - 1) / zlen) < 2048) zlen /= 2;
-    const unsigned nb = (unsigned)((long)gx * gy * ((d.z + zlen - 1) / zlen));
-    hipLaunchKernelGGL(zconv48_kernel, dim3(nb), dim3(256), 0, s, d, in, w, bias, relu ? 1 : 0, out, zlen);
-    return;
-  }
-  if (cin % 32 == 0)
-    fwd_dispatch<8>(s, d, in, cin, w, bias, relu ? 1 : 0, out, cout);
-  else
-    fwd_dispatch<4>(s, d, in, cin, w, bias, relu ? 1 : 0, out, cout);
+  throw std::logic_error("internal: unsupported convolution");
 }
 
 void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db) {

@@ -211,6 +211,7 @@ struct Net {
   struct Acts {
     Dims d1, d2, d3;
     long V1, V2, V3;
+    bool backward = false;
     uint16_t *a1, *cat1, *p1, *a2, *cat2, *p2, *a3, *b3, *g2, *dd2, *g1, *dd1;
     float* o;
     uint16_t *gd1 = nullptr, *gz = nullptr, *gg1 = nullptr, *gcat1 = nullptr, *gd2 = nullptr, *gg2 = nullptr,
@@ -244,7 +245,7 @@ struct Net {
   double train(const TrainData& td, const TrainOpts& to, std::vector<double>& curve);
 
  private:
-  void conv(const Acts& a, int l, Dims d, View in, View out, bool relu);
+  void conv(const Acts& a, int l, Dims d, View in, View out, bool relu, View up = View{nullptr, 0, 0}, int cup = 0);
   void conv_back(const Acts& a, int l, Dims d, View in, View post, View dh, View din);
 };
 

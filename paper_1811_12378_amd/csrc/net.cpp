@@ -118,11 +118,12 @@ Net::Acts Net::acts(Dims d, bool backward) {
   a.V1 = V1;
   a.V2 = V2;
   a.V3 = V3;
+  a.backward = backward;
   a.a1 = b16("net_a1", V1 * 16);
-  a.cat1 = b16("net_cat1", V1 * 48);
+  a.cat1 = b16("net_cat1", V1 * (backward ? 48 : 16));  // (up(d2),) e1
   a.p1 = b16("net_p1", V2 * 16);
   a.a2 = b16("net_a2", V2 * 32);
-  a.cat2 = b16("net_cat2", V2 * 96);
+  a.cat2 = b16("net_cat2", V2 * (backward ? 96 : 32));  // (up(b3),) e2
   a.p2 = b16("net_p2", V3 * 32);
   a.a3 = b16("net_a3", V3 * 64);
   a.b3 = b16("net_b3", V3 * 64);
@@ -158,27 +159,30 @@ Net::Acts Net::acts(Dims d, bool backward) {
   return a;
 }
 
-void Net::conv(const Acts&, int l, Dims d, View in, View out, bool relu) {
+void Net::conv(const Acts&, int l, Dims d, View in, View out, bool relu, View up, int cup) {
   launch_conv_fwd(ctx->stream, d, in, layers[l].cin, wb + layers[l].w_off, p + layers[l].b_off, relu, out,
-                  layers[l].cout);
+                  layers[l].cout, up, cup);
 }
 
+// The decoder's convolutions read the coarse features in place of their up-sampling; only the
+// weight gradients need that in memory.
 void Net::forward(Dims d, const uint16_t* x16, const Acts& a) {
   hipStream_t s = ctx->stream;
   View x{const_cast<uint16_t*>(x16), 16, 0};
+  const View e1 = a.backward ? V(a.cat1, 48, 32) : V(a.cat1, 16), e2 = a.backward ? V(a.cat2, 96, 64) : V(a.cat2, 32);
   conv(a, C1A, a.d1, x, V(a.a1, 16), true);
-  conv(a, C1B, a.d1, V(a.a1, 16), V(a.cat1, 48, 32), true);          // e1 -> cat1[32:48]
-  launch_pool(s, a.d1, V(a.cat1, 48, 32), 16, V(a.p1, 16));
+  conv(a, C1B, a.d1, V(a.a1, 16), e1, true);
+  launch_pool(s, a.d1, e1, 16, V(a.p1, 16));
   conv(a, C2A, a.d2, V(a.p1, 16), V(a.a2, 32), true);
-  conv(a, C2B, a.d2, V(a.a2, 32), V(a.cat2, 96, 64), true);          // e2 -> cat2[64:96]
-  launch_pool(s, a.d2, V(a.cat2, 96, 64), 32, V(a.p2, 32));
+  conv(a, C2B, a.d2, V(a.a2, 32), e2, true);
+  launch_pool(s, a.d2, e2, 32, V(a.p2, 32));
   conv(a, C3A, a.d3, V(a.p2, 32), V(a.a3, 64), true);
   conv(a, C3B, a.d3, V(a.a3, 64), V(a.b3, 64), true);
-  launch_up(s, a.d2, V(a.b3, 64), 64, V(a.cat2, 96, 0));             // up(b3) -> cat2[0:64]
-  conv(a, D2A, a.d2, V(a.cat2, 96), V(a.g2, 32), true);
+  if (a.backward) launch_up(s, a.d2, V(a.b3, 64), 64, V(a.cat2, 96, 0));  // up(b3) -> cat2[0:64]
+  conv(a, D2A, a.d2, e2, V(a.g2, 32), true, V(a.b3, 64), 64);
   conv(a, D2B, a.d2, V(a.g2, 32), V(a.dd2, 32), true);
-  launch_up(s, a.d1, V(a.dd2, 32), 32, V(a.cat1, 48, 0));            // up(d2) -> cat1[0:32]
-  conv(a, D1A, a.d1, V(a.cat1, 48), V(a.g1, 16), true);
+  if (a.backward) launch_up(s, a.d1, V(a.dd2, 32), 32, V(a.cat1, 48, 0));  // up(d2) -> cat1[0:32]
+  conv(a, D1A, a.d1, e1, V(a.g1, 16), true, V(a.dd2, 32), 32);
   conv(a, D1B, a.d1, V(a.g1, 16), V(a.dd1, 16), true);
   launch_head_fwd(s, V(a.dd1, 16), a.V1, p + head_off, p + head_off + 32, a.o);
 }

@@ -17,9 +17,10 @@ struct View {
   int cs, off;
 };
 
-bool conv_shape_ok(int cin, int cout);
+// cup > 0: the first cup input channels are the x2 up-sampling of `up` (half the grid), the
+// others `in`
 void launch_conv_fwd(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, const float* bias, bool relu,
-                     View out, int cout);
+                     View out, int cout, View up = View{nullptr, 0, 0}, int cup = 0);
 long wgrad_part_floats(Dims d, int cin, int cout);
 // weight gradient dw [27][cout][cin] and bias gradient db [cout] (part: wgrad_part_floats)
 void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db);
