@@ -236,7 +236,7 @@ struct Net {
   void zero_moments();
   void refresh_bf16();
   Acts acts(Dims d, bool backward);
-  void forward(Dims d, const uint16_t* x16, const Acts& a);
+  void forward(Dims d, const uint16_t* x16, const Acts& a, float* o);
   void backward(const uint16_t* x16, const Acts& a);
   double train_step(Dims d, const uint16_t* x16, const float* target, float lr, bool update, bool read_loss,
                     int loss_kind);

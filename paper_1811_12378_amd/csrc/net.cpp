@@ -166,16 +166,14 @@ void Net::conv(const Acts&, int l, Dims d, View in, View out, bool relu, View up
 
 // The decoder's convolutions read the coarse features in place of their up-sampling; only the
 // weight gradients need that in memory.
-void Net::forward(Dims d, const uint16_t* x16, const Acts& a) {
+void Net::forward(Dims d, const uint16_t* x16, const Acts& a, float* o) {
   hipStream_t s = ctx->stream;
   View x{const_cast<uint16_t*>(x16), 16, 0};
   const View e1 = a.backward ? V(a.cat1, 48, 32) : V(a.cat1, 16), e2 = a.backward ? V(a.cat2, 96, 64) : V(a.cat2, 32);
   conv(a, C1A, a.d1, x, V(a.a1, 16), true);
-  conv(a, C1B, a.d1, V(a.a1, 16), e1, true);
-  launch_pool(s, a.d1, e1, 16, V(a.p1, 16));
+  launch_conv_pool(s, a.d1, V(a.a1, 16), 16, wb + layers[C1B].w_off, p + layers[C1B].b_off, e1, V(a.p1, 16));
   conv(a, C2A, a.d2, V(a.p1, 16), V(a.a2, 32), true);
-  conv(a, C2B, a.d2, V(a.a2, 32), e2, true);
-  launch_pool(s, a.d2, e2, 32, V(a.p2, 32));
+  launch_conv_pool(s, a.d2, V(a.a2, 32), 32, wb + layers[C2B].w_off, p + layers[C2B].b_off, e2, V(a.p2, 32));
   conv(a, C3A, a.d3, V(a.p2, 32), V(a.a3, 64), true);
   conv(a, C3B, a.d3, V(a.a3, 64), V(a.b3, 64), true);
   if (a.backward) launch_up(s, a.d2, V(a.b3, 64), 64, V(a.cat2, 96, 0));  // up(b3) -> cat2[0:64]
@@ -183,8 +181,13 @@ void Net::forward(Dims d, const uint16_t* x16, const Acts& a) {
   conv(a, D2B, a.d2, V(a.g2, 32), V(a.dd2, 32), true);
   if (a.backward) launch_up(s, a.d1, V(a.dd2, 32), 32, V(a.cat1, 48, 0));  // up(d2) -> cat1[0:32]
   conv(a, D1A, a.d1, e1, V(a.g1, 16), true, V(a.dd2, 32), 32);
-  conv(a, D1B, a.d1, V(a.g1, 16), V(a.dd1, 16), true);
-  launch_head_fwd(s, V(a.dd1, 16), a.V1, p + head_off, p + head_off + 32, a.o);
+  if (a.backward) {  // which needs d1
+    conv(a, D1B, a.d1, V(a.g1, 16), V(a.dd1, 16), true);
+    launch_head_fwd(s, V(a.dd1, 16), a.V1, p + head_off, p + head_off + 32, o);
+  } else {
+    launch_conv_head(s, a.d1, V(a.g1, 16), wb + layers[D1B].w_off, p + layers[D1B].b_off, V(a.dd1, 16), p + head_off,
+                     p + head_off + 32, o);
+  }
 }
 
 // gradient of one ReLU conv layer: dz = dh * (post > 0); weight/bias grads; optional input grad
@@ -226,7 +229,7 @@ double Net::train_step(Dims d, const uint16_t* x16, const float* target, float l
   const Acts a = acts(d, true);
   double* lpart = (double*)ctx->ws.get("net_lpart", 4 * 1024 * sizeof(double));
   double* lsum = (double*)ctx->ws.get("net_lsum", 5 * sizeof(double));
-  forward(d, x16, a);
+  forward(d, x16, a, a.o);
   if (loss_kind == 2) {
     float* pb = (float*)ctx->ws.get("net_rp", (size_t)a.V1 * 2 * sizeof(float));
     float* dpb = (float*)ctx->ws.get("net_rdp", (size_t)a.V1 * 2 * sizeof(float));
@@ -249,9 +252,7 @@ double Net::train_step(Dims d, const uint16_t* x16, const float* target, float l
 }
 
 void Net::eval(Dims d, const uint16_t* x16, float* out) {
-  const Acts a = acts(d, false);
-  forward(d, x16, a);
-  HFCI_HIP(hipMemcpyAsync(out, a.o, (size_t)a.V1 * 2 * sizeof(float), hipMemcpyDeviceToDevice, ctx->stream));
+  forward(d, x16, acts(d, false), out);
 }
 
 // z = s * N(r / s) with s = rms(r): the preconditioner applied to complex128 vectors.
@@ -267,7 +268,7 @@ void Net::apply(const Op& op, int nvec, const double2* r, double2* z) {
     launch_sumsq_c128(s, n, r + k * n, part);
     launch_finish_rms(s, part, rms_blocks(n), (double)n, scale);
     launch_prep_input_c128(s, n, r + k * n, op.kappa32, (float)(1.0 / op.s_h2), scale, x16);
-    forward(d, x16, a);
+    forward(d, x16, a, a.o);
     launch_output_c128(s, n, a.o, scale, z + k * n);
   }
 }

@@ -17,10 +17,22 @@ struct View {
   int cs, off;
 };
 
+// what a convolution does with a finished output plane besides (or instead of) storing it
+struct ConvTail {
+  View pool{nullptr, 0, 0};
+  const float *hw = nullptr, *hb = nullptr;
+  float* o = nullptr;
+};
 // cup > 0: the first cup input channels are the x2 up-sampling of `up` (half the grid), the
 // others `in`
 void launch_conv_fwd(hipStream_t s, Dims d, View in, int cin, const uint16_t* w, const float* bias, bool relu,
                      View out, int cout, View up = View{nullptr, 0, 0}, int cup = 0);
+// ch -> ch (16 or 32) ReLU layer and the 2x2x2 average of its output (even sides)
+void launch_conv_pool(hipStream_t s, Dims d, View in, int ch, const uint16_t* w, const float* bias, View out,
+                      View pool);
+// 16 -> 16 ReLU layer and the head; h, its output, may be left unwritten
+void launch_conv_head(hipStream_t s, Dims d, View in, const uint16_t* w, const float* bias, View h, const float* W,
+                      const float* b, float* o);
 long wgrad_part_floats(Dims d, int cin, int cout);
 // weight gradient dw [27][cout][cin] and bias gradient db [cout] (part: wgrad_part_floats)
 void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db);
