@@ -399,6 +399,13 @@ hfci_status hfci_op_create_spectral(hfci_ctx* ctx, int nx, int ny, int nz, doubl
   op->form = 3;
   op->b1 = -op->kmax;
   op->b2 = op->s * lmax - op->kmin;
+  try {
+    DeviceGuard dg(op->device);
+    spectral_tables(*op);
+  } catch (...) {
+    hfci_op_destroy(op);
+    throw;
+  }
   *out = op;
   return HFCI_OK;
   HFCI_API_END
@@ -448,6 +455,7 @@ void hfci_op_destroy(hfci_op* op) {
   // operator may be released after its context.
   if (op->kappa64) (void)hipFree(op->kappa64);
   if (op->kappa32) (void)hipFree(op->kappa32);
+  if (op->sfft_mem) (void)hipFree(op->sfft_mem);
   if (prev >= 0) (void)hipSetDevice(prev);
   delete op;
 }

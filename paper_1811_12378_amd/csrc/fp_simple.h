@@ -38,6 +38,7 @@ struct SimpleFactor {
   const T2* y1;                // per system (kFacAdd)
   const int* active;           // [nsys] (device)
   const int* host_active;      // [nsys] (host): the systems this launch runs
+  const int* list;             // those systems in turn (device)
   double* partial;             // [nsys][nblk] (kFacResid)
   int nrhs, nsys;
 };
@@ -86,6 +87,7 @@ void fp_simple(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int
   a.f = f;
   a.y1 = y1;
   a.active = active;
+  a.list = list;
   a.partial = partial;
   a.nrhs = nrhs;
   a.nsys = nsys;

@@ -172,6 +172,10 @@ struct Op {
   // points, [b1, b2] x [-rho2, 0] the box of Thm 3.2's remark); 3: A with the
   // Fourier-spectral Laplacian of Sec. 7.1 on a periodic grid
   int form = 1;
+  // form 3, sides of prime factors up to 7: the tables of its transforms (one allocation)
+  bool smooth = false;
+  SpecFft sfft;
+  void* sfft_mem = nullptr;
 };
 
 struct Contour {
@@ -328,6 +332,7 @@ template <typename T2>
 void shifted_solve_spectral(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int fixed_steps,
                             double reduce, int max_steps, int* steps_out, FciStats& st);
 void spectral_release(Ctx& ctx);
+void spectral_tables(Op& op);  // Op::sfft
 // case_two.hip: factors k and k + 1 of a case-two fixed-point step in one pass (a.k is k;
 // kind: kFacResid or kFacInF on the input, kFacAdd or kFacDual on the output); false for
 // other kind bits

@@ -135,6 +135,33 @@ struct SpecArgs {
   int nrhs, cstride, k;
 };
 int spec_blocks(const GridDesc& g);
+
+// sfft.hip: the transforms of the spectral operator on grids of small prime factors.  Stage i of
+// an axis splits blocks of n / (r_0 .. r_{i-1}) values r_i ways.
+constexpr int kAxisStages = 12;
+struct AxisStages {
+  int ns = 0;
+  int r[kAxisStages];
+};
+struct SpecFft {
+  AxisStages x, y, z;
+  const float2* tw32 = nullptr;   // exp(-2 pi i k / n), k < n, of x, y and z in turn
+  const double2* tw64 = nullptr;
+  const double* lam = nullptr;    // s (2 pi min(m, n - m) / (n h))^2 by place after the stages, same order
+};
+bool sfft_stages(int n, AxisStages& a);           // false: a prime factor above 7, or a side of one point
+bool sfft_fits(const GridDesc& g, bool f64);      // LDS
+// out_v = in_{sys[v]} (sys null: in_v) transformed, times Lambda / N and back over z
+template <typename T2>
+void launch_sfft_fwd(hipStream_t st, const GridDesc& g, const SpecFft& sf, const T2* in, T2* out, const int* sys,
+                     int nvec);
+// and back over x and y: S in_v in place, or the factor of system sys[v] (sys null: v) with S w_v at
+// a.sw + v n, partial [nsys][nz]; false for an unsupported kind
+template <typename T2>
+void launch_sfft_inv(hipStream_t st, const GridDesc& g, const SpecFft& sf, T2* c, int nvec);
+template <typename T2>
+bool launch_sfft_factor(hipStream_t st, const GridDesc& g, const SpecFft& sf, const void* K, int kind,
+                        const SpecArgs<T2>& a, const int* sys, int nvec);
 // c_v *= lambda / N (the diagonal between a forward and an unnormalised inverse FFT)
 template <typename T2>
 void launch_spec_scale(hipStream_t st, T2* c, int nvec, const GridDesc& g, double s, double h);

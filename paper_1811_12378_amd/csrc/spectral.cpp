@@ -1,12 +1,14 @@
 // The Fourier-spectral operator (Sec. 7.1, eq. eig-Laplacian-spectral) on the GPU:
-// S x = F^H Lambda F x with library 3D FFTs (hipFFT, batched over vectors, in place) and
-// the diagonal between them (spec_scale_kernel); the shifted solves run the loop of
-// fp_simple.h with one batched FFT pair and one epilogue launch per factor.
+// S x = F^H Lambda F x in three passes of sfft.hip where the grid allows it, else with library
+// 3D FFTs (hipFFT, batched over vectors, in place) and the diagonal between them
+// (spec_scale_kernel); the shifted solves run the loop of fp_simple.h with one batched transform
+// pair per factor, the factor itself in the last pass or, after the library, in a launch of its own.
 #include <hipfft/hipfft.h>
 
 #include <algorithm>
 #include <cmath>
 #include <string>
+#include <vector>
 
 #include "fp_simple.h"
 
@@ -61,7 +63,17 @@ void exec(hipfftHandle p, double2* x, int dir) {
 
 namespace {
 
-// x_v <- S x_v for v < nvec, in place
+// The passes of sfft.hip: sides of prime factors up to 7, planes and 64 columns within LDS, and
+// planes of 256 points at least (its residual partials, one per plane, then need no more room
+// than the others').  Shifted solves of 16 systems, library and own: complex64 32^3 1118 and 876 us,
+// 48^3 2952 and 1246, 80 x 70 x 90 4583 and 2648, 96^3 5034 and 3200; complex128 32^3 1202 and
+// 1027 us, 96^3 6550 and 4837.  No grid that fits was found on which the library is faster.
+template <typename T2>
+bool own_fft(const Op& op) {
+  return op.smooth && sfft_fits(op.g, sizeof(T2) == 16) && op.g.nz <= spec_blocks(op.g);
+}
+
+// x_v <- S x_v for v < nvec, in place, by the library
 template <typename T2>
 void spectral_S_inplace(const Op& op, int nvec, T2* x) {
   Ctx& ctx = *op.ctx;
@@ -77,6 +89,12 @@ void spectral_S_inplace(const Op& op, int nvec, T2* x) {
 // out_v = S in_v for v < nvec (out distinct from in)
 template <typename T2>
 void spectral_S(const Op& op, int nvec, const T2* in, T2* out) {
+  if (own_fft<T2>(op)) {
+    if (nvec <= 0) return;
+    launch_sfft_fwd<T2>(op.ctx->stream, op.g, op.sfft, in, out, nullptr, nvec);
+    launch_sfft_inv<T2>(op.ctx->stream, op.g, op.sfft, out, nvec);
+    return;
+  }
   HFCI_HIP(hipMemcpyAsync(out, in, (size_t)nvec * op.n * sizeof(T2), hipMemcpyDeviceToDevice, op.ctx->stream));
   spectral_S_inplace<T2>(op, nvec, out);
 }
@@ -92,6 +110,46 @@ void spectral_apply(const Op& op, int nvec, const T2* x, T2* y, double sr, doubl
 template void spectral_apply<float2>(const Op&, int, const float2*, float2*, double, double);
 template void spectral_apply<double2>(const Op&, int, const double2*, double2*, double, double);
 
+void spectral_tables(Op& op) {
+  const int side[3] = {op.g.nx, op.g.ny, op.g.nz};
+  AxisStages* ax[3] = {&op.sfft.x, &op.sfft.y, &op.sfft.z};
+  op.smooth = true;
+  for (int a = 0; a < 3; ++a) op.smooth = op.smooth && sfft_stages(side[a], *ax[a]);
+  if (!op.smooth) return;
+  std::vector<double> lam;
+  std::vector<double2> tw64;
+  std::vector<float2> tw32;
+  for (int a = 0; a < 3; ++a) {
+    const int n = side[a];
+    for (int place = 0; place < n; ++place) {
+      int m = 0, rest = place, L = n, w = 1;  // the digits of the place, the other way round
+      for (int i = 0; i < ax[a]->ns; ++i) {
+        L /= ax[a]->r[i];
+        m += rest / L * w;
+        rest %= L;
+        w *= ax[a]->r[i];
+      }
+      const double k = 2.0 * M_PI / (n * op.h) * std::min(m, n - m);
+      lam.push_back(op.s * k * k);
+      const long double t = 2.0L * 3.14159265358979323846264338327950288L * place / n;
+      const double c = (double)std::cos(t), s = (double)-std::sin(t);
+      tw64.push_back(double2{c, s});
+      tw32.push_back(float2{(float)c, (float)s});
+    }
+  }
+  const size_t t = lam.size();
+  HFCI_HIP(hipMalloc(&op.sfft_mem, t * (sizeof(double) + sizeof(double2) + sizeof(float2))));
+  double2* d64 = (double2*)op.sfft_mem;
+  double* dl = (double*)(d64 + t);
+  float2* d32 = (float2*)(dl + t);
+  HFCI_HIP(hipMemcpy(d64, tw64.data(), t * sizeof(double2), hipMemcpyHostToDevice));
+  HFCI_HIP(hipMemcpy(dl, lam.data(), t * sizeof(double), hipMemcpyHostToDevice));
+  HFCI_HIP(hipMemcpy(d32, tw32.data(), t * sizeof(float2), hipMemcpyHostToDevice));
+  op.sfft.tw64 = d64;
+  op.sfft.lam = dl;
+  op.sfft.tw32 = d32;
+}
+
 void spectral_release(Ctx& ctx) {
   for (auto& kv : ctx.fft) (void)hipfftDestroy((hipfftHandle)kv.second);
   ctx.fft.clear();
@@ -105,9 +163,11 @@ void shifted_solve_spectral(const Op& op, const Contour& c, int nrhs, const T2* 
   const void* K = kappa_for<T2>(op);
   const int nsys = c.J * nrhs;
   T2* sw = (T2*)ctx.ws.get("sp_sw", (size_t)nsys * op.n * sizeof(T2));
+  const bool own = own_fft<T2>(op);
   int* slot_sys = (int*)ctx.ws.get("sp_slot_sys", (size_t)nsys * sizeof(int));
   int* sys_slot = (int*)ctx.ws.get("sp_sys_slot", (size_t)nsys * sizeof(int));
-  fp_simple<T2>(op, c, nrhs, f, y, fixed_steps, reduce, max_steps, steps_out, st, spec_blocks(op.g), false,
+  fp_simple<T2>(op, c, nrhs, f, y, fixed_steps, reduce, max_steps, steps_out, st, own ? op.g.nz : spec_blocks(op.g),
+                false,
                 [&](const SimpleFactor<T2>& sf) {
                   // S w of the factor's inputs, one batched transform: the right-hand sides
                   // (step one's first factor), all vectors when every system iterates, else
@@ -119,7 +179,10 @@ void shifted_solve_spectral(const Op& op, const Contour& c, int nrhs, const T2* 
                   int nact = 0;
                   for (int k = 0; k < sf.nsys; ++k) nact += sf.host_active[k] != 0;
                   const int* slot = nullptr;
-                  if ((sf.kind & kFacInF) != 0) {
+                  const bool last = own && (sf.kind & kFacInF) == 0;  // the factor in the last pass
+                  if (last) {
+                    launch_sfft_fwd<T2>(s, op.g, op.sfft, sf.in, sw, sf.list, nact);
+                  } else if ((sf.kind & kFacInF) != 0) {
                     spectral_S<T2>(op, sf.nrhs, sf.in, sw);
                   } else if (nact == sf.nsys) {
                     spectral_S<T2>(op, sf.nsys, sf.in, sw);
@@ -144,7 +207,8 @@ void shifted_solve_spectral(const Op& op, const Contour& c, int nrhs, const T2* 
                   a.nrhs = sf.nrhs;
                   a.cstride = c.cstride;
                   a.k = sf.k;
-                  const bool ok = launch_spec_factor_slots<T2>(s, op.g, K, sf.kind, sf.nsys, a, slot);
+                  const bool ok = last ? launch_sfft_factor<T2>(s, op.g, op.sfft, K, sf.kind, a, sf.list, nact)
+                                       : launch_spec_factor_slots<T2>(s, op.g, K, sf.kind, sf.nsys, a, slot);
                   HFCI_REQUIRE(ok, "internal: unsupported factor kind");
                 });
 }
