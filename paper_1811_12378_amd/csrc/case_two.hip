@@ -119,7 +119,11 @@ __device__ __forceinline__ double block_sum_nt(double v, double* sh) {
 // z-marching: a workgroup of PTX x PTY threads takes tiles of PTX x PTY columns by pcz
 // planes (b2_chunk; a grid-stride loop over the tiles of its system, so the residual partials keep
 // the single factor's layout); each thread carries x1 and x2 of planes k - 1, k and k + 1
-// of its column in registers and gathers only the in-plane neighbours through the cache.
+// of its column in registers.  The x-neighbours are the next lanes (a wave is a row of 64; its
+// end lanes load theirs), the y-neighbours come through the cache, and all that plane k + 1
+// needs is loaded while plane k is computed: with one or two systems still iterating a pass is
+// bound by the latency of these loads (one complex64 system of 128^3: a middle pair 35.0 us when
+// a plane's loads were waited for in turn, 28.8 now; shifted solves 25.7 -> 20.3 ms).
 // With a grid width that is a multiple of 8 the workgroups of one XCD (blockIdx.x % 8)
 // sweep one contiguous eighth of the tiles.
 constexpr int PTX = 64, PTY = NT / PTX;
@@ -129,16 +133,28 @@ struct Pt2 {
   Cx<T> a, b;  // x1, x2 at a point
 };
 
-// Waves per SIMD asked of the compiler: 8 (64 VGPRs) for the complex64 kinds that fit
-// without spilling (single factors; the middle pairs and the first pair of step one), else
-// its own choice.
-template <typename T, int KIND, int NF>
+// the value of lane l - 1 or l + 1; where there is none, `end`
+constexpr int kLeft = 0x138, kRight = 0x130;
+template <int CTRL>
+__device__ __forceinline__ float next_lane(float end, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ double next_lane(double end, double v) {
+  return __hiloint2double(
+      __builtin_amdgcn_update_dpp(__double2hiint(end), __double2hiint(v), CTRL, 0xf, 0xf, false),
+      __builtin_amdgcn_update_dpp(__double2loint(end), __double2loint(v), CTRL, 0xf, 0xf, false));
+}
+
+// Waves per SIMD asked of the compiler: 5 (up to 96 VGPRs) hold a complex64 pair's two planes of
+// operands without spilling; complex128 as the compiler chooses.
+template <typename T>
 constexpr int b2_zm_waves() {
-  return (sizeof(T) == 4 && (NF == 1 || (KIND & (kFacResid | kFacAdd | kFacDual)) == 0)) ? 8 : 1;
+  return sizeof(T) == 4 ? 5 : 1;
 }
 
 template <typename T, int KIND, int NF>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<T, KIND, NF>()))) void b2_zm_kernel(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<T>()))) void b2_zm_kernel(
     GridDesc g, const T* __restrict__ K, B2Args<typename Vec2<T>::t> a, int pcz) {
   static_assert(NF == 1 || NF == 2, "one or two factors per pass");
   using T2 = typename Vec2<T>::t;
@@ -173,39 +189,85 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<
   // the first factor's x1' at a point from x1, x2 there (zero at a ghost)
   auto fac1 = [&](const Pt2<T>& u) { return b2_fac(a1r, a1i, b1r, b1i, b2_block1(u.a, u.b, z0r, z0i), u.a); };
   double acc = 0.0;
+  // what a plane needs beside the column itself: its rows' neighbours, those of the end lanes,
+  // kappa and the epilogue's vectors
+  struct Around {
+    Pt2<T> ym, yp, e;
+    T kap;
+    T2 a1, a2;
+  };
   for (int t = t_lo + (int)(blockIdx.x / nsl); t < t_hi; t += (int)(gridDim.x / nsl)) {
     const int i = (t % gx) * PTX + tx, j = ((t / gx) % gy) * PTY + ty, zc = t / (gx * gy);
     const int zb = zc * pcz, ze = min(g.nz, zb + pcz);
-    if (i >= g.nx || j >= g.ny) continue;  // no barrier inside the tile loop
-    const size_t col = (size_t)i + sy * (size_t)j;
-    Pt2<T> xm = zb > 0 ? ld2(col + sz * (size_t)(zb - 1)) : zero;
-    Pt2<T> xc = ld2(col + sz * (size_t)zb);
+    if (j >= g.ny) continue;  // uniform over the wave; no barrier inside the tile loop
+    // lanes past the grid's columns load valid addresses and hold zeros, as the ghosts do
+    const bool iok = i < g.nx, jm = j > 0, jp = j + 1 < g.ny;
+    const bool end = (tx == 0 && i > 0) || (tx == PTX - 1 && i + 1 < g.nx);
+    const size_t col = (size_t)min(i, g.nx - 1) + sy * (size_t)j;
+    const size_t ce = end ? (tx == 0 ? col - 1 : col + 1) : col, cm = jm ? col - sy : col, cp = jp ? col + sy : col;
+    auto pick = [](bool ok, const Pt2<T>& u) {
+      return Pt2<T>{{ok ? u.a.x : (T)0, ok ? u.a.y : (T)0}, {ok ? u.b.x : (T)0, ok ? u.b.y : (T)0}};
+    };
+    auto centre = [&](int k) { return pick(iok && k >= 0 && k < g.nz, ld2(col + sz * (size_t)min(max(k, 0), g.nz - 1))); };
+    auto around = [&](int k) {
+      const size_t o = sz * (size_t)k;
+      Around r;
+      r.ym = pick(iok && jm, ld2(cm + o));
+      r.yp = pick(iok && jp, ld2(cp + o));
+      r.e = zero;
+      if (end) r.e = ld2(ce + o);
+      r.kap = K[col + o];
+      if constexpr (ADD || RESID) {
+        const T2* A = RESID ? F : Y1;
+        r.a1 = A[col + o];
+        r.a2 = A[npt + col + o];
+      }
+      return r;
+    };
+    Pt2<T> xm = centre(zb - 1), xc = centre(zb), xp = centre(zb + 1);
+    Cx<T> vm = fac1(xm), vc = fac1(xc);
+    Around ar = around(zb);
+#pragma unroll 2
     for (int k = zb; k < ze; ++k) {
+      // plane k + 1's loads (the last plane's again at the end)
+      const Pt2<T> x2p = centre(min(k + 2, ze));
+      const Around an = around(min(k + 1, ze - 1));
       const size_t p = col + sz * (size_t)k;
-      const Pt2<T> xp = k + 1 < g.nz ? ld2(p + sz) : zero;
+      const Cx<T> vp = fac1(xp);
       // neighbour sums of x1 (first factor) and of the first factor's x1' (second factor),
       // in the order -x, +x, -y, +y, -z, +z
-      T nr = (T)0, ni = (T)0, mr = (T)0, mi = (T)0;
-      auto add = [&](const Pt2<T>& u) {
-        nr += u.a.x;
-        ni += u.a.y;
-        if constexpr (NF == 2) {
-          const Cx<T> v = fac1(u);
-          mr += v.x;
-          mi += v.y;
-        }
-      };
-      if (i > 0) add(ld2(p - 1));
-      if (i + 1 < g.nx) add(ld2(p + 1));
-      if (j > 0) add(ld2(p - sy));
-      if (j + 1 < g.ny) add(ld2(p + sy));
-      if (k > 0) add(xm);
-      if (k + 1 < g.nz) add(xp);
+      T nr = next_lane<kLeft>(ar.e.a.x, xc.a.x), ni = next_lane<kLeft>(ar.e.a.y, xc.a.y);
+      nr += next_lane<kRight>(ar.e.a.x, xc.a.x);
+      ni += next_lane<kRight>(ar.e.a.y, xc.a.y);
+      nr += ar.ym.a.x;
+      ni += ar.ym.a.y;
+      nr += ar.yp.a.x;
+      ni += ar.yp.a.y;
+      nr += xm.a.x;
+      ni += xm.a.y;
+      nr += xp.a.x;
+      ni += xp.a.y;
+      T mr = (T)0, mi = (T)0;
+      if constexpr (NF == 2) {
+        const Cx<T> ve = fac1(ar.e), v0 = fac1(ar.ym), v1 = fac1(ar.yp);
+        mr = next_lane<kLeft>(ve.x, vc.x);
+        mi = next_lane<kLeft>(ve.y, vc.y);
+        mr += next_lane<kRight>(ve.x, vc.x);
+        mi += next_lane<kRight>(ve.y, vc.y);
+        mr += v0.x;
+        mi += v0.y;
+        mr += v1.x;
+        mi += v1.y;
+        mr += vm.x;
+        mi += vm.y;
+        mr += vp.x;
+        mi += vp.y;
+      }
       const Cx<T> x1 = xc.a, x2 = xc.b;
-      const T kap = K[p], dmp = b2_damping<T>(g, i, j, k);
+      const T kap = ar.kap, dmp = b2_damping<T>(g, i, j, k);
       const Cx<T> o1 = b2_block1(x1, x2, z0r, z0i), o2 = b2_block2(g, x1, x2, nr, ni, kap, dmp, z0r, z0i);
       // the first factor at the point (t1, t2), then the second (a pair)
-      const Cx<T> t1 = b2_fac(a1r, a1i, b1r, b1i, o1, x1), t2 = b2_fac(a1r, a1i, b1r, b1i, o2, x2);
+      const Cx<T> t1 = vc, t2 = b2_fac(a1r, a1i, b1r, b1i, o2, x2);
       Cx<T> c1 = t1, c2 = t2;
       if constexpr (NF == 2) {
         const Cx<T> p1 = b2_block1(t1, t2, z0r, z0i), p2 = b2_block2(g, t1, t2, mr, mi, kap, dmp, z0r, z0i);
@@ -218,29 +280,35 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<
       w2.x = c2.x;
       w2.y = c2.y;
       if constexpr (ADD) {
-        const T2 e1 = Y1[p], e2 = Y1[npt + p];
+        const T2 e1 = RESID ? Y1[p] : ar.a1, e2 = RESID ? Y1[npt + p] : ar.a2;
         w1.x += e1.x;
         w1.y += e1.y;
         w2.x += e2.x;
         w2.y += e2.y;
       }
-      O[p] = w1;
-      O[npt + p] = w2;
-      if constexpr (DUAL) {
-        O2[p] = w1;
-        O2[npt + p] = w2;
-      }
-      if constexpr (RESID) {
-        const double zr = pd.zz_re, zi = pd.zz_im;
-        const T2 g1 = F[p], g2 = F[npt + p];
-        const double r1x = (double)g1.x - (double)o1.x + zr * (double)x1.x - zi * (double)x1.y;
-        const double r1y = (double)g1.y - (double)o1.y + zr * (double)x1.y + zi * (double)x1.x;
-        const double r2x = (double)g2.x - (double)o2.x + zr * (double)x2.x - zi * (double)x2.y;
-        const double r2y = (double)g2.y - (double)o2.y + zr * (double)x2.y + zi * (double)x2.x;
-        acc += r1x * r1x + r1y * r1y + r2x * r2x + r2y * r2y;
+      if (iok) {
+        O[p] = w1;
+        O[npt + p] = w2;
+        if constexpr (DUAL) {
+          O2[p] = w1;
+          O2[npt + p] = w2;
+        }
+        if constexpr (RESID) {
+          const double zr = pd.zz_re, zi = pd.zz_im;
+          const T2 g1 = ar.a1, g2 = ar.a2;
+          const double r1x = (double)g1.x - (double)o1.x + zr * (double)x1.x - zi * (double)x1.y;
+          const double r1y = (double)g1.y - (double)o1.y + zr * (double)x1.y + zi * (double)x1.x;
+          const double r2x = (double)g2.x - (double)o2.x + zr * (double)x2.x - zi * (double)x2.y;
+          const double r2y = (double)g2.y - (double)o2.y + zr * (double)x2.y + zi * (double)x2.x;
+          acc += r1x * r1x + r1y * r1y + r2x * r2x + r2y * r2y;
+        }
       }
       xm = xc;
       xc = xp;
+      xp = x2p;
+      vm = vc;
+      vc = vp;
+      ar = an;
     }
   }
   if constexpr (RESID) {
