@@ -370,7 +370,13 @@ __global__ __launch_bounds__(FTT) void fp_test_kernel(const double* __restrict__
     if (active[s] == 0) continue;  // converged earlier: its partial row was not written
     const double* row = partial + (size_t)s * nblk;
     double v = 0.0;
-    for (int i = lane; i < nblk; i += 64) v += row[i];
+    for (int i = lane; i < nblk; i += 64 * 8) {  // eight loads at a time, summed in turn
+      double t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) t[u] = i + 64 * u < nblk ? row[i + 64 * u] : 0.0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v += t[u];
+    }
     v = wave_sum(v);
     if (lane == 0) {
       const double r2 = v;

@@ -31,13 +31,15 @@ void shifted_solve_case_two(const Op& op, const Contour& c, int nrhs, const T2* 
                   a.wout2 = sf.out2;
                   a.coef = c.d_coef;
                   a.poles = c.d_poles;
-                  a.active = sf.active;
+                  a.list = sf.list;
                   a.partial = sf.partial;
                   a.nrhs = sf.nrhs;
                   a.cstride = c.cstride;
                   a.k = sf.k;
-                  const bool ok = sf.nfac == 2 ? launch_b2_pair<T2>(s, op.g, K, sf.kind, sf.nsys, a)
-                                               : launch_b2_factor<T2>(s, op.g, K, sf.kind, sf.nsys, a);
+                  int count = 0;
+                  for (int k = 0; k < sf.nsys; ++k) count += sf.host_active[k] != 0;
+                  const bool ok = sf.nfac == 2 ? launch_b2_pair<T2>(s, op.g, K, sf.kind, count, a)
+                                               : launch_b2_factor<T2>(s, op.g, K, sf.kind, count, a);
                   HFCI_REQUIRE(ok, "internal: unsupported factor kind");
                 });
 }

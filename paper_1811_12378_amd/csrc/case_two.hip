@@ -9,8 +9,8 @@
 // pass over HBM, over all shifted systems, with the epilogues of the case-one kernels
 // (residual partials, adding y1, a second output): b2_zm_kernel, one thread per grid
 // column marching in z.  Then the plain product (B - shift) x, the step-size partials and
-// the FP64 residual: one thread per grid point.  Both blocks per thread; the neighbours come
-// through the cache (no LDS staging).
+// the FP64 residual: one thread per grid point, the neighbours through the cache.  Both blocks per
+// thread, no LDS staging.
 #include "kernels.h"
 
 namespace hfci {
@@ -161,8 +161,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(b2_zm_waves<
   constexpr bool RESID = (KIND & kFacResid) != 0, ADD = (KIND & kFacAdd) != 0, DUAL = (KIND & kFacDual) != 0,
                  INF = (KIND & kFacInF) != 0;
   __shared__ double sh[NT / 64];
-  const int s = blockIdx.y;
-  if (a.active[s] == 0) return;  // block-uniform: stopped systems are skipped
+  const int s = a.list[blockIdx.y];
   const int pole = s / a.nrhs, r = s % a.nrhs;
   const size_t npt = (size_t)g.nx * g.ny * g.nz, n2 = 2 * npt;
   // the second coefficient only for a pair: k + 1 may lie past the pole's entries otherwise

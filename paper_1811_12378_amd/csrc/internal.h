@@ -337,7 +337,7 @@ void spectral_tables(Op& op);  // Op::sfft
 // kind: kFacResid or kFacInF on the input, kFacAdd or kFacDual on the output); false for
 // other kind bits
 template <typename T2>
-bool launch_b2_pair(hipStream_t st, const GridDesc& g, const void* K, int kind, int nsys, const B2Args<T2>& a);
+bool launch_b2_pair(hipStream_t st, const GridDesc& g, const void* K, int kind, int count, const B2Args<T2>& a);
 // case_two.cpp: the shifted solves of a case-two operator (op.form == 2)
 template <typename T2>
 void shifted_solve_case_two(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int fixed_steps,

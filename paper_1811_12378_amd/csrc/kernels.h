@@ -99,8 +99,9 @@ struct FactorArgs {
 
 // Case two (eq. mat-2x2): factors of the fixed-point step on B = iC - I, whose vectors
 // hold 2 n values (x1 then x2).  System s = pole * nrhs + rhs, vectors strided by 2 n;
-// kind bits as for the case-one factors (kFacResid, kFacAdd, kFacInF, kFacDual), and a
-// system with active[s] == 0 is skipped.  Residual partials: [nsys][b2_blocks(g)].
+// kind bits as for the case-one factors (kFacResid, kFacAdd, kFacInF, kFacDual).  A
+// launch runs the systems list[0 .. count) only: the returning blocks of 15 stopped systems cost a
+// pass of the last one about 1 us of 28.  Residual partials: [nsys][b2_blocks(g)].
 template <typename T2>
 struct B2Args {
   const T2* win;           // input, per system (the right-hand sides, per rhs, with kFacInF)
@@ -110,14 +111,14 @@ struct B2Args {
   T2* wout2;               // second output, per system (kFacDual)
   const FactorCoef* coef;  // [pole][cstride]; this launch uses entry k
   const PoleDev* poles;    // [pole]
-  const int* active;       // [nsys]
+  const int* list;         // systems of this launch
   double* partial;         // [nsys][b2_blocks(g)] (kFacResid)
   int nrhs, cstride, k;
 };
 int b2_blocks(const GridDesc& g);
 // false for an unsupported combination of kind bits (nothing is launched)
 template <typename T2>
-bool launch_b2_factor(hipStream_t st, const GridDesc& g, const void* K, int kind, int nsys, const B2Args<T2>& a);
+bool launch_b2_factor(hipStream_t st, const GridDesc& g, const void* K, int kind, int count, const B2Args<T2>& a);
 // Fourier-spectral operator (Sec. 7.1): kernels around the library FFTs.  SpecArgs are the
 // factor arguments of B2Args plus sw = S w of the inputs (indexed as the inputs).
 template <typename T2>
