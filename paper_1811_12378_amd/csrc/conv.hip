@@ -19,6 +19,7 @@
 // (k = voxel) whose per-block partial sums are reduced in a fixed order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <stdexcept>
 #include <type_traits>
@@ -514,23 +515,25 @@ __global__ __launch_bounds__(WGNT) void conv_wgrad_kernel(Dims d, View x, View d
 }
 
 // sum over chunks, fixed order: out[i] = sum_c part[c][i].  A block
-// takes 64 values; 16 waves sum every 16th chunk each, then the 16 sums in order (one thread
+// takes 64 values of a job; 16 waves sum every 16th chunk each, then the 16 sums in order (one thread
 // per value over all chunks left most of the chip idle: 22 us per layer on 64^3 voxels).
-__global__ __launch_bounds__(1024) void sum_chunks_kernel(const float* __restrict__ part, int nchunk, long len,
-                                                          float* __restrict__ out) {
+__global__ __launch_bounds__(1024) void sum_chunks_kernel(SumJobs jobs) {
   __shared__ float sh[16][64];
+  int j = 0;
+  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.j[j + 1].blk0) ++j;  // uniform
+  const SumJob job = jobs.j[j];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long i = (long)blockIdx.x * 64 + lane;
+  const int i = ((int)blockIdx.x - job.blk0) * 64 + lane;
   float s = 0.f;
-  if (i < len)
-    for (int c = wave; c < nchunk; c += 16) s += part[(size_t)c * len + i];
+  if (i < job.len)
+    for (int c = wave; c < job.nchunk; c += 16) s += job.part[(size_t)c * job.len + i];
   sh[wave][lane] = s;
   __syncthreads();
-  if (wave == 0 && i < len) {
+  if (wave == 0 && i < job.len) {
     s = 0.f;
 #pragma unroll
     for (int w = 0; w < 16; ++w) s += sh[w][lane];
-    out[i] = s;
+    job.out[i] = s;
   }
 }
 
@@ -550,75 +553,94 @@ __global__ void f32_to_bf16_kernel(const float* __restrict__ a, long n, uint16_t
   if (i < n) b[i] = f2bf(a[i]);
 }
 
+// The elementwise passes take 8 channels (16 bytes) per thread; views are multiples of 8 wide.
+struct alignas(16) Piece {
+  uint16_t h[8];
+};
+__device__ __forceinline__ Piece piece_at(const View& v, long vox, int part) {
+  return *reinterpret_cast<const Piece*>(v.p + vox * v.cs + v.off + 8 * part);
+}
+__device__ __forceinline__ void put_piece(const View& v, long vox, int part, const Piece& x) {
+  *reinterpret_cast<Piece*>(v.p + vox * v.cs + v.off + 8 * part) = x;
+}
+// the coarse voxel above fine voxel v
+__device__ __forceinline__ long parent_of(long v, const Dims& d) {
+  const Coord f = coord_of(v, d);
+  return ((long)(f.z / 2) * (d.y / 2) + f.y / 2) * (d.x / 2) + f.x / 2;
+}
+// sums of the 8 fine voxels below coarse voxel vc, in the order z, y, x
+__device__ __forceinline__ void sum_children(const Dims& d, const View& in, long vc, int part, float (&s)[8]) {
+  const Coord q = coord_of(vc, Dims{d.z / 2, d.y / 2, d.x / 2});
+#pragma unroll
+  for (int c = 0; c < 8; ++c) s[c] = 0.f;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const long v = ((long)(2 * q.z + (k >> 2)) * d.y + 2 * q.y + ((k >> 1) & 1)) * d.x + 2 * q.x + (k & 1);
+    const Piece x = piece_at(in, v, part);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s[c] += bf2f(x.h[c]);
+  }
+}
+
 // relu backward: dzo[v][c] = dh[v][c] if post[v][c] > 0 else 0
-__global__ void relu_mask_kernel(View dh, View post, int C, long nvox, View dzo) {
+__global__ void relu_mask_kernel(View dh, View post, int parts, long nvox, View dzo) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nvox * C) return;
-  const long v = i / C;
-  const int c = (int)(i % C);
-  const uint16_t pv = post.p[v * post.cs + post.off + c];
-  const bool pos = (pv & 0x8000u) == 0 && (pv & 0x7fffu) != 0;
-  dzo.p[v * dzo.cs + dzo.off + c] = pos ? dh.p[v * dh.cs + dh.off + c] : (uint16_t)0;
+  if (i >= nvox * parts) return;
+  const long v = i / parts;
+  const int part = (int)(i % parts);
+  const Piece pv = piece_at(post, v, part);
+  Piece x = piece_at(dh, v, part);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const bool pos = (pv.h[c] & 0x8000u) == 0 && (pv.h[c] & 0x7fffu) != 0;
+    x.h[c] = pos ? x.h[c] : (uint16_t)0;
+  }
+  put_piece(dzo, v, part, x);
 }
 
 // 2x2x2 average pooling (fine dims d, coarse dims d/2)
-__global__ void pool_kernel(Dims d, View in, int C, View out) {
-  const Dims e{d.z / 2, d.y / 2, d.x / 2};
+__global__ void pool_kernel(Dims d, View in, int parts, long n, View out) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n = (long)e.x * e.y * e.z * C;
   if (i >= n) return;
-  const int c = (int)(i % C);
-  const long vc = i / C;
-  const Coord q = coord_of(vc, e);
-  float s = 0.f;
-  for (int k = 0; k < 8; ++k) {
-    const long v = ((long)(2 * q.z + (k >> 2)) * d.y + 2 * q.y + ((k >> 1) & 1)) * d.x + 2 * q.x + (k & 1);
-    s += bf2f(in.p[v * in.cs + in.off + c]);
-  }
-  out.p[vc * out.cs + out.off + c] = f2bf(0.125f * s);
+  float s[8];
+  sum_children(d, in, i / parts, (int)(i % parts), s);
+  Piece x;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) x.h[c] = f2bf(0.125f * s[c]);
+  put_piece(out, i / parts, (int)(i % parts), x);
 }
 
-// adjoint of pooling: out[v][c] (+)= in[parent(v)][c] / 8  (fine dims d)
-__global__ void pool_back_kernel(Dims d, View in, int C, View out, View addend) {
+// adjoint of pooling: out[v][c] = in[parent(v)][c] / 8 + addend[v][c]  (fine dims d)
+__global__ void pool_back_kernel(Dims d, View in, int parts, long n, View out, View addend) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n = (long)d.x * d.y * d.z * C;
   if (i >= n) return;
-  const int c = (int)(i % C);
-  const long v = i / C;
-  const Coord f = coord_of(v, d);
-  const long vc = ((long)(f.z / 2) * (d.y / 2) + f.y / 2) * (d.x / 2) + f.x / 2;
-  float s = 0.125f * bf2f(in.p[vc * in.cs + in.off + c]);
-  if (addend.p) s += bf2f(addend.p[v * addend.cs + addend.off + c]);
-  out.p[v * out.cs + out.off + c] = f2bf(s);
+  const long v = i / parts;
+  const int part = (int)(i % parts);
+  const Piece a = piece_at(in, parent_of(v, d), part), b = piece_at(addend, v, part);
+  Piece x;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) x.h[c] = f2bf(0.125f * bf2f(a.h[c]) + bf2f(b.h[c]));
+  put_piece(out, v, part, x);
 }
 
 // nearest-neighbour x2 up-sampling (fine dims d)
-__global__ void up_kernel(Dims d, View in, int C, View out) {
+__global__ void up_kernel(Dims d, View in, int parts, long n, View out) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n = (long)d.x * d.y * d.z * C;
   if (i >= n) return;
-  const int c = (int)(i % C);
-  const long v = i / C;
-  const Coord f = coord_of(v, d);
-  const long vc = ((long)(f.z / 2) * (d.y / 2) + f.y / 2) * (d.x / 2) + f.x / 2;
-  out.p[v * out.cs + out.off + c] = in.p[vc * in.cs + in.off + c];
+  const long v = i / parts;
+  put_piece(out, v, (int)(i % parts), piece_at(in, parent_of(v, d), (int)(i % parts)));
 }
 
 // adjoint of up-sampling: out[vc][c] = sum of the 8 children (coarse dims d/2)
-__global__ void up_back_kernel(Dims d, View in, int C, View out) {
-  const Dims e{d.z / 2, d.y / 2, d.x / 2};
+__global__ void up_back_kernel(Dims d, View in, int parts, long n, View out) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long n = (long)e.x * e.y * e.z * C;
   if (i >= n) return;
-  const int c = (int)(i % C);
-  const long vc = i / C;
-  const Coord q = coord_of(vc, e);
-  float s = 0.f;
-  for (int k = 0; k < 8; ++k) {
-    const long v = ((long)(2 * q.z + (k >> 2)) * d.y + 2 * q.y + ((k >> 1) & 1)) * d.x + 2 * q.x + (k & 1);
-    s += bf2f(in.p[v * in.cs + in.off + c]);
-  }
-  out.p[vc * out.cs + out.off + c] = f2bf(s);
+  float s[8];
+  sum_children(d, in, i / parts, (int)(i % parts), s);
+  Piece x;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) x.h[c] = f2bf(s[c]);
+  put_piece(out, i / parts, (int)(i % parts), x);
 }
 
 // 1x1x1 head 16 -> 2 channels: o[v][k] = b[k] + sum_c W[k][c] h[v][c]  (FP32 out)
@@ -636,38 +658,45 @@ __global__ void head_fwd_kernel(View h, long nvox, const float* __restrict__ W, 
   o[2 * v + 1] = o1;
 }
 
-// head backward: dh[v][c] = sum_k dout[v][k] W[k][c] (bf16); partial dW/db per block
+// head backward: dh[v][c] = sum_k dout[v][k] W[k][c] (bf16); partial dW/db per block.  A thread
+// keeps its 34 sums over the voxels it takes; one reduction per block (a tree through LDS for
+// each of the 34 and every 256 voxels: 36 us on 64^3 voxels).
+constexpr int kHeadBlocks = 512;
 __global__ __launch_bounds__(256) void head_back_kernel(View h, long nvox, const float* __restrict__ W,
                                                         const float* __restrict__ dout, View dh,
                                                         float* __restrict__ part /* [blk][34] */) {
-  __shared__ float sh[256];
-  const long v = (long)blockIdx.x * 256 + threadIdx.x;
-  float g0 = 0.f, g1 = 0.f;
-  float x[16];
-  if (v < nvox) {
-    g0 = dout[2 * v];
-    g1 = dout[2 * v + 1];
-    for (int c = 0; c < 16; ++c) {
-      x[c] = bf2f(h.p[v * h.cs + h.off + c]);
-      dh.p[v * dh.cs + dh.off + c] = f2bf(g0 * W[c] + g1 * W[16 + c]);
+  __shared__ float sh[4][34];
+  float s[34];
+#pragma unroll
+  for (int k = 0; k < 34; ++k) s[k] = 0.f;
+  for (long v = (long)blockIdx.x * 256 + threadIdx.x; v < nvox; v += (long)gridDim.x * 256) {
+    const float g0 = dout[2 * v], g1 = dout[2 * v + 1];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const Piece x = piece_at(h, v, p);
+      Piece y;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const float f = bf2f(x.h[c]);
+        s[8 * p + c] += g0 * f;
+        s[16 + 8 * p + c] += g1 * f;
+        y.h[c] = f2bf(g0 * W[8 * p + c] + g1 * W[16 + 8 * p + c]);
+      }
+      put_piece(dh, v, p, y);
     }
-  } else {
-    for (int c = 0; c < 16; ++c) x[c] = 0.f;
+    s[32] += g0;
+    s[33] += g1;
   }
+#pragma unroll
   for (int k = 0; k < 34; ++k) {
-    float val;
-    if (k < 16) val = g0 * x[k];
-    else if (k < 32) val = g1 * x[k - 16];
-    else val = k == 32 ? g0 : g1;
-    sh[threadIdx.x] = val;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) part[(size_t)blockIdx.x * 34 + k] = sh[0];
-    __syncthreads();
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s[k] += __shfl_down(s[k], o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = s[k];
   }
+  __syncthreads();
+  if (threadIdx.x < 34)
+    part[(size_t)blockIdx.x * 34 + threadIdx.x] =
+        (sh[0][threadIdx.x] + sh[1][threadIdx.x]) + (sh[2][threadIdx.x] + sh[3][threadIdx.x]);
 }
 
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
@@ -686,10 +715,6 @@ __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, 
 }
 
 unsigned blocks_for(long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
-
-void launch_sum_chunks(hipStream_t s, const float* part, int nchunk, long len, float* out) {
-  hipLaunchKernelGGL(sum_chunks_kernel, dim3(blocks_for(len, 64)), dim3(1024), 0, s, part, nchunk, len, out);
-}
 
 template <int CIN, int COUT, int UP, bool SMALL, Tail TAIL>
 void run_tiles(hipStream_t s, Dims d, View in, View up, const uint16_t* w, const float* bias, bool relu, View out,
@@ -795,7 +820,8 @@ void launch_conv_head(hipStream_t s, Dims d, View in, const uint16_t* w, const f
   launch_head_fwd(s, h, (long)d.x * d.y * d.z, W, b, o);
 }
 
-void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db) {
+void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db,
+                       SumJobs& sums) {
   const WgradPlan p = wgrad_plan(d, cin);
   const dim3 g(p.nblk, cin / 16);
   float* bpart = part + (size_t)p.nblk * 27 * cout * cin;
@@ -805,8 +831,18 @@ void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout
     case 4: hipLaunchKernelGGL((conv_wgrad_kernel<4>), g, dim3(WGNT), 0, s, d, x, dz, cin, p.tz, p.ntiles, part, bpart); break;
     default: break;
   }
-  launch_sum_chunks(s, part, p.nblk, 27L * cout * cin, dw);
-  launch_sum_chunks(s, bpart, p.nblk, cout, db);
+  sums.add(part, dw, p.nblk, 27 * cout * cin);
+  sums.add(bpart, db, p.nblk, cout);
+}
+
+void SumJobs::add(const float* part, float* out, int nchunk, int len) {
+  const int b = n == 0 ? 0 : j[n - 1].blk0 + (j[n - 1].len + 63) / 64;
+  j[n++] = SumJob{part, out, nchunk, len, b};
+}
+
+void launch_sums(hipStream_t s, const SumJobs& sums) {
+  const SumJob& last = sums.j[sums.n - 1];
+  hipLaunchKernelGGL(sum_chunks_kernel, dim3(last.blk0 + (last.len + 63) / 64), dim3(1024), 0, s, sums);
 }
 
 long wgrad_part_floats(Dims d, int cin, int cout) {
@@ -823,40 +859,41 @@ void launch_f32_to_bf16(hipStream_t s, const float* a, long n, uint16_t* b) {
 }
 
 void launch_relu_mask(hipStream_t s, View dh, View post, int C, long nvox, View dz) {
-  hipLaunchKernelGGL(relu_mask_kernel, dim3(blocks_for(nvox * C)), dim3(256), 0, s, dh, post, C, nvox, dz);
+  hipLaunchKernelGGL(relu_mask_kernel, dim3(blocks_for(nvox * (C / 8))), dim3(256), 0, s, dh, post, C / 8, nvox, dz);
 }
 
 void launch_pool(hipStream_t s, Dims d, View in, int C, View out) {
-  const long n = (long)(d.x / 2) * (d.y / 2) * (d.z / 2) * C;
-  hipLaunchKernelGGL(pool_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C, out);
+  const long n = (long)(d.x / 2) * (d.y / 2) * (d.z / 2) * (C / 8);
+  hipLaunchKernelGGL(pool_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C / 8, n, out);
 }
 
 void launch_pool_back(hipStream_t s, Dims d, View in, int C, View out, View addend) {
-  const long n = (long)d.x * d.y * d.z * C;
-  hipLaunchKernelGGL(pool_back_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C, out, addend);
+  const long n = (long)d.x * d.y * d.z * (C / 8);
+  hipLaunchKernelGGL(pool_back_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C / 8, n, out, addend);
 }
 
 void launch_up(hipStream_t s, Dims d, View in, int C, View out) {
-  const long n = (long)d.x * d.y * d.z * C;
-  hipLaunchKernelGGL(up_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C, out);
+  const long n = (long)d.x * d.y * d.z * (C / 8);
+  hipLaunchKernelGGL(up_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C / 8, n, out);
 }
 
 void launch_up_back(hipStream_t s, Dims d, View in, int C, View out) {
-  const long n = (long)(d.x / 2) * (d.y / 2) * (d.z / 2) * C;
-  hipLaunchKernelGGL(up_back_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C, out);
+  const long n = (long)(d.x / 2) * (d.y / 2) * (d.z / 2) * (C / 8);
+  hipLaunchKernelGGL(up_back_kernel, dim3(blocks_for(n)), dim3(256), 0, s, d, in, C / 8, n, out);
 }
 
 void launch_head_fwd(hipStream_t s, View h, long nvox, const float* W, const float* b, float* o) {
   hipLaunchKernelGGL(head_fwd_kernel, dim3(blocks_for(nvox)), dim3(256), 0, s, h, nvox, W, b, o);
 }
 
-long head_part_floats(long nvox) { return ((nvox + 255) / 256) * 34; }
+static unsigned head_blocks(long nvox) { return (unsigned)std::min<long>((nvox + 255) / 256, kHeadBlocks); }
+long head_part_floats(long nvox) { return (long)head_blocks(nvox) * 34; }
 
 void launch_head_back(hipStream_t s, View h, long nvox, const float* W, const float* dout, View dh, float* part,
-                      float* dWb /* [34]: dW (32) then db (2) */) {
-  const unsigned nb = blocks_for(nvox);
+                      float* dWb /* [34]: dW (32) then db (2) */, SumJobs& sums) {
+  const unsigned nb = head_blocks(nvox);
   hipLaunchKernelGGL(head_back_kernel, dim3(nb), dim3(256), 0, s, h, nvox, W, dout, dh, part);
-  launch_sum_chunks(s, part, (int)nb, 34L, dWb);
+  sums.add(part, dWb, (int)nb, 34);
 }
 
 void launch_adam(hipStream_t s, float* p, const float* g, float* m, float* v, long n, float lr, float b1, float b2,

@@ -250,7 +250,8 @@ struct Net {
 
  private:
   void conv(const Acts& a, int l, Dims d, View in, View out, bool relu, View up = View{nullptr, 0, 0}, int cup = 0);
-  void conv_back(const Acts& a, int l, Dims d, View in, View post, View dh, View din);
+  void conv_back(const Acts& a, int l, Dims d, View in, View post, View dh, View din, float*& part,
+                 SumJobs& sums);
 };
 
 // ---- params.cpp ----

@@ -152,7 +152,7 @@ Net::Acts Net::acts(Dims d, bool backward) {
     long part = head_part_floats(V1);
     for (int l = 0; l < kNL; ++l) {
       const Dims dl = (l < C2A || l >= D1A) ? a.d1 : ((l < C3A || l >= D2A) ? a.d2 : a.d3);
-      part = std::max(part, wgrad_part_floats(dl, layers[l].cin, layers[l].cout));
+      part += wgrad_part_floats(dl, layers[l].cin, layers[l].cout);
     }
     a.part = (float*)ws.get("net_part", (size_t)part * sizeof(float));
   }
@@ -191,13 +191,15 @@ void Net::forward(Dims d, const uint16_t* x16, const Acts& a, float* o) {
 }
 
 // gradient of one ReLU conv layer: dz = dh * (post > 0); weight/bias grads; optional input grad
-void Net::conv_back(const Acts& a, int l, Dims d, View in, View post, View dh, View din) {
+void Net::conv_back(const Acts& a, int l, Dims d, View in, View post, View dh, View din, float*& part,
+                    SumJobs& sums) {
   hipStream_t s = ctx->stream;
   const long nv = (long)d.x * d.y * d.z;
   const int ci = layers[l].cin, co = layers[l].cout;
   const View dz = V(a.gz, co);
   launch_relu_mask(s, dh, post, co, nv, dz);
-  launch_conv_wgrad(s, d, in, ci, dz, co, a.part, g + layers[l].w_off, g + layers[l].b_off);
+  launch_conv_wgrad(s, d, in, ci, dz, co, part, g + layers[l].w_off, g + layers[l].b_off, sums);
+  part += wgrad_part_floats(d, ci, co);
   if (din.p) launch_conv_fwd(s, d, dz, co, wt + layers[l].w_off, nullptr, false, din, ci);
 }
 
@@ -205,22 +207,26 @@ void Net::backward(const uint16_t* x16, const Acts& a) {
   hipStream_t s = ctx->stream;
   View x{const_cast<uint16_t*>(x16), 16, 0};
   const View none{nullptr, 0, 0};
-  launch_head_back(s, V(a.dd1, 16), a.V1, p + head_off, a.dout, V(a.gd1, 16), a.part, g + head_off);
-  conv_back(a, D1B, a.d1, V(a.g1, 16), V(a.dd1, 16), V(a.gd1, 16), V(a.gg1, 16));
-  conv_back(a, D1A, a.d1, V(a.cat1, 48), V(a.g1, 16), V(a.gg1, 16), V(a.gcat1, 48));
+  float* part = a.part;
+  SumJobs sums;
+  launch_head_back(s, V(a.dd1, 16), a.V1, p + head_off, a.dout, V(a.gd1, 16), part, g + head_off, sums);
+  part += head_part_floats(a.V1);
+  conv_back(a, D1B, a.d1, V(a.g1, 16), V(a.dd1, 16), V(a.gd1, 16), V(a.gg1, 16), part, sums);
+  conv_back(a, D1A, a.d1, V(a.cat1, 48), V(a.g1, 16), V(a.gg1, 16), V(a.gcat1, 48), part, sums);
   launch_up_back(s, a.d1, V(a.gcat1, 48, 0), 32, V(a.gd2, 32));
-  conv_back(a, D2B, a.d2, V(a.g2, 32), V(a.dd2, 32), V(a.gd2, 32), V(a.gg2, 32));
-  conv_back(a, D2A, a.d2, V(a.cat2, 96), V(a.g2, 32), V(a.gg2, 32), V(a.gcat2, 96));
+  conv_back(a, D2B, a.d2, V(a.g2, 32), V(a.dd2, 32), V(a.gd2, 32), V(a.gg2, 32), part, sums);
+  conv_back(a, D2A, a.d2, V(a.cat2, 96), V(a.g2, 32), V(a.gg2, 32), V(a.gcat2, 96), part, sums);
   launch_up_back(s, a.d2, V(a.gcat2, 96, 0), 64, V(a.gb3, 64));
-  conv_back(a, C3B, a.d3, V(a.a3, 64), V(a.b3, 64), V(a.gb3, 64), V(a.ga3, 64));
-  conv_back(a, C3A, a.d3, V(a.p2, 32), V(a.a3, 64), V(a.ga3, 64), V(a.gp2, 32));
+  conv_back(a, C3B, a.d3, V(a.a3, 64), V(a.b3, 64), V(a.gb3, 64), V(a.ga3, 64), part, sums);
+  conv_back(a, C3A, a.d3, V(a.p2, 32), V(a.a3, 64), V(a.ga3, 64), V(a.gp2, 32), part, sums);
   // de2 = dcat2[64:96] + pool^T(dp2)
   launch_pool_back(s, a.d2, V(a.gp2, 32), 32, V(a.ge2, 32), V(a.gcat2, 96, 64));
-  conv_back(a, C2B, a.d2, V(a.a2, 32), V(a.cat2, 96, 64), V(a.ge2, 32), V(a.ga2, 32));
-  conv_back(a, C2A, a.d2, V(a.p1, 16), V(a.a2, 32), V(a.ga2, 32), V(a.gp1, 16));
+  conv_back(a, C2B, a.d2, V(a.a2, 32), V(a.cat2, 96, 64), V(a.ge2, 32), V(a.ga2, 32), part, sums);
+  conv_back(a, C2A, a.d2, V(a.p1, 16), V(a.a2, 32), V(a.ga2, 32), V(a.gp1, 16), part, sums);
   launch_pool_back(s, a.d1, V(a.gp1, 16), 16, V(a.ge1, 16), V(a.gcat1, 48, 32));
-  conv_back(a, C1B, a.d1, V(a.a1, 16), V(a.cat1, 48, 32), V(a.ge1, 16), V(a.ga1, 16));
-  conv_back(a, C1A, a.d1, x, V(a.a1, 16), V(a.ga1, 16), none);
+  conv_back(a, C1B, a.d1, V(a.a1, 16), V(a.cat1, 48, 32), V(a.ge1, 16), V(a.ga1, 16), part, sums);
+  conv_back(a, C1A, a.d1, x, V(a.a1, 16), V(a.ga1, 16), none, part, sums);
+  launch_sums(s, sums);
 }
 
 double Net::train_step(Dims d, const uint16_t* x16, const float* target, float lr, bool update, bool read_loss,

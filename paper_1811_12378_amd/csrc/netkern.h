@@ -33,9 +33,24 @@ void launch_conv_pool(hipStream_t s, Dims d, View in, int ch, const uint16_t* w,
 // 16 -> 16 ReLU layer and the head; h, its output, may be left unwritten
 void launch_conv_head(hipStream_t s, Dims d, View in, const uint16_t* w, const float* bias, View h, const float* W,
                       const float* b, float* o);
+// The sums over blocks of every gradient of a backward pass, one launch (a launch for each of the
+// 21 cost 6.6 us): out[i] = sum over chunks of part[chunk][i], len values; job j's blocks start
+// at blk0.  The kernels that write the partials add theirs; each keeps its own part until then.
+struct SumJob {
+  const float* part;
+  float* out;
+  int nchunk, len, blk0;
+};
+struct SumJobs {
+  SumJob j[21];
+  int n = 0;
+  void add(const float* part, float* out, int nchunk, int len);
+};
+void launch_sums(hipStream_t s, const SumJobs& sums);
 long wgrad_part_floats(Dims d, int cin, int cout);
 // weight gradient dw [27][cout][cin] and bias gradient db [cout] (part: wgrad_part_floats)
-void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db);
+void launch_conv_wgrad(hipStream_t s, Dims d, View x, int cin, View dz, int cout, float* part, float* dw, float* db,
+                       SumJobs& sums);
 void launch_flip_transpose(hipStream_t s, const uint16_t* w, int cout, int cin, uint16_t* wt);
 void launch_f32_to_bf16(hipStream_t s, const float* a, long n, uint16_t* b);
 void launch_relu_mask(hipStream_t s, View dh, View post, int C, long nvox, View dz);
@@ -46,7 +61,7 @@ void launch_up_back(hipStream_t s, Dims d, View in, int C, View out);
 void launch_head_fwd(hipStream_t s, View h, long nvox, const float* W, const float* b, float* o);
 long head_part_floats(long nvox);
 void launch_head_back(hipStream_t s, View h, long nvox, const float* W, const float* dout, View dh, float* part,
-                      float* dWb);
+                      float* dWb, SumJobs& sums);
 void launch_adam(hipStream_t s, float* p, const float* g, float* m, float* v, long n, float lr, float b1, float b2,
                  float eps, int step, uint16_t* pb);
 
