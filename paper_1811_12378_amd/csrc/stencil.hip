@@ -1564,7 +1564,7 @@ const KernelTune& tune_of(const GridDesc& g) {
 }
 
 // nfill: the systems of a launch whose blocks write no partials: an unset shape may then take chunks
-// down to 2 planes where those of 8 leave fewer than two blocks per CU
+// down to 2 planes where those of 8 leave CUs without a block
 template <typename T>
 Shape shape_for(const GridDesc& g, int nsys, int nfill = 0) {
   const KernelTune& t = tune_of<T>(g);
@@ -1575,7 +1575,7 @@ Shape shape_for(const GridDesc& g, int nsys, int nfill = 0) {
     // keep >= ~2048 blocks per system on large grids, chunks of >= 8 planes
     cz = 32;
     while (cz > 8 && (long)gx * gy * ((g.nz + cz - 1) / cz) < 2048) cz /= 2;
-    while (nfill > 0 && cz > 2 && (long)gx * gy * ((g.nz + cz - 1) / cz) * nfill < 512) cz /= 2;
+    while (nfill > 0 && cz > 2 && (long)gx * gy * ((g.nz + cz - 1) / cz) * nfill < 256) cz /= 2;
   }
   sh.czlen = cz;
   sh.nzc = (g.nz + cz - 1) / cz;
