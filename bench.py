@@ -90,6 +90,8 @@ def middle_kernel_name(t, triple=False):
     """The library's kernel for the middle factors of a fixed-point step at launch shape t
     (triple: the three-factor passes of shapes with fuse 2)."""
     kern, ty, pd, _, fuse = t[:5]
+    if fuse and kern <= 1:
+        return "zrows_kernel (up to four middle factors of a fixed-point step per pass, planes in registers)"
     if triple:
         return ("ztrip_kernel (three middle factors of a fixed-point step per pass on 64 x 18 tiles, "
                 "streams loaded straight into LDS)")
@@ -99,8 +101,6 @@ def middle_kernel_name(t, triple=False):
     if fuse and kern == 2:
         return ("zpair_dma_kernel<0, %d> (two middle factors of a fixed-point step per pass, streams loaded "
                 "straight into LDS)" % (4 if pd >= 3 else 2))
-    if fuse:
-        return "zpair_kernel<float, 0, %d> (two middle factors of a fixed-point step per pass)" % (2 if pd >= 3 else 1)
     return "%s<float, EpiFactor<float, 0>, %d, %d> (middle factor of a fixed-point step)" % (
         "zlds_kernel" if kern == 1 else "zmarch_kernel", ty, pd)
 
@@ -108,14 +108,14 @@ def middle_kernel_name(t, triple=False):
 def traffic_kernel(t, triple=False):
     """Kernel-name key of the counter summary for the middle kernel at launch shape t."""
     kern, _, pd, _, fuse = t[:5]
+    if fuse and kern <= 1:
+        return "zrows_kernel"
     if triple:
         return "ztrip_kernel"
     if fuse and kern == 3:
         return "zpair_tall_kernel<0>"
     if fuse and kern == 2:
         return "zpair_dma_kernel<0, %d>" % (4 if pd >= 3 else 2)
-    if fuse:
-        return "zpair_kernel<float, 0, %d>" % (2 if pd >= 3 else 1)
     return "zlds_kernel" if kern == 1 else "zmarch_kernel"
 
 
