@@ -256,10 +256,12 @@ hfci_status hfci_apply(const hfci_op* op, hfci_c128 shift, int prec, int nvec,
  * As hfci_op_create, with the discrete Laplacian replaced by the Fourier-spectral one on
  * a periodic grid: S = F^H Lambda F, lambda = s sum_j (2 pi min(m_j, N_j - m_j)/(N_j h))^2
  * for the Fourier mode m (the paper's (l_min/N)^2 sum_j min(i_j^2, (N - i_j)^2)), applied
- * with library 3D FFTs; kappa and the damping layer as for hfci_op_create.  The box
+ * with transforms of the library's own where the sides have no prime factor above 7 and a
+ * plane fits on a CU (to 140 x 140 in HFCI_F32, 98 x 98 in HFCI_F64), else with hipFFT's;
+ * kappa and the damping layer as for hfci_op_create.  The box
  * reported by hfci_op_info is [-kappa_max, lambda_max - kappa_min] x [-rho2, 0].
  * Accepted by hfci_op_info, hfci_op_get_tune, hfci_apply, hfci_contour_create / get / q,
- * hfci_shifted_solve (one FFT pair and one epilogue launch per fixed-point factor),
+ * hfci_shifted_solve (one batched transform pair per fixed-point factor),
  * hfci_fci_apply and hfci_solve (precond FCI or NONE, k_in = 0); the other entry points
  * return HFCI_E_STATE.  Errors: as hfci_op_create. */
 hfci_status hfci_op_create_spectral(hfci_ctx* ctx, int nx, int ny, int nz, double h,

@@ -1,7 +1,7 @@
 // Kernels of the Fourier-spectral operator (Sec. 7.1, eq. eig-Laplacian-spectral):
-// A = S - kappa - i D with S = F^H Lambda F on a periodic grid.  The FFTs are library
-// transforms (spectral.cpp); these kernels are the diagonal Lambda between them and the
-// pointwise epilogues that turn S w into a factor of the fixed-point step, a product
+// A = S - kappa - i D with S = F^H Lambda F on a periodic grid.  The FFTs are those of
+// sfft.hip or library transforms (spectral.cpp); these kernels are the diagonal Lambda between the
+// library's and the pointwise epilogues that turn S w into a factor of the fixed-point step, a product
 // with A - shift, the step-size partials and the FP64 residual.
 #include <cmath>
 
