@@ -55,7 +55,6 @@ class Workspace {
   void set_arena(void* base, size_t cap);
   void clear_arena();
   size_t arena_used() const { return arena_used_; }
-  bool arena_set() const { return arena_ != nullptr; }
 
  private:
   struct Buf {

@@ -221,10 +221,10 @@ struct Launch {
   // nf.  The output must not alias the input.
   static bool factor_rows(hipStream_t st, const GridDesc& g, const void* kappa, const FactorArgs<T2>& a, int kind,
                           int nf, const RowsShape& sh);
-  // max_blocks > 0 bounds per_sys where some geometry allows it
-  static RowsShape rows_shape(const GridDesc& g, int nf, int kind, int count, int max_blocks = 0);
-  // upper bound of per_sys of the kinds that form residuals, for any count
-  static int rows_max_blocks(const GridDesc& g, int nf);
+  static RowsShape rows_shape(const GridDesc& g, int nf, int kind, int count);
+  // residual partials (doubles) per system that fit in one vector: at least per_sys of any
+  // geometry, since every block of one has an output point of its own
+  static size_t rows_partial_room(const GridDesc& g) { return (size_t)g.nx * g.ny * g.nz * (sizeof(T2) / sizeof(double)); }
   // whether factor_rows runs on this grid (32-bit offsets within a z-chunk)
   static bool rows_fits(const GridDesc& g);
   // whether the fixed-point factors run through factor_rows with the current launch shape

@@ -89,12 +89,13 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
     const bool fuse = rows || (tn.fuse != 0 && Launch<T2>::pair_fits(op.g));
     const bool triples = fuse && !rows && Launch<T2>::triple_runs(op.g);
     // residual partials come from the first launch of a step: a multi-factor launch when
-    // fusing.  Its geometry, and so the partials per system, depends on the systems still
-    // iterating; in a fixed arena it keeps to the partials of the tile kernels.
-    const int tile_blk = (tn.fuse != 0 && fuse && q >= 3) ? Launch<T2>::pair_blocks(op.g)
-                                                          : Launch<T2>::partial_blocks(op.g);
-    const int max_blk = (rows && q >= 3 && ctx.ws.arena_set()) ? tile_blk : 0;
-    int nblk = tile_blk, nblk_cap = tile_blk;
+    // fusing.  In registers its geometry, and so the partials per system, depends on the
+    // systems still iterating; they go to wB, which a step writes after its stopping test only
+    // and which holds them whatever the geometry (rows_partial_room), so that a fixed arena
+    // needs no room for them and its solves take the geometries, and the bits, of the others.
+    const bool rows_step = rows && q >= 3;
+    const size_t nblk_cap = Launch<T2>::rows_partial_room(op.g);
+    int nblk = (fuse && q >= 3) ? Launch<T2>::pair_blocks(op.g) : Launch<T2>::partial_blocks(op.g);
     struct Part {
       int k, width, kind;
     };
@@ -108,12 +109,9 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
       return v;
     };
     std::vector<Part> step_rows;
-    if (rows && q >= 3) {
-      step_rows = plan_rows(0, q, kFacResid, kFacAdd);
-      nblk_cap = Launch<T2>::rows_max_blocks(op.g, step_rows[0].width);
-      if (max_blk > 0) nblk_cap = std::min(nblk_cap, std::max(max_blk, 1));
-    }
-    double* partial = (double*)ctx.ws.get("fp_partial", (size_t)nsys * nblk_cap * sizeof(double));
+    if (rows_step) step_rows = plan_rows(0, q, kFacResid, kFacAdd);
+    double* partial = rows_step ? (double*)wB
+                                : (double*)ctx.ws.get("fp_partial", (size_t)nsys * nblk * sizeof(double));
     int* active = (int*)ctx.ws.get("fp_active", (size_t)nsys * sizeof(int));
     int* list = (int*)ctx.ws.get("fp_list", (size_t)nsys * sizeof(int));
     double* rnorm2 = (double*)ctx.ws.get("fp_rnorm2", (size_t)nsys * sizeof(double));
@@ -135,7 +133,7 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
       const int extra = kind & (kFacResid | kFacAdd) ? 1 : 0;
       for (const Geometry& x : geometries)
         if (x.width == width && x.extra == extra && x.count == a.count) return x.s;
-      geometries.push_back(Geometry{width, extra, a.count, Launch<T2>::rows_shape(op.g, width, kind, a.count, max_blk)});
+      geometries.push_back(Geometry{width, extra, a.count, Launch<T2>::rows_shape(op.g, width, kind, a.count)});
       return geometries.back().s;
     };
 
@@ -194,11 +192,11 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
       bool ok;
       if (rows && width >= 2) {
         const RowsShape& sh = rows_shape(width, kind);
-        ok = Launch<T2>::factor_rows(s, op.g, kap, a, kind, width, sh);
         if (resid) {
+          HFCI_REQUIRE((size_t)sh.per_sys <= nblk_cap, "internal: more residual partials than allocated");
           nblk = sh.per_sys;
-          HFCI_REQUIRE(nblk <= nblk_cap, "internal: more residual partials than allocated");
         }
+        ok = Launch<T2>::factor_rows(s, op.g, kap, a, kind, width, sh);
       } else
         ok = width == 3   ? kind == 0 && Launch<T2>::factor_triple(s, op.g, kap, a)
                       : width == 2 ? Launch<T2>::factor_pair(s, op.g, kap, a, kind)

@@ -4,8 +4,7 @@
 namespace hfci {
 template bool Launch<float2>::factor_rows(hipStream_t, const GridDesc&, const void*, const FactorArgs<float2>&, int, int,
                                           const RowsShape&);
-template RowsShape Launch<float2>::rows_shape(const GridDesc&, int, int, int, int);
-template int Launch<float2>::rows_max_blocks(const GridDesc&, int);
+template RowsShape Launch<float2>::rows_shape(const GridDesc&, int, int, int);
 template bool Launch<float2>::rows_fits(const GridDesc&);
 template bool Launch<float2>::rows_run(const GridDesc&);
 }  // namespace hfci

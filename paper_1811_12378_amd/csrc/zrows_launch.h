@@ -126,7 +126,7 @@ inline double launch_cycles(double comp, double hbm, double l2) {
 }
 
 template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
-void shape_try(const GridDesc& g, int count, int max_blocks, RowsShape& best, double& best_t, RowsShape& any) {
+void shape_try(const GridDesc& g, int count, RowsShape& best, double& best_t, RowsShape& any) {
   using C = Cfg<T, NF, EXTRA, SM>;
   const KernelTune& t = sizeof(T) == 4 ? g.tune32 : g.tune64;
   const int climit = chunk_limit<T>(g), cap = rows_cap<T, NF, EXTRA>(g);
@@ -145,7 +145,7 @@ void shape_try(const GridDesc& g, int count, int max_blocks, RowsShape& best, do
       double hbm, l2;
       launch_bytes<T, NF, EXTRA, RESID, SM>(g, s, count, hbm, l2);
       const double tm = launch_cycles(comp, hbm, l2);
-      if (s.per_sys <= cap && (max_blocks <= 0 || s.per_sys <= max_blocks) && tm < best_t) {
+      if (s.per_sys <= cap && tm < best_t) {
         best_t = tm;
         best = s;
       }
@@ -164,11 +164,11 @@ void shape_try(const GridDesc& g, int count, int max_blocks, RowsShape& best, do
 // precisions, every kind): the geometry chosen costs 4 % more than the best measured one on
 // average (33 % at worst), where one fixed geometry per grid costs 30 % and more at either end.
 template <typename T, int NF, bool EXTRA, bool RESID>
-RowsShape shape_for(const GridDesc& g, int count, int max_blocks) {
+RowsShape shape_for(const GridDesc& g, int count) {
   RowsShape best{}, any{};
   double best_t = 1e300;
-  shape_try<T, NF, EXTRA, RESID, false>(g, count, max_blocks, best, best_t, any);
-  shape_try<T, NF, EXTRA, RESID, true>(g, count, max_blocks, best, best_t, any);
+  shape_try<T, NF, EXTRA, RESID, false>(g, count, best, best_t, any);
+  shape_try<T, NF, EXTRA, RESID, true>(g, count, best, best_t, any);
   return best.w == 0 ? any : best;
 }
 
@@ -213,29 +213,19 @@ bool Launch<T2>::factor_rows(hipStream_t st, const GridDesc& g, const void* kapp
 }
 
 template <typename T2>
-RowsShape Launch<T2>::rows_shape(const GridDesc& g, int nf, int kind, int count, int max_blocks) {
+RowsShape Launch<T2>::rows_shape(const GridDesc& g, int nf, int kind, int count) {
   using T = typename zrows::Elem<T2>::t;
   auto of = [&](auto nfc) {
     constexpr int NF = decltype(nfc)::value;
-    return (kind & kFacResid) ? zrows::shape_for<T, NF, true, true>(g, count, max_blocks)
-           : (kind & kFacAdd) ? zrows::shape_for<T, NF, true, false>(g, count, max_blocks)
-                              : zrows::shape_for<T, NF, false, false>(g, count, max_blocks);
+    return (kind & kFacResid) ? zrows::shape_for<T, NF, true, true>(g, count)
+           : (kind & kFacAdd) ? zrows::shape_for<T, NF, true, false>(g, count)
+                              : zrows::shape_for<T, NF, false, false>(g, count);
   };
   if (nf == 2) return of(std::integral_constant<int, 2>{});
   if (nf == 3) return of(std::integral_constant<int, 3>{});
   if constexpr (sizeof(T2) == 8)
     if (nf == 4) return of(std::integral_constant<int, 4>{});
   return RowsShape{};
-}
-
-template <typename T2>
-int Launch<T2>::rows_max_blocks(const GridDesc& g, int nf) {
-  using T = typename zrows::Elem<T2>::t;
-  if (nf == 2) return zrows::rows_cap<T, 2, true>(g);
-  if (nf == 3) return zrows::rows_cap<T, 3, true>(g);
-  if constexpr (sizeof(T2) == 8)
-    if (nf == 4) return zrows::rows_cap<T, 4, true>(g);
-  return 0;
 }
 
 template <typename T2>
