@@ -662,14 +662,13 @@ hfci_status hfci_contour_create(const hfci_op* op, int J, double t, double eps, 
       const cd zj = c->z[j];
       if (!(c->nu[j] < 1.0)) throw Error(HFCI_E_CONTOUR, "no contraction for a pole (nu >= 1)");
       FactorCoef* cj = &c->coef[(size_t)j * c->cstride];
-      factor_coefficients(zj, c->z0[j], c->delta[j], q, cj, cj + q, c->pz[j]);
+      // the eigenvalue nearest the pole: the real axis, or the band's lower edge, below or above it
+      complete_coefficients(factor_coefficients(zj, c->z0[j], c->delta[j], q, c->pz[j]), q, c->z0[j], op->s_h2,
+                            cd(std::min(std::max(zj.real(), op->b1), op->b2), zj.imag() > 0.0 ? 0.0 : -op->rho2), cj);
       for (int k = 0; k < c->cstride; ++k)
         if (!std::isfinite(cj[k].a_re) || !std::isfinite(cj[k].a_im) || !std::isfinite(cj[k].b_re) ||
             !std::isfinite(cj[k].b_im))
           throw Error(HFCI_E_NUMERIC, "non-finite factor coefficient");
-      // the eigenvalue nearest the pole: the real axis, or the band's lower edge, below or above it
-      complete_coefficients(cj, q, c->z0[j], op->s_h2,
-                            cd(std::min(std::max(zj.real(), op->b1), op->b2), zj.imag() > 0.0 ? 0.0 : -op->rho2));
       const cd zz = zj - c->z0[j];
       c->pdev[j] = PoleDev{c->z0[j].real(), c->z0[j].imag(), zz.real(), zz.imag()};
     }

@@ -37,9 +37,14 @@ struct Error : public std::runtime_error {
     if (!(cond)) throw Error(HFCI_E_ARG, msg);                    \
   } while (0)
 
-// c, g and al of a pole's factor coefficients from their a and b: the q factors of a step, then
-// those of step one.  lambda: where on the spectrum the pole's iteration is slowest.
-void complete_coefficients(FactorCoef* k, int q, cd z0, double s_h2, cd lambda);
+// A factor a (A - z0) w + b w before its rounding to double.
+using cld = std::complex<long double>;
+struct Factor {
+  cld a, b;
+};
+// A pole's factors as the kernels take them, from those of factor_coefficients: the q factors of
+// a step, then those of step one.  lambda: where on the spectrum the pole's iteration is slowest.
+void complete_coefficients(const std::vector<Factor>& k, int q, cd z0, double s_h2, cd lambda, FactorCoef* out);
 
 // Device workspace owned by a context: named buffers that only grow.
 class Workspace {
@@ -282,7 +287,7 @@ constexpr int kAutoQMax = 16;
 // per_pass: factors applied per pass over HBM (2 for the pair kernels, 1 otherwise)
 int choose_q(cd z, double b1, double b2, double rho2, int qmax, int per_pass);
 std::vector<cd> poly_roots(std::vector<cd> coeffs);
-void factor_coefficients(cd z, cd z0, double delta, int q, FactorCoef* out_L, FactorCoef* out_P, cd& pz);
+std::vector<Factor> factor_coefficients(cd z, cd z0, double delta, int q, cd& pz);
 
 // ---- solver.cpp ----
 template <typename T2>

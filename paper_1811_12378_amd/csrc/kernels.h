@@ -59,12 +59,13 @@ bool streams_fit(const GridDesc& g);
 //   w_out = a * (A - z0) w_in + b * w_in   (+ y1 on the last factor of a step).
 struct FactorCoef {
   double a_re, a_im, b_re, b_im;
-  // for the multi-factor passes in registers: g = a s_h2 and c = 6 - z0 / s_h2 + b / g, so that
-  // a (A - z0) w + b w = g ((c - kappa / s_h2 - i D / s_h2) w - sum of the six neighbours)
-  double c_re, c_im, g_re, g_im;
-  // at the first factor of a multi-factor pass in complex64: the scalar of the pass's output,
-  // the product of its g corrected for the rounding of its c (complete_coefficients)
-  double al_re, al_im;
+  // for the multi-factor passes in registers: c = 6 - z0 / s_h2 + b / (a s_h2), so that
+  // a (A - z0) w + b w = a s_h2 ((c - kappa / s_h2 - i D / s_h2) w - sum of the six neighbours)
+  double c_re, c_im;
+  // at the first factor of such a pass in complex64 and in complex128 (their passes differ): the
+  // scalar of the pass's output, the product of its a s_h2 corrected for the rounding of its c
+  // (complete_coefficients)
+  double al32_re, al32_im, al64_re, al64_im;
 };
 
 // Per-pole constants used inside the stage kernels.

@@ -381,43 +381,58 @@ std::vector<cd> leja_order(std::vector<cd> r) {
 // and one full step is q such factors plus the added y1.  y1 uses the q-1 roots mu_k
 // of P2 (leading coefficient e_{q-1} = 1/q!) in the same way; for q = 1, y1 = g / p~(z)
 // is a single factor with a = 0.
-// out_L: q factors, out_P: max(q-1, 1) factors, both in application order.
-void factor_coefficients(cd z, cd z0, double delta, int q, FactorCoef* out_L, FactorCoef* out_P, cd& pz) {
-  const cd beta = cd(0.0, -delta) * (z - z0);
-  const cd mid(0.0, -delta);  // B = mid * (A - z0)
+// Returned: the q factors of L, then the max(q-1, 1) of P2, each in application order.
+// The coefficients are the same at every one of some hundred steps, so their errors add up where
+// those of the passes' arithmetic do not, hence long double: complex128 solves of 64 x 60 x 70
+// points with eps 0.02 and 12 factors were 7e-14 from the 64-bit recursion with roots, scalars
+// and c in double, 5.7e-15 now (96^3, eps 0.25, 8 factors: 4.6e-15 and 3.3e-15).
+std::vector<Factor> factor_coefficients(cd z, cd z0, double delta, int q, cd& pz) {
   pz = ptilde(z, z0, delta, q);
   std::vector<double> fact(q + 1, 1.0);
-  for (int j = 1; j <= q; ++j) fact[j] = fact[j - 1] * j;
-  // p~(x) = sum_m x^m / m!
-  std::vector<cd> cp(q + 1);
-  for (int m = 0; m <= q; ++m) cp[m] = 1.0 / fact[m];
-  const std::vector<cd> rho = leja_order(poly_roots(cp));
-  const cd sL = std::pow(1.0 / (fact[q] * pz), 1.0 / q);
-  for (int k = 0; k < q; ++k) {
-    const cd a = sL * mid, b = -sL * rho[k];
-    out_L[k] = FactorCoef{a.real(), a.imag(), b.real(), b.imag(), 0, 0, 0, 0, 0, 0};
-  }
-  const cd g_scale = cd(0.0, delta) / pz;  // y1 = P2(B) (i delta f) / p~(z)
-  if (q == 1) {
-    // P2 = e_0 = 1
-    out_P[0] = FactorCoef{0.0, 0.0, g_scale.real(), g_scale.imag(), 0, 0, 0, 0, 0, 0};
-    return;
-  }
-  std::vector<cd> ce(q);
+  for (int j = 1; j <= q; ++j) fact[j] = fact[j - 1] * j;  // exact: q <= 16
+  const cld mid(0.0L, -(long double)delta);  // B = mid * (A - z0)
+  const cld beta = mid * (cld(z) - cld(z0));
+  // p~(x) = sum_m x^m / m!, P2(x) = sum_m e_m x^m, p~(beta)
+  std::vector<cld> cp(q + 1), ce(q);
+  for (int m = 0; m <= q; ++m) cp[m] = 1.0L / (long double)fact[m];
   for (int m = 0; m < q; ++m) {
-    cd e(0.0, 0.0), bp(1.0, 0.0);
+    cld bp(1.0L);
     for (int j = m + 1; j <= q; ++j) {
-      e += bp / fact[j];
+      ce[m] += bp * cp[j];
       bp *= beta;
     }
-    ce[m] = e;
   }
-  const std::vector<cd> mu = leja_order(poly_roots(ce));
-  const cd s2 = std::pow(g_scale * ce[q - 1], 1.0 / (q - 1));
-  for (int k = 0; k < q - 1; ++k) {
-    const cd a = s2 * mid, b = -s2 * mu[k];
-    out_P[k] = FactorCoef{a.real(), a.imag(), b.real(), b.imag(), 0, 0, 0, 0, 0, 0};
+  const cld p = 1.0L + beta * ce[0];
+  // the roots in double fix the order, Newton corrections in long double the values
+  auto roots = [](const std::vector<cld>& c) {
+    std::vector<cd> cr;
+    for (const cld& v : c) cr.push_back(cd((double)v.real(), (double)v.imag()));
+    std::vector<cld> r;
+    for (const cd& x0 : leja_order(poly_roots(cr))) {
+      cld x(x0);
+      for (int k = 0; k < 3; ++k) {
+        cld v = c.back(), dv(0.0L);
+        for (int m = (int)c.size() - 2; m >= 0; --m) {
+          dv = dv * x + v;
+          v = v * x + c[m];
+        }
+        if (dv != cld(0.0L)) x -= v / dv;
+      }
+      r.push_back(x);
+    }
+    return r;
+  };
+  std::vector<Factor> out;
+  const cld sL = std::pow(1.0L / ((long double)fact[q] * p), 1.0L / q);
+  for (const cld& r : roots(cp)) out.push_back(Factor{sL * mid, -sL * r});
+  const cld scale = cld(0.0L, (long double)delta) / p;  // y1 = P2(B) (i delta f) / p~(z)
+  if (q == 1) {  // P2 = e_0 = 1
+    out.push_back(Factor{cld(0.0L), scale});
+    return out;
   }
+  const cld s2 = std::pow(scale * ce[q - 1], 1.0L / (q - 1));
+  for (const cld& r : roots(ce)) out.push_back(Factor{s2 * mid, -s2 * r});
+  return out;
 }
 
 std::vector<int> rows_plan(int count, int most, bool step) {
@@ -435,46 +450,56 @@ std::vector<int> rows_plan(int count, int most, bool step) {
 }
 
 // A pass of the register kernels evaluates al prod_f (c_f - kappa / s_h2 - i D / s_h2 - nb) with
-// c_f and al rounded to the vectors' precision.  In complex64 the rounding of the c_f shifts
-// every eigenvalue's multiplier by the same few 1e-7 at every step, which a pole near the real
-// axis repeats over some hundred steps: al takes it back at the eigenvalue where the iteration
-// is slowest (the shift hardly varies along the slow part of the spectrum), and each pass's al
-// also takes back the rounding of the ones before it.
-void complete_coefficients(FactorCoef* k, int q, cd z0, double s_h2, cd lambda) {
-  const int n = q + std::max(q - 1, 1);
-  const double inv = 1.0 / s_h2;
-  for (int i = 0; i < n; ++i) {
-    const cd g = cd(k[i].a_re, k[i].a_im) * s_h2;
+// c_f and al rounded to the vectors' precision.  The rounding of the c_f shifts every
+// eigenvalue's multiplier by the same amount at every step (complex64: a few 1e-7), which a pole
+// near the real axis repeats over some hundred steps: al takes it back at the eigenvalue where
+// the iteration is slowest (the shift hardly varies along the slow part of the spectrum), and
+// each pass's al also takes back the rounding of the ones before it.
+void complete_coefficients(const std::vector<Factor>& k, int q, cd z0, double s_h2, cd lambda, FactorCoef* out) {
+  const long double sh = s_h2;
+  const cld lam(lambda), z(z0), at = lam / sh - 6.0L;
+  std::vector<cld> c(k.size());
+  for (size_t i = 0; i < k.size(); ++i) {
     // (a lone constant factor, a = 0 for q = 1, is never in a multi-factor pass)
-    const cd c = g == cd(0.0, 0.0) ? cd(0.0, 0.0) : 6.0 - z0 * inv + cd(k[i].b_re, k[i].b_im) / g;
-    k[i].c_re = c.real();
-    k[i].c_im = c.imag();
-    k[i].g_re = g.real();
-    k[i].g_im = g.imag();
-    k[i].al_re = k[i].al_im = 0.0;
+    c[i] = k[i].a == cld(0.0L) ? cld(0.0L) : 6.0L - z / sh + k[i].b / (k[i].a * sh);
+    out[i] = FactorCoef{(double)k[i].a.real(), (double)k[i].a.imag(), (double)k[i].b.real(), (double)k[i].b.imag(),
+                        (double)c[i].real(), (double)c[i].imag(), 0, 0, 0, 0};
   }
+  // the residual's diagonal as the kernels form it
+  const double inv = 1.0 / s_h2;
+  const cd zc(std::fma(-z0.real(), inv, 6.0), -z0.imag() * inv);
+  auto scalars = [&](int k0, int count, bool step, int most, auto round, auto put) {
+    cld want(1.0L), have(1.0L);
+    int f = k0;
+    for (int w : rows_plan(count, most, step)) {
+      const int first = f;
+      for (; f < first + w; ++f) {
+        const cd cf(out[f].c_re, out[f].c_im);
+        // the residual's pass adds the first factor's share to the residual's own diagonal
+        const cld rounded = step && f == 0 ? cld(round(zc)) + cld(round(cf - zc)) : cld(round(cf));
+        want *= k[f].a * sh;
+        if (std::abs(rounded + at) > 1e-2L) want *= (c[f] + at) / (rounded + at);
+      }
+      const cld al = want / have;
+      const cd al64((double)al.real(), (double)al.imag());
+      put(out[first], al64);
+      have *= cld(round(al64));
+    }
+  };
   auto single = [](cd v) { return cd((float)v.real(), (float)v.imag()); };
+  auto whole = [](cd v) { return v; };
   for (int part = 0; part < 2; ++part) {
     const bool step = part == 0;
     const int count = step ? q : q - 1, k0 = step ? 0 : q;
     if (count < 2) continue;
-    cd want(1.0, 0.0), have(1.0, 0.0);
-    int f = k0;
-    for (int w : rows_plan(count, kRowsMax32, step)) {
-      const int first = f;
-      for (; f < first + w; ++f) {
-        const cd c(k[f].c_re, k[f].c_im), zc(6.0 - z0.real() * inv, -z0.imag() * inv);
-        // the residual's pass adds the first factor's share to the residual's own diagonal
-        const cd rounded = step && f == 0 ? single(zc) + single(c - zc) : single(c);
-        const cd at = lambda * inv - 6.0;
-        want *= cd(k[f].g_re, k[f].g_im);
-        if (std::abs(rounded + at) > 1e-2) want *= (c + at) / (rounded + at);
-      }
-      const cd al = want / have;
-      k[first].al_re = al.real();
-      k[first].al_im = al.imag();
-      have *= single(al);
-    }
+    scalars(k0, count, step, kRowsMax32, single, [](FactorCoef& o, cd al) {
+      o.al32_re = al.real();
+      o.al32_im = al.imag();
+    });
+    scalars(k0, count, step, kRowsMax64, whole, [](FactorCoef& o, cd al) {
+      o.al64_re = al.real();
+      o.al64_im = al.imag();
+    });
   }
 }
 

@@ -463,8 +463,8 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   int* list = (int*)ctx.ws.get("tune_list", (size_t)nsys * sizeof(int));
   const PoleDev p0{0.5 * (op.b1 + op.b2), 0.5, 0.0, 0.0};
   FactorCoef c0[4 + 3];
-  for (FactorCoef& c : c0) c = FactorCoef{1e-3, 0.0, 0.5, 0.0, 0, 0, 0, 0, 0, 0};
-  complete_coefficients(c0, 4, cd(p0.z0_re, p0.z0_im), op.s_h2, cd(0.0, 0.0));
+  complete_coefficients(std::vector<Factor>(4 + 3, Factor{cld(1e-3L), cld(0.5L)}), 4, cd(p0.z0_re, p0.z0_im), op.s_h2,
+                        cd(0.0, 0.0), c0);
   std::vector<int> ids(nsys);
   for (int k = 0; k < nsys; ++k) ids[k] = k;
   HFCI_HIP(hipMemcpyAsync(coef, c0, sizeof(c0), hipMemcpyHostToDevice, s));

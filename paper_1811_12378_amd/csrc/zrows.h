@@ -30,8 +30,8 @@
 //
 // Arithmetic: a (A - z0) x + b x = a sh2 (m x - nb), nb the sum of the six neighbours and
 // m = 6 - z0 / sh2 + b / (a sh2) - kappa / sh2 - i D / sh2; the scalars a sh2 of a pass are
-// multiplied together and applied once to its output (in complex64 corrected for the rounding
-// of the constants, see complete_coefficients).  17 vector instructions per point and
+// multiplied together, corrected for the rounding of the constants (complete_coefficients), and
+// applied once to its output.  17 vector instructions per point and
 // factor in complex64 (10 adds for nb, 3 for m, 4 multiply-adds), 4 more per point and pass.
 #pragma once
 
@@ -142,28 +142,21 @@ __device__ __forceinline__ void rows_tile(const GridDesc& g, const RowsShape& q,
 
   // constants of the pass, in FP64 (uniform)
   T cr[NF], ci[NF];
-  double alr = 1.0, ali = 0.0;
   const PoleDev pd = a.poles[pole];
   const FactorCoef* __restrict__ cf = a.coef + pole * a.cstride + a.k;
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
-    const FactorCoef c = cf[f];
-    cr[f] = uniform<T>((T)c.c_re);
-    ci[f] = uniform<T>((T)c.c_im);
-    const double t = alr * c.g_re - ali * c.g_im;
-    ali = alr * c.g_im + ali * c.g_re;
-    alr = t;
+    cr[f] = uniform<T>((T)cf[f].c_re);
+    ci[f] = uniform<T>((T)cf[f].c_im);
   }
-  if constexpr (sizeof(T) == 4) {
-    alr = cf[0].al_re;
-    ali = cf[0].al_im;
-  }
+  const double alr = sizeof(T) == 4 ? cf[0].al32_re : cf[0].al64_re;
+  const double ali = sizeof(T) == 4 ? cf[0].al32_im : cf[0].al64_im;
   const T al_r = uniform<T>((T)alr), al_i = uniform<T>((T)ali);
   // what the last pass of a step in complex64 adds for the rounding of its scalar
   const T lo_r = uniform<T>((T)(alr - (double)al_r)), lo_i = uniform<T>((T)(ali - (double)al_i));
   const T kinv = (T)-q.inv_sh2, dsc = (T)q.damp_sh2;
   // the residual's diagonal 6 - z0 / sh2, and what the first factor adds to it
-  const double zcr = 6.0 - pd.z0_re * q.inv_sh2, zci = -pd.z0_im * q.inv_sh2;
+  const double zcr = __builtin_fma(-pd.z0_re, q.inv_sh2, 6.0), zci = -pd.z0_im * q.inv_sh2;
   const T zr = uniform<T>((T)zcr), zi = uniform<T>((T)zci);
   const T br = uniform<T>((T)(cf[0].c_re - zcr)), bi = uniform<T>((T)(cf[0].c_im - zci));
 

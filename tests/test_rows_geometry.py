@@ -51,3 +51,89 @@ int main() {
 def test_residual_partials_have_room(tmp_path):
     out = run_native(ROOM, tmp_path)
     assert "bad 0 of 19110" in out, out[-2000:]
+
+
+# One step's multiplier at the eigenvalue the scalars are corrected at (the nearest to the pole),
+# from the stored coefficients as the passes take them, against p~(B) / p~(z) in long double.
+# The rounding of the c is taken back exactly there and the scalars carry each other's, so what is
+# left is the rounding of the last pass's scalar: 2^-53 in complex128; in complex64, whose last
+# pass of a step also adds that rounding (in single precision), 2^-24 of it twice.  Then the same
+# for the polynomial of step one, whose last pass adds nothing in complex64.
+MULTIPLIER = r"""
+#include <cstdio>
+#include "internal.h"
+using namespace hfci;
+using L = long double;
+int main() {
+  static_assert(sizeof(L) > sizeof(double), "the exact side needs more than double");
+  for (double s_h2 : {0.4, 1.6, 5.0})
+    for (double eps : {0.02, 0.1, 0.5})
+      for (int q : {2, 3, 5, 7, 8, 10, 12, 16}) {
+        const double b1 = -1.0, b2 = 12.0 * s_h2 - 0.05;
+        std::vector<cd> z, sigma;
+        contour_poles(6, 1.0, eps, 1.0, z, sigma);
+        for (int j = 0; j < 6; ++j) {
+          double delta, nu;
+          cd z0, pz;
+          optimise_delta(z[j], b1, b2, 1.0, q, delta, nu, z0, 200, 80);
+          if (!(nu < 1.0)) continue;
+          const cd lam(std::min(std::max(z[j].real(), b1), b2), z[j].imag() > 0.0 ? 0.0 : -1.0);
+          std::vector<FactorCoef> k(q + std::max(q - 1, 1));
+          complete_coefficients(factor_coefficients(z[j], z0, delta, q, pz), q, z0, s_h2, lam, k.data());
+          const cld mid(0.0L, -(L)delta), B = mid * (cld(lam) - cld(z0)), beta = mid * (cld(z[j]) - cld(z0));
+          const cld at = cld(lam) / (L)s_h2 - 6.0L;
+          std::vector<L> fact(q + 1, 1.0L);
+          for (int m = 1; m <= q; ++m) fact[m] = fact[m - 1] * m;
+          cld pb(0.0L), p(0.0L), p2(0.0L);
+          for (int m = q; m >= 0; --m) {
+            pb = pb * B + 1.0L / fact[m];
+            p = p * beta + 1.0L / fact[m];
+          }
+          for (int m = q - 1; m >= 0; --m) {
+            cld e(0.0L);
+            for (int i = q; i > m; --i) e = e * beta + 1.0L / fact[i];
+            p2 = p2 * B + e;
+          }
+          const cld want[2] = {pb / p, p2 * cld(0.0L, (L)delta) / p};
+          for (int prec : {32, 64})
+            for (int part = 0; part < 2; ++part) {
+              const bool step = part == 0;
+              const int count = step ? q : q - 1;
+              if (count < 2) continue;
+              int f = step ? 0 : q;
+              cld have(1.0L);
+              L nearest = 1e9L;
+              const std::vector<int> w = rows_plan(count, prec == 32 ? kRowsMax32 : kRowsMax64, step);
+              for (size_t i = 0; i < w.size(); ++i) {
+                const FactorCoef& h = k[f];
+                auto r = [&](double v) { return prec == 32 ? (double)(float)v : v; };
+                cld al = prec == 32 ? cld(h.al32_re, h.al32_im) : cld(h.al64_re, h.al64_im);
+                if (!(step && i + 1 == w.size())) al = cld(r((double)al.real()), r((double)al.imag()));
+                have *= al;
+                for (int u = 0; u < w[i]; ++u, ++f) {
+                  cld c(r(k[f].c_re), r(k[f].c_im));
+                  if (step && f == 0) {
+                    const double inv = 1.0 / s_h2, zr = std::fma(-z0.real(), inv, 6.0), zi = -z0.imag() * inv;
+                    c = cld(r(zr), r(zi)) + cld(r(k[0].c_re - zr), r(k[0].c_im - zi));
+                  }
+                  have *= c + at;
+                  nearest = std::min(nearest, std::abs(c + at));
+                }
+              }
+              if (nearest < 1e-2L) continue;  // (next to a root the rounding is not taken back)
+              printf("%d %d %.3Le s_h2 %g eps %g q %d pole %d\n", prec, part, std::abs(have / want[part] - 1.0L), s_h2, eps, q,
+                     j);
+            }
+        }
+      }
+}
+"""
+
+
+def test_step_multipliers_carry_no_rounding_of_the_constants(tmp_path):
+    bars = {("32", "0"): 2.0 ** -47, ("64", "0"): 1.01 * 2.0 ** -53, ("32", "1"): 1.01 * 2.0 ** -24,
+            ("64", "1"): 1.01 * 2.0 ** -53}
+    rows = [r.split(maxsplit=3) for r in run_native(MULTIPLIER, tmp_path).splitlines()]
+    assert len(rows) > 1000 and {(r[0], r[1]) for r in rows} == set(bars)
+    for prec, part, err, case in rows:
+        assert float(err) <= bars[prec, part], (prec, part, err, case)
