@@ -226,10 +226,12 @@ hfci_status hfci_op_info(const hfci_op* op, double* out7);
  *                 slabs, the systems of a launch are taken sg at a time, tile by tile,
  *                 so kappa of a tile is read once per sg systems (1 = one system's
  *                 tiles after another's).
- * Shapes change launch geometry only: every grid point gets the same arithmetic,
- * while reductions (residual norms, the step size d) sum their block partials in a
- * different order.  New operators start at {1, 8, 2, 0, 0, 1}, with the fixed-point factors
- * several per pass as for fuse 1 until a shape is set or tuned.  Errors: HFCI_E_ARG. */
+ * Among the shapes of one kind of pass (planes in registers; all others) every grid point
+ * gets the same arithmetic; the passes in registers evaluate the same factors in another
+ * form, so between the two kinds results differ by rounding.  Reductions (residual norms,
+ * the step size d) sum their block partials in an order that depends on the shape.  New
+ * operators start at {1, 8, 2, 0, 1, 1}; hfci_op_get_tune's shape set again changes nothing.
+ * Errors: HFCI_E_ARG. */
 hfci_status hfci_op_set_tune(hfci_op* op, int prec, const int* tune6);
 hfci_status hfci_op_get_tune(const hfci_op* op, int prec, int* tune6);
 

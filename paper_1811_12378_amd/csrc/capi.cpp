@@ -486,7 +486,6 @@ hfci_status hfci_op_set_tune(hfci_op* op, int prec, const int* t3) {
   t.cz = t3[3];
   t.fuse = t3[4];
   t.sg = t3[5];
-  t.chosen = true;
   HFCI_REQUIRE(tune_valid(t), "tune must be {0, ty in {4, 8}, pd in {1, 2}, cz, fuse, sg} or {1, 4, pd in 1..3, cz, "
                               "fuse, sg} or {1, 8, pd in {2, 3}, cz, fuse, sg} or {2, 8, pd in {2, 3}, cz, 1, sg} or "
                               "{3, 8, 2, cz, 1, sg}, cz in [0, 4096], fuse in {0, 1}, sg in [1, 16]");

@@ -16,14 +16,11 @@ namespace hfci {
 // fuse 1 applies the fixed-point factors several per pass (kern 0 and 1 in registers, kern 2
 // and 3 two per pass on tiles in LDS).
 struct KernelTune {
-  // fuse: 0 one factor per pass, 1 two (the later steps' first and last factors and the
-  // middle ones in pairs), 2 (kern 3 only) as 1 with the middle factors in threes where
-  // they split so; sg: with several factors per pass, the systems of a launch are taken sg
+  // fuse: 0 one factor per pass, 1 several (kern 0 and 1: up to four or three; kern 2 and 3: the
+  // later steps' first and last factors and the middle ones in pairs), 2 (kern 3 only) as 1
+  // with the middle factors in threes where they split so; sg: with several factors per pass, the systems of a launch are taken sg
   // at a time, tile by tile, inside each XCD's slab of tiles (1 = system after system)
-  int kern = 1, ty = 8, pd = 2, cz = 0, fuse = 0, sg = 1;
-  // false until a shape is set or tuned: the fixed-point factors then run several per pass
-  // (Launch::factor_rows) as with fuse 1
-  bool chosen = false;
+  int kern = 1, ty = 8, pd = 2, cz = 0, fuse = 1, sg = 1;
 };
 
 // Tile geometry of a multi-factor pass in registers (zrows.h): gx x gy x nzc blocks of w

@@ -486,7 +486,6 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   const KernelTune saved = cur;
   const void* kap = Prec<T2>::kappa(op);
   std::vector<KernelTune> cands;
-  // (every candidate is a shape set on purpose)
   for (int cz : {0, 16, 64}) {
     for (int ty : {4, 8})
       for (int pd : {1, 2}) cands.push_back(KernelTune{0, ty, pd, cz, 0});
@@ -520,7 +519,6 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
     for (const KernelTune& t : cands) {
       if (t.cz > 0 && t.cz >= op.g.nz) continue;  // same as one chunk per column: covered by cz = 0 or larger
       cur = t;
-      cur.chosen = true;
       const int rows = Launch<T2>::rows_run(op.g) ? (sizeof(T2) == 8 ? kRowsMax32 : kRowsMax64) : 0;
       if (t.fuse == 2 && !Launch<T2>::triple_runs(op.g)) continue;  // (an odd nx: the pairs' shape covers it)
       const RowsShape sh = rows ? Launch<T2>::rows_shape(op.g, rows, 0, nsys) : RowsShape{};

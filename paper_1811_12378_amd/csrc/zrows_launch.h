@@ -238,7 +238,7 @@ bool Launch<T2>::rows_run(const GridDesc& g) {
   const KernelTune& t = sizeof(T2) == 8 ? g.tune32 : g.tune64;
   // kerns 2 and 3 are the complex64 kernels that stream into LDS; where the grid does not
   // suit them (an odd nx, vectors of 2 GiB or more) their shapes run these passes too
-  return (!t.chosen || (t.fuse != 0 && (t.kern <= 1 || !streams_fit(g)))) && rows_fits(g);
+  return t.fuse != 0 && (t.kern <= 1 || !streams_fit(g)) && rows_fits(g);
 }
 
 }  // namespace hfci

@@ -303,7 +303,8 @@ class Operator(_Handle):
 
     def set_tune(self, prec: int, kern: int, ty: int, pd: int, cz: int = 0, fuse: int = 0, sg: int = 1):
         """hfci_op_set_tune: stencil launch shape (kernel, 64 x ty tile, prefetch depth pd, z-chunk cz,
-        two fixed-point factors per pass, systems taken sg at a time tile by tile)."""
+        several fixed-point factors per pass, systems taken sg at a time tile by tile); get_tune's
+        six values set again change nothing."""
         t = (ctypes.c_int * 6)(kern, ty, pd, cz, fuse, sg)
         _check(load_library().hfci_op_set_tune(self.h, prec, ctypes.cast(t, ctypes.c_void_p)))
 
