@@ -197,19 +197,25 @@ struct MultiFp {
     for (const Part& p : plan(q, std::max(q - 1, 1), kFacInF, kFacDual)) add(first, p);
     levels = nsys <= 4096 ? kLevels : 1;
     nlater = (int)later.size();
-    auto geometry = [&](const RowsClass& x, double part) {
-      std::vector<double> systems(J.begin(), J.end());
-      for (double& v : systems) v *= part;
-      std::vector<RowsShape> sh(count);
-      const RowsClass c = MultiLaunch<T2>::rows_class(grids, systems, x.width, x.kind, sh);
-      classes.push_back(c);
-      h_shapes.insert(h_shapes.end(), sh.begin(), sh.end());
-      return c.w > 0;
-    };
+    const std::vector<double> systems(J.begin(), J.end());
+    std::vector<double> parts;
+    for (int l = 0; l < levels; ++l) parts.push_back(std::pow(0.25, l));
+    const size_t nclass = (size_t)levels * nlater + first.size();
+    classes.resize(nclass);
+    h_shapes.resize(nclass * count);
     bool ok = true;
-    for (int l = 0; l < levels; ++l)
-      for (const RowsClass& x : later) ok = geometry(x, std::pow(0.25, l)) && ok;
-    for (const RowsClass& x : first) ok = geometry(x, 1.0) && ok;
+    // a class of the later steps sits at table l * nlater + its index for every level l
+    auto geometry = [&](const RowsClass& x, const std::vector<double>& at, size_t table, size_t stride) {
+      std::vector<RowsClass> c(at.size(), x);
+      std::vector<std::vector<RowsShape>> sh(at.size());
+      ok = ok && MultiLaunch<T2>::rows_class(grids, systems, at, c.data(), sh.data());
+      for (size_t l = 0; ok && l < at.size(); ++l, table += stride) {
+        classes[table] = c[l];
+        std::copy(sh[l].begin(), sh[l].end(), h_shapes.begin() + table * count);
+      }
+    };
+    for (int k = 0; k < nlater; ++k) geometry(later[k], parts, k, nlater);
+    for (size_t k = 0; k < first.size(); ++k) geometry(first[k], {1.0}, (size_t)levels * nlater + k, 1);
     if (!ok) {
       classes.clear();
       h_shapes.clear();

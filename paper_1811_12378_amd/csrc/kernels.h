@@ -274,10 +274,11 @@ struct MultiLaunch {
   static bool factor_rows(hipStream_t st, const RowsClass& c, const MultiInst* inst, const RowsShape* shapes,
                           const MultiSys<T2>* sys, const int2* seg, int nseg, int nblocks, int kind, int role_in,
                           int role_out, int role_out2, int k, int cstride);
-  // the block size, and the geometry per instance, of a pass over systems[i] systems (an
-  // expected number, not necessarily whole) of grid g[i]
-  static RowsClass rows_class(const std::vector<GridDesc>& g, const std::vector<double>& systems, int width, int kind,
-                              std::vector<RowsShape>& shapes);
+  // for each p < parts.size(): the block size (into c[p], whose width and kind are set alike) and
+  // the geometry per instance (shapes[p]) of a pass over parts[p] systems[i] systems, an expected
+  // number, of grid g[i]; false where there is none
+  static bool rows_class(const std::vector<GridDesc>& g, const std::vector<double>& systems,
+                         const std::vector<double>& parts, RowsClass* c, std::vector<RowsShape>* shapes);
   // geometry of one instance for this launch shape (host)
   static MultiInst describe(const GridDesc& g, const void* kappa);
 };

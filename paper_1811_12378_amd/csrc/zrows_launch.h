@@ -102,21 +102,28 @@ bool shape_of(const GridDesc& g, int w, int cz, RowsShape& s) {
   return true;
 }
 
-// CU cycles (2.4 GHz) of one block of w waves on a z-chunk, `conc` blocks on its CU at once
+// Planes a block steps through for a chunk, and CU cycles (2.4 GHz) of one of them for a block of
+// w waves with `conc` blocks on its CU at once; a block costs kBlockCycles beside.
+template <int NF>
+int block_iters(int czlen) { return (czlen + 2 * (NF - 1) + 3) / 4 * 4; }
 template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
-double block_cycles(int w, int czlen, double conc) {
+double iter_cycles(int w, double conc) {
   const double v = Cfg<T, NF, EXTRA, SM>::R * (NF * (sizeof(T) == 4 ? 83.0 : 137.0) + (RESID ? 72.0 : 0.0));
-  const double iters = (czlen + 2 * (NF - 1) + 3) / 4 * 4;
-  return iters * std::max(std::ceil(w * conc / 4) * v * 1.19, 820.0 + v * 1.02) + 6100.0;
+  return std::max(std::ceil(w * conc / 4) * v * 1.19, 820.0 + v * 1.02);
 }
+constexpr double kBlockCycles = 6100.0;
 
-// bytes of HBM, and requested of the L2s, by a launch over `count` systems
-template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
-void launch_bytes(const GridDesc& g, const RowsShape& s, double count, double& hbm, double& l2) {
-  const double e = 2 * sizeof(T), pts = (double)g.nx * g.ny * g.nz * count;
-  hbm = pts * (2.5 * e + (RESID ? e / std::max(count, 1.0) : EXTRA ? e : 0.0));
-  l2 = (double)s.gx * 64 * s.gy * s.w * Cfg<T, NF, EXTRA, SM>::R * s.nzc * (s.czlen + 2 * NF) * count * 1.5 * e +
-       pts * (EXTRA ? 2.0 : 1.0) * e;
+// Bytes of HBM of a launch over `count` systems of `pts` points each, and bytes requested of the
+// L2s by blocks of w waves that load `planes` planes in all, for `pts` points in all
+template <typename T, bool EXTRA, bool RESID>
+double hbm_bytes(double pts, double count) {
+  const double e = 2 * sizeof(T);
+  return pts * count * (2.5 * e + (RESID ? e / std::max(count, 1.0) : EXTRA ? e : 0.0));
+}
+template <typename T, int NF, bool EXTRA, bool SM>
+double l2_bytes(int w, double planes, double pts) {
+  const double e = 2 * sizeof(T);
+  return planes * 64 * w * Cfg<T, NF, EXTRA, SM>::R * 1.5 * e + pts * (EXTRA ? 2.0 : 1.0) * e;
 }
 
 // memory time (cycles) overlaps with all but a quarter of the shorter of the two
@@ -140,11 +147,13 @@ void shape_try(const GridDesc& g, int count, RowsShape& best, double& best_t, Ro
       const double blocks = (double)s.per_sys * count;
       const double conc = std::max(1.0, std::min((double)bpc, std::ceil(blocks / 256.0)));
       const double full = std::floor(blocks / (256.0 * conc)), rest = blocks - full * 256.0 * conc;
-      const double comp = full * block_cycles<T, NF, EXTRA, RESID, SM>(w, s.czlen, conc) +
-                          (rest > 0 ? block_cycles<T, NF, EXTRA, RESID, SM>(w, s.czlen, std::ceil(rest / 256.0)) : 0.0);
-      double hbm, l2;
-      launch_bytes<T, NF, EXTRA, RESID, SM>(g, s, count, hbm, l2);
-      const double tm = launch_cycles(comp, hbm, l2);
+      auto block = [&](double n) {
+        return block_iters<NF>(s.czlen) * iter_cycles<T, NF, EXTRA, RESID, SM>(w, n) + kBlockCycles;
+      };
+      const double comp = full * block(conc) + (rest > 0 ? block(std::ceil(rest / 256.0)) : 0.0);
+      const double pts = (double)g.nx * g.ny * g.nz;
+      const double tm = launch_cycles(comp, hbm_bytes<T, EXTRA, RESID>(pts, count),
+                                      l2_bytes<T, NF, EXTRA, SM>(w, blocks * (s.czlen + 2 * NF), pts * count));
       if (s.per_sys <= cap && tm < best_t) {
         best_t = tm;
         best = s;

@@ -50,63 +50,93 @@ __global__ __launch_bounds__((64 * KindCfg<T, KIND, NF, SM>::WMAX))
   rows_tile<T, KIND, NF, KindCfg<T, KIND, NF, SM>::R>(inst[in].g, q, 0, b, a, (const T*)inst[in].kappa, lds);
 }
 
-// Block size and per-instance geometry of a pass over `systems[i]` systems of each instance:
-// every block size, with z-chunks of one length for all, by the cost model of shape_for with
-// the blocks of all instances in one pool (whole rounds of the chip, and half of the longest
-// block for the ragged end).
+// Block size and chunk length of a pass over parts[p] systems[i] systems of each instance, for
+// every p at once: every block size, with z-chunks of one length for all, by the cost model of
+// shape_for with the blocks of all instances in one pool (whole rounds of the chip, and half of
+// the longest block for the ragged end).  What a candidate costs is linear in the systems up to
+// the rounds, so an instance is visited once per candidate whatever the parts, with a few
+// additions each: the search runs on the host while the GPU waits (512 instances, three kinds of
+// pass, four parts: 1.1 ms; rebuilding every geometry for every part took 20 ms).
+struct ClassBest {
+  double tm = 1e300;
+  int w = 0, small = 0, cz = 0;
+};
 template <typename T, int NF, bool EXTRA, bool RESID, bool SM>
-void class_try(const std::vector<GridDesc>& g, const std::vector<double>& systems, RowsClass& best, double& best_t,
-               std::vector<RowsShape>& shapes) {
+void class_try(const std::vector<GridDesc>& g, const std::vector<double>& systems, const std::vector<double>& parts,
+               std::vector<ClassBest>& best) {
   using C = Cfg<T, NF, EXTRA, SM>;
-  std::vector<RowsShape> s(g.size());
+  const size_t n = g.size();
+  constexpr int kIters[] = {8, 12, 16, 24, 32, 48, 64, 96, 128}, kN = 9;
+  std::vector<int> gx(n), gy(n), cap(n), nzc(n * kN), len(n * kN);
+  std::vector<double> hbm(parts.size(), 0.0);
+  double pts = 0.0;
+  int step;
+  for (size_t i = 0; i < n; ++i) {
+    gx[i] = tiles<NF>(g[i].nx, 64, step);
+    const int limit = std::min(g[i].nz, chunk_limit<T>(g[i]));
+    for (int m = 0; m < kN; ++m) {
+      len[m * n + i] = std::min(kIters[m] - 2 * (NF - 1), limit);
+      nzc[m * n + i] = (g[i].nz + len[m * n + i] - 1) / len[m * n + i];
+    }
+    // enough blocks to fill the chip eight times over with one system, or what the longest
+    // chunks and largest blocks give
+    cap[i] = std::max(2048, gx[i] * tiles<NF>(g[i].ny, C::WMAX * C::R, step) * nzc[(kN - 1) * n + i]);
+    const double p = (double)g[i].nx * g[i].ny * g[i].nz;
+    pts += p * systems[i];
+    for (size_t k = 0; k < parts.size(); ++k) hbm[k] += hbm_bytes<T, EXTRA, RESID>(p, systems[i] * parts[k]);
+  }
   for (int w = C::WMAX; w >= 2; --w) {
-    const int bpc = std::max(1, C::WMAX / w);
-    for (const int iters : {8, 12, 16, 24, 32, 48, 64, 96, 128}) {
-      const int cz = iters - 2 * (NF - 1);
-      double blocks = 0.0, hbm = 0.0, l2 = 0.0;
-      bool ok = true;
-      for (size_t i = 0; i < g.size() && ok; ++i) {
-        ok = shape_of<T, NF, EXTRA, SM>(g[i], w, cz, s[i]) && s[i].per_sys <= rows_cap<T, NF, EXTRA>(g[i]);
-        double h, l;
-        launch_bytes<T, NF, EXTRA, RESID, SM>(g[i], s[i], systems[i], h, l);
-        blocks += systems[i] * s[i].per_sys;
-        hbm += h;
-        l2 += l;
+    const int rb = w * C::R, bpc = std::max(1, C::WMAX / w);
+    if (lds_bytes(NF, w, 2 * sizeof(T)) > 160 * 1024) continue;
+    bool ok = true;
+    for (size_t i = 0; i < n; ++i) {
+      ok = ok && (g[i].ny <= rb || rb > 2 * NF);
+      gy[i] = ok ? tiles<NF>(g[i].ny, rb, step) : 0;
+    }
+    if (!ok) continue;
+    for (int m = 0; m < kN; ++m) {
+      // per unit of parts: blocks, planes they load, planes they step through; the longest block
+      double blocks = 0.0, planes = 0.0, iters = 0.0;
+      int most = 0, over = 0;
+      for (size_t i = 0; i < n; ++i) {
+        const int per = gx[i] * gy[i] * nzc[m * n + i], l = len[m * n + i], it = block_iters<NF>(l);
+        const double v = systems[i] * per;
+        over |= per > cap[i];
+        blocks += v;
+        planes += v * (l + 2 * NF);
+        iters += v * it;
+        most = std::max(most, it);
       }
-      if (!ok) continue;
-      const double conc = std::max(1.0, std::min((double)bpc, std::ceil(blocks / 256.0)));
-      double sum = 0.0, longest = 0.0;
-      for (size_t i = 0; i < g.size(); ++i) {
-        const double t = block_cycles<T, NF, EXTRA, RESID, SM>(w, s[i].czlen, conc);
-        sum += t * systems[i] * s[i].per_sys;
-        longest = std::max(longest, t);
-      }
-      const double comp = std::max(longest, sum / (256.0 * conc) + 0.5 * longest);
-      const double tm = launch_cycles(comp, hbm, l2);
-      if (tm < best_t) {
-        best_t = tm;
-        best.w = w;
-        best.small = SM ? 1 : 0;
-        shapes = s;
+      if (over) continue;
+      for (size_t k = 0; k < parts.size(); ++k) {
+        const double conc = std::max(1.0, std::min((double)bpc, std::ceil(blocks * parts[k] / 256.0)));
+        const double c = iter_cycles<T, NF, EXTRA, RESID, SM>(w, conc), longest = most * c + kBlockCycles;
+        const double sum = parts[k] * (iters * c + blocks * kBlockCycles);
+        const double comp = std::max(longest, sum / (256.0 * conc) + 0.5 * longest);
+        const double tm = launch_cycles(comp, hbm[k], l2_bytes<T, NF, EXTRA, SM>(w, parts[k] * planes, parts[k] * pts));
+        if (tm < best[k].tm) best[k] = ClassBest{tm, w, SM ? 1 : 0, kIters[m] - 2 * (NF - 1)};
       }
     }
   }
 }
 
-template <typename T, int NF>
-void class_for(const std::vector<GridDesc>& g, const std::vector<double>& systems, int kind, RowsClass& c,
-               std::vector<RowsShape>& shapes) {
-  double t = 1e300;
-  if (kind & kFacResid) {
-    class_try<T, NF, true, true, false>(g, systems, c, t, shapes);
-    class_try<T, NF, true, true, true>(g, systems, c, t, shapes);
-  } else if (kind & kFacAdd) {
-    class_try<T, NF, true, false, false>(g, systems, c, t, shapes);
-    class_try<T, NF, true, false, true>(g, systems, c, t, shapes);
-  } else {
-    class_try<T, NF, false, false, false>(g, systems, c, t, shapes);
-    class_try<T, NF, false, false, true>(g, systems, c, t, shapes);
+template <typename T, int NF, bool EXTRA, bool RESID>
+bool class_of(const std::vector<GridDesc>& g, const std::vector<double>& systems, const std::vector<double>& parts,
+              RowsClass* c, std::vector<RowsShape>* shapes) {
+  std::vector<ClassBest> best(parts.size());
+  class_try<T, NF, EXTRA, RESID, false>(g, systems, parts, best);
+  class_try<T, NF, EXTRA, RESID, true>(g, systems, parts, best);
+  for (size_t k = 0; k < parts.size(); ++k) {
+    const ClassBest& b = best[k];
+    if (b.w == 0) return false;
+    c[k].w = b.w;
+    c[k].small = b.small;
+    shapes[k].resize(g.size());
+    for (size_t i = 0; i < g.size(); ++i)
+      if (b.small) shape_of<T, NF, EXTRA, true>(g[i], b.w, b.cz, shapes[k][i]);
+      else shape_of<T, NF, EXTRA, false>(g[i], b.w, b.cz, shapes[k][i]);
   }
+  return true;
 }
 
 template <typename T, int KIND, int NF>
@@ -156,17 +186,20 @@ bool MultiLaunch<T2>::factor_rows(hipStream_t st, const RowsClass& c, const Mult
 }
 
 template <typename T2>
-RowsClass MultiLaunch<T2>::rows_class(const std::vector<GridDesc>& g, const std::vector<double>& systems, int width,
-                                      int kind, std::vector<RowsShape>& shapes) {
+bool MultiLaunch<T2>::rows_class(const std::vector<GridDesc>& g, const std::vector<double>& systems,
+                                 const std::vector<double>& parts, RowsClass* c, std::vector<RowsShape>* shapes) {
   using T = typename zrows::Elem<T2>::t;
-  RowsClass c;
-  c.width = width;
-  c.kind = kind & (kFacResid | kFacAdd);
-  if (width == 2) zrows::class_for<T, 2>(g, systems, kind, c, shapes);
-  if (width == 3) zrows::class_for<T, 3>(g, systems, kind, c, shapes);
+  auto of = [&](auto nfc) {
+    constexpr int NF = decltype(nfc)::value;
+    return (c[0].kind & kFacResid) ? zrows::class_of<T, NF, true, true>(g, systems, parts, c, shapes)
+           : (c[0].kind & kFacAdd) ? zrows::class_of<T, NF, true, false>(g, systems, parts, c, shapes)
+                                   : zrows::class_of<T, NF, false, false>(g, systems, parts, c, shapes);
+  };
+  if (c[0].width == 2) return of(std::integral_constant<int, 2>{});
+  if (c[0].width == 3) return of(std::integral_constant<int, 3>{});
   if constexpr (sizeof(T2) == 8)
-    if (width == 4) zrows::class_for<T, 4>(g, systems, kind, c, shapes);
-  return c;
+    if (c[0].width == 4) return of(std::integral_constant<int, 4>{});
+  return false;
 }
 
 }  // namespace hfci

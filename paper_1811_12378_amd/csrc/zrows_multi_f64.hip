@@ -5,6 +5,6 @@ namespace hfci {
 template bool MultiLaunch<double2>::factor_rows(hipStream_t, const RowsClass&, const MultiInst*, const RowsShape*,
                                                const MultiSys<double2>*, const int2*, int, int, int, int, int, int, int,
                                                int);
-template RowsClass MultiLaunch<double2>::rows_class(const std::vector<GridDesc>&, const std::vector<double>&, int, int,
-                                                   std::vector<RowsShape>&);
+template bool MultiLaunch<double2>::rows_class(const std::vector<GridDesc>&, const std::vector<double>&,
+                                              const std::vector<double>&, RowsClass*, std::vector<RowsShape>*);
 }  // namespace hfci
