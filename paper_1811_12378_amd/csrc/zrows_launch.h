@@ -102,6 +102,13 @@ bool shape_of(const GridDesc& g, int w, int cz, RowsShape& s) {
   return true;
 }
 
+// Blocks of w waves on a CU at once, by registers (C::WMAX waves) and LDS (complex128 with three
+// factors: 30 KB for 2 waves, 55 KB for 4)
+template <typename T, int NF, class C>
+int blocks_per_cu(int w) {
+  return std::max(1, std::min(C::WMAX / w, (int)(160 * 1024 / lds_bytes(NF, w, 2 * sizeof(T)))));
+}
+
 // Planes a block steps through for a chunk, and CU cycles (2.4 GHz) of one of them for a block of
 // w waves with `conc` blocks on its CU at once; a block costs kBlockCycles beside.
 template <int NF>
@@ -139,7 +146,7 @@ void shape_try(const GridDesc& g, int count, RowsShape& best, double& best_t, Ro
   const int climit = chunk_limit<T>(g), cap = rows_cap<T, NF, EXTRA>(g);
   for (int w = C::WMAX; w >= 2; --w) {
     if (w > 2 && (w - 1) * C::R >= g.ny) continue;  // a smaller block covers every row
-    const int bpc = std::max(1, C::WMAX / w);       // blocks per CU (registers; LDS allows as many)
+    const int bpc = blocks_per_cu<T, NF, C>(w);
     for (const int m : {1, 2, 3, 4, 6, 8, 12, 16, 24, 32}) {
       const int cz = t.cz > 0 ? t.cz : 4 * m - 2 * (NF - 1) % 4;
       RowsShape s;

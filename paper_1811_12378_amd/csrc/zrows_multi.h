@@ -86,7 +86,7 @@ void class_try(const std::vector<GridDesc>& g, const std::vector<double>& system
     for (size_t k = 0; k < parts.size(); ++k) hbm[k] += hbm_bytes<T, EXTRA, RESID>(p, systems[i] * parts[k]);
   }
   for (int w = C::WMAX; w >= 2; --w) {
-    const int rb = w * C::R, bpc = std::max(1, C::WMAX / w);
+    const int rb = w * C::R, bpc = blocks_per_cu<T, NF, C>(w);
     if (lds_bytes(NF, w, 2 * sizeof(T)) > 160 * 1024) continue;
     bool ok = true;
     for (size_t i = 0; i < n; ++i) {

@@ -199,3 +199,24 @@ def test_batch_geometries_cover_the_grids_and_cost_little(tmp_path):
     out = run_native(BATCH, tmp_path)
     assert "bad" not in out, out
     assert 0.0 < float(out.split()[-1]) < 8.0, out
+
+
+# Blocks per CU in the cost model are bounded by LDS too: three factors in complex128 take 43 KB
+# for three waves, so three blocks fit where the registers would hold five.  With five the choice
+# for a thin grid is chunks of 48 planes (1.31 ms for six steps of nine factors, 44 systems), with
+# three it is 64 (1.21 ms).
+OCCUPANCY = r"""
+#include <cstdio>
+#include "kernels.h"
+using namespace hfci;
+int main() {
+  GridDesc g{};
+  g.nx = 239, g.ny = 3, g.nz = 167;
+  g.s_h2 = 1.0;
+  for (int kind : {0, (int)kFacResid, (int)kFacAdd}) printf("%d ", Launch<double2>::rows_shape(g, 3, kind, 45).czlen);
+}
+"""
+
+
+def test_cost_model_counts_the_blocks_that_fit_in_lds(tmp_path):
+    assert run_native(OCCUPANCY, tmp_path).split() == ["64", "64", "64"]
