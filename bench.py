@@ -62,7 +62,7 @@ def log(*a):
 
 def source_hash():
     h = hashlib.sha256()
-    for name in ("stencil.hip", "kernels.h"):
+    for name in ("stencil.hip", "zrows.h", "zrows_launch.h", "kernels.h"):
         with open(os.path.join(ROOT, "paper_1811_12378_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

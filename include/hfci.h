@@ -258,8 +258,9 @@ hfci_status hfci_apply(const hfci_op* op, hfci_c128 shift, int prec, int nvec,
  * As hfci_op_create, with the discrete Laplacian replaced by the Fourier-spectral one on
  * a periodic grid: S = F^H Lambda F, lambda = s sum_j (2 pi min(m_j, N_j - m_j)/(N_j h))^2
  * for the Fourier mode m (the paper's (l_min/N)^2 sum_j min(i_j^2, (N - i_j)^2)), applied
- * with transforms of the library's own where the sides have no prime factor above 7 and a
- * plane fits on a CU (to 140 x 140 in HFCI_F32, 98 x 98 in HFCI_F64), else with hipFFT's;
+ * with transforms of the library's own where the sides are above 1 and have no prime factor
+ * above 7, a plane fits on a CU (to 140 x 140 in HFCI_F32, 98 x 98 in HFCI_F64) and so do 64
+ * columns (nz to 312 and 156), and nz <= nx ny nz / 256 rounded up; else with hipFFT's;
  * kappa and the damping layer as for hfci_op_create.  The box
  * reported by hfci_op_info is [-kappa_max, lambda_max - kappa_min] x [-rho2, 0].
  * Accepted by hfci_op_info, hfci_op_get_tune, hfci_apply, hfci_contour_create / get / q,

@@ -244,8 +244,9 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
     // ---- step one: y1 = prod over the max(q-1, 1) factors of P2, applied to f ----
     // After it y = y1.  Unless a captured graph replays the later steps (their first launch
     // reads y) or no later step runs, step one writes y1 only, the first later step reads
-    // y1, and the systems that stop before any later step get y = y1 at the end.  With an
-    // odd number of factors the single launch comes first: it reads f, shared by the poles.
+    // y1, and the systems that stop before any later step get y = y1 at the end.  Without the
+    // passes in registers, which leave no factor alone, the single launch of an odd number of
+    // factors comes first: it reads f, shared by the poles.
     a.count = nsys;
     const int nP = std::max(q - 1, 1);
     const bool dual = (graphs && !pr.on) || (fixed && cap <= 1);
@@ -447,9 +448,14 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
 }  // namespace
 
 // Launch-shape autotuner: times the middle-factor kernel (the dominant launch of the
-// fixed-point iteration) over nsys systems for every valid shape, one, two and (complex64)
-// three factors per pass, and keeps the fastest per factor for this operator and precision.  Inputs are zeros and the factor is a fixed benign
-// one: the kernel's time does not depend on the values.
+// fixed-point iteration) over nsys systems for every valid shape, one to four factors per pass,
+// and keeps the fastest per factor for this operator and precision.  Inputs are zeros and the
+// factor is a fixed benign one: the kernel's time does not depend on the values.
+// Complex64 middle factors of cubes of 48 to 320 points a side with 2, 8 and 16 systems: the
+// passes in registers are the fastest in 23 of 27 cases, kern 3 with fuse 2 in four (128, 192 and
+// 320 with 16 systems, 256 with two: 0.83-0.98 of their time); kern 2, kern 3 with fuse 1 and
+// single factors in none (1.2-2.2, 1.1-3.6 and 1.4-2.8 times their time), but kern 2
+// runs the first and last launches of a fuse-2 step and kern 3's pairs what its threes leave.
 template <typename T2>
 KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, double>>& timings) {
   Ctx& ctx = *op.ctx;

@@ -64,8 +64,8 @@ void exec(hipfftHandle p, double2* x, int dir) {
 namespace {
 
 // The passes of sfft.hip: sides of prime factors up to 7, planes and 64 columns within LDS, and
-// planes of 256 points at least (its residual partials, one per plane, then need no more room
-// than the others').  Shifted solves of 16 systems, library and own: complex64 32^3 1118 and 876 us,
+// no more planes than spec_blocks: a 256th of the grid's points (the residual partials, one per
+// plane, then need no more room than the others').  Shifted solves of 16 systems, library and own: complex64 32^3 1118 and 876 us,
 // 48^3 2952 and 1246, 80 x 70 x 90 4583 and 2648, 96^3 5034 and 3200; complex128 32^3 1202 and
 // 1027 us, 96^3 6550 and 4837.  No grid that fits was found on which the library is faster.
 template <typename T2>

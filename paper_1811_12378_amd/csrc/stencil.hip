@@ -1563,7 +1563,7 @@ const KernelTune& tune_of(const GridDesc& g) {
   return sizeof(T) == 4 ? g.tune32 : g.tune64;
 }
 
-// nfill: the systems of a launch whose blocks write no partials: an unset shape may then take chunks
+// nfill: the systems of a launch whose blocks write no partials: a shape with cz 0 may then take chunks
 // down to 2 planes where those of 8 leave CUs without a block
 template <typename T>
 Shape shape_for(const GridDesc& g, int nsys, int nfill = 0) {

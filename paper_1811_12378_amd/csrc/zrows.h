@@ -1,6 +1,6 @@
 // Several consecutive factors of the product-form fixed-point step in one pass over HBM
 // (temporal blocking), planes held in registers: the launches of the shapes with fuse 1 and
-// kern 0 or 1, and of operators whose launch shape was never set.
+// kern 0 or 1 (a new operator's among them) and, where the grid does not suit kerns 2 and 3, of theirs.
 //
 //   t_1 = a_1 (A - z0) w + b_1 w,  t_f = a_f (A - z0) t_{f-1} + b_f t_{f-1},  out = t_NF [+ y1]
 //

@@ -176,7 +176,7 @@ void shape_try(const GridDesc& g, int count, RowsShape& best, double& best_t, Ro
 // launch shape's chunk.  A block's planes cost its vector instructions or, with few waves on
 // a CU, the latency of a barrier and the LDS exchange; short chunks repeat 2 (NF - 1) planes,
 // small blocks 2 NF rows; long chunks and large blocks leave CUs idle where systems are few.
-// The constants are fitted to 5000 measured launches (32^3 to 256^3, 1 to 24 systems, both
+// The constants are fitted to 6300 measured launches (32^3 to 256^3, 1 to 24 systems, both
 // precisions, every kind): the geometry chosen costs 4 % more than the best measured one on
 // average (33 % at worst), where one fixed geometry per grid costs 30 % and more at either end.
 template <typename T, int NF, bool EXTRA, bool RESID>

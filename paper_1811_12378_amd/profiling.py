@@ -122,7 +122,7 @@ def _counter_per_dispatch(d, counter, kernel_sub):
 
 def source_hash():
     h = hashlib.sha256()
-    for name in ("stencil.hip", "kernels.h"):
+    for name in ("stencil.hip", "zrows.h", "zrows_launch.h", "kernels.h"):
         with open(os.path.join(HERE, "csrc", name), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

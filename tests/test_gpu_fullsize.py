@@ -178,7 +178,7 @@ def test_tall_tiles_match_the_oracle_and_the_register_kernel(ctx, q, steps, cz, 
     # kern 3: the pairs without an extra stream on 64 x 28 tiles (the residual and y1 pairs
     # as kern 2), at a geometry whose tall tiles split into XCD slabs (72 per system with
     # cz 8), groups of systems taken sg at a time, every kind of pair launch; each result
-    # within the FP32 bar of the oracle and within twice it of the register pair kernel
+    # within the FP32 bar of the oracle and within twice it of the passes in registers
     assert tall_tiles(TALL_SHAPE, 8) == 72
     rng = np.random.default_rng(81)
     c = rng.uniform(1.0, 3.0, size=TALL_SHAPE)

@@ -48,7 +48,7 @@ def setup(ctx, shape, seed, q, J=4):
 
 @pytest.mark.parametrize("tune,q", [((1, 8, 2, 0, 1), 8), ((3, 8, 2, 0, 2, 1), 10)])
 def test_noalloc_equals_shifted_solve_twice(ctx, tune, q):
-    # call 1: complex64, two factors per pass (and, with kern 3 and fuse 2, the middle
+    # call 1: complex64, up to four factors per pass (and, with kern 3 and fuse 2, the middle
     # factors three per pass), adaptive stopping, 4 poles x 3 sources
     o, g, cg, poles, rng = setup(ctx, (20, 24, 30), 81, q)
     g.set_tune(32, *tune)
@@ -62,7 +62,7 @@ def test_noalloc_equals_shifted_solve_twice(ctx, tune, q):
     assert torch.equal(y, y_ref)
     assert len(set(st.ravel().tolist())) > 1  # the systems stop at different steps
 
-    # call 2, right after: a smaller grid, complex128, one factor per pass, fixed steps;
+    # call 2, right after: a smaller grid, complex128, the default shape, fixed steps;
     # the array still holds call 1's buffers, which must not leak into this result
     o2, g2, cg2, poles2, rng2 = setup(ctx, (12, 10, 14), 82, 5)
     f2 = rng2.standard_normal((1, 12, 10, 14)) + 1j * rng2.standard_normal((1, 12, 10, 14))
