@@ -290,6 +290,14 @@ std::vector<cd> poly_roots(std::vector<cd> coeffs);
 std::vector<Factor> factor_coefficients(cd z, cd z0, double delta, int q, cd& pz);
 
 // ---- solver.cpp ----
+// coefficients and constants of the tuner's launches: system s is pole s with one right-hand
+// side, and a launch reads up to four coefficients from the pole's first on
+struct TuneTables {
+  int cstride;
+  std::vector<FactorCoef> coef;  // [nsys][cstride]
+  std::vector<PoleDev> poles;    // [nsys]
+};
+TuneTables tune_tables(const Op& op, int nsys);
 template <typename T2>
 KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, double>>& timings);
 struct FciStats {

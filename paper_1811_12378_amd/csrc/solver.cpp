@@ -447,6 +447,19 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
 
 }  // namespace
 
+TuneTables tune_tables(const Op& op, int nsys) {
+  const PoleDev p{0.5 * (op.b1 + op.b2), 0.5, 0.0, 0.0};
+  const int q = 4;
+  TuneTables t;
+  t.cstride = q + q - 1;
+  t.poles.assign(nsys, p);
+  t.coef.resize((size_t)nsys * t.cstride);
+  const std::vector<Factor> k(t.cstride, Factor{cld(1e-3L), cld(0.5L)});
+  for (int s = 0; s < nsys; ++s)
+    complete_coefficients(k, q, cd(p.z0_re, p.z0_im), op.s_h2, cd(0.0, 0.0), &t.coef[(size_t)s * t.cstride]);
+  return t;
+}
+
 // Launch-shape autotuner: times the middle-factor kernel (the dominant launch of the
 // fixed-point iteration) over nsys systems for every valid shape, one to four factors per pass,
 // and keeps the fastest per factor for this operator and precision.  Inputs are zeros and the
@@ -464,17 +477,15 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   const size_t vbytes = n * sizeof(T2);
   T2* win = (T2*)ctx.ws.get("fp_wA", (size_t)nsys * vbytes);
   T2* wout = (T2*)ctx.ws.get("fp_wB", (size_t)nsys * vbytes);
-  FactorCoef* coef = (FactorCoef*)ctx.ws.get("tune_coef", 7 * sizeof(FactorCoef));
-  PoleDev* pole = (PoleDev*)ctx.ws.get("tune_pole", sizeof(PoleDev));
+  const TuneTables tables = tune_tables(op, nsys);
+  const size_t coef_bytes = tables.coef.size() * sizeof(FactorCoef), pole_bytes = tables.poles.size() * sizeof(PoleDev);
+  FactorCoef* coef = (FactorCoef*)ctx.ws.get("tune_coef", coef_bytes);
+  PoleDev* pole = (PoleDev*)ctx.ws.get("tune_pole", pole_bytes);
   int* list = (int*)ctx.ws.get("tune_list", (size_t)nsys * sizeof(int));
-  const PoleDev p0{0.5 * (op.b1 + op.b2), 0.5, 0.0, 0.0};
-  FactorCoef c0[4 + 3];
-  complete_coefficients(std::vector<Factor>(4 + 3, Factor{cld(1e-3L), cld(0.5L)}), 4, cd(p0.z0_re, p0.z0_im), op.s_h2,
-                        cd(0.0, 0.0), c0);
   std::vector<int> ids(nsys);
   for (int k = 0; k < nsys; ++k) ids[k] = k;
-  HFCI_HIP(hipMemcpyAsync(coef, c0, sizeof(c0), hipMemcpyHostToDevice, s));
-  HFCI_HIP(hipMemcpyAsync(pole, &p0, sizeof(p0), hipMemcpyHostToDevice, s));
+  HFCI_HIP(hipMemcpyAsync(coef, tables.coef.data(), coef_bytes, hipMemcpyHostToDevice, s));
+  HFCI_HIP(hipMemcpyAsync(pole, tables.poles.data(), pole_bytes, hipMemcpyHostToDevice, s));
   HFCI_HIP(hipMemcpyAsync(list, ids.data(), nsys * sizeof(int), hipMemcpyHostToDevice, s));
   launch_fill_zero(s, win, (size_t)nsys * vbytes);
   FactorArgs<T2> a{};
@@ -486,7 +497,7 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   a.count = nsys;
   a.sys0 = 0;
   a.nrhs = 1;
-  a.cstride = 7;
+  a.cstride = tables.cstride;
   a.k = 0;
   KernelTune& cur = (sizeof(T2) == 8) ? op.g.tune32 : op.g.tune64;
   const KernelTune saved = cur;

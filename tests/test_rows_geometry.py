@@ -220,3 +220,27 @@ int main() {
 
 def test_cost_model_counts_the_blocks_that_fit_in_lds(tmp_path):
     assert run_native(OCCUPANCY, tmp_path).split() == ["64", "64", "64"]
+
+
+# The tuner's launches take system s as pole s: its tables must have a pole, and the coefficients
+# of the widest launch, for every system it times.
+TUNE = r"""
+#include <cmath>
+#include <cstdio>
+#include "internal.h"
+using namespace hfci;
+int main() {
+  Op op;
+  op.s_h2 = 1.3, op.b1 = -1.0, op.b2 = 15.0;
+  for (int nsys : {1, 2, 8, 64}) {
+    const TuneTables t = tune_tables(op, nsys);
+    bool ok = t.poles.size() == (size_t)nsys && t.cstride >= kRowsMax32 && t.coef.size() == (size_t)nsys * t.cstride;
+    for (const FactorCoef& c : t.coef) ok = ok && std::isfinite(c.c_re) && c.a_re != 0.0;
+    printf("%s\n", ok ? "ok" : "bad");
+  }
+}
+"""
+
+
+def test_tuner_tables_cover_every_system(tmp_path):
+    assert run_native(TUNE, tmp_path).split() == ["ok"] * 4
