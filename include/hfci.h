@@ -235,16 +235,16 @@ hfci_status hfci_op_info(const hfci_op* op, double* out7);
 hfci_status hfci_op_set_tune(hfci_op* op, int prec, const int* tune6);
 hfci_status hfci_op_get_tune(const hfci_op* op, int prec, int* tune6);
 
-/* Launch-shape autotuner: times the middle factors of the fixed-point iteration
- * (the dominant launches) over nsys systems (1..64, e.g. the number of shifted
- * systems that usually iterate together) for every valid shape, one to
- * four factors per pass, keeps the fastest per factor for this operator and precision and writes
- * it to best6 (HOST, may be NULL).  timings (HOST, may be NULL if cap = 0) receives
- * up to cap rows of {kern, ty, pd, cz, fuse, sg, milliseconds per factor}; *count
- * (may be NULL) the number of shapes timed.  Uses the context's workspace (2 nsys
- * vectors of the precision); the operator's inputs and outputs of other calls are not
- * touched.  Timing-based, so two runs may pick different shapes (results then differ
- * only in the summation order of reductions).  Errors: HFCI_E_ARG. */
+/* Launch-shape autotuner: times a step's launches of the fixed-point iteration (first, middle
+ * and last of 10 factors) over nsys systems (1..64, e.g. the number of shifted systems that
+ * usually iterate together), a quarter of them and one, for every valid shape with sg = 1 and
+ * then the best one with other sg, keeps the fastest per factor for this operator and precision
+ * and writes it to best6 (HOST, may be NULL).  timings (HOST, may be NULL if cap = 0) receives
+ * up to cap rows of {kern, ty, pd, cz, fuse, sg, milliseconds per factor of nsys systems} (for
+ * shapes out of reach an estimate from their middle launches); *count (may be NULL) the number
+ * of shapes timed.  Uses the context's workspace (2 nsys vectors of the precision); the
+ * operator's inputs and outputs of other calls are not touched.  Timing-based, so two runs may
+ * pick different shapes (results then differ by rounding).  Errors: HFCI_E_ARG. */
 hfci_status hfci_op_autotune(hfci_op* op, int prec, int nsys, int* best6, double* timings, int cap,
                              int* count);
 

@@ -447,9 +447,11 @@ void fp_run(const Op& op, const Contour& c, int nrhs, const T2* f, T2* y, int sy
 
 }  // namespace
 
+constexpr int kTuneQ = 10;  // the headline solve's degree
+
 TuneTables tune_tables(const Op& op, int nsys) {
   const PoleDev p{0.5 * (op.b1 + op.b2), 0.5, 0.0, 0.0};
-  const int q = 4;
+  const int q = kTuneQ;
   TuneTables t;
   t.cstride = q + q - 1;
   t.poles.assign(nsys, p);
@@ -460,15 +462,19 @@ TuneTables tune_tables(const Op& op, int nsys) {
   return t;
 }
 
-// Launch-shape autotuner: times the middle-factor kernel (the dominant launch of the
-// fixed-point iteration) over nsys systems for every valid shape, one to four factors per pass,
-// and keeps the fastest per factor for this operator and precision.  Inputs are zeros and the
-// factor is a fixed benign one: the kernel's time does not depend on the values.
-// Complex64 middle factors of cubes of 48 to 320 points a side with 2, 8 and 16 systems: the
-// passes in registers are the fastest in 23 of 27 cases, kern 3 with fuse 2 in four (128, 192 and
-// 320 with 16 systems, 256 with two: 0.83-0.98 of their time); kern 2, kern 3 with fuse 1 and
-// single factors in none (1.2-2.2, 1.1-3.6 and 1.4-2.8 times their time), but kern 2
-// runs the first and last launches of a fuse-2 step and kern 3's pairs what its threes leave.
+// Launch-shape autotuner: times the launches of a later step of kTuneQ factors (first, middle and
+// last) for every valid shape, over nsys systems, a quarter of them (twice the weight) and one
+// (four times), and keeps the shape with the least time per factor and system.  Both ends of a
+// step, and the few systems that most steps of a solve run, belong to the choice: by the middle
+// launches over nsys systems alone, 128^3 complex64 with 16 systems went to kern 3 with fuse 2
+// (0.86 of the registers' time) or to chunks of 64 planes, and a solve with q = 10 and 6 systems
+// took 25.9 and 11.3 ms against 5.8 with the shape of a new operator.  Inputs are zeros and the
+// factor is a fixed benign one: a kernel's time does not depend on the values.
+// In such steps of complex64 cubes of 48 to 320 points a side with 2, 8 and 16 systems the passes
+// in registers are the fastest shape in 26 of 27 cases, kern 3 with fuse 2 in one (320 with 16
+// systems, 0.98 of their time; its threes are up to 17 % faster on sides of 128, 192, 256 and
+// 320, its ends are pairs); kern 2, kern 3 with fuse 1 and single factors in none (1.25 times
+// their time and more).
 template <typename T2>
 KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, double>>& timings) {
   Ctx& ctx = *op.ctx;
@@ -488,9 +494,11 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   HFCI_HIP(hipMemcpyAsync(pole, tables.poles.data(), pole_bytes, hipMemcpyHostToDevice, s));
   HFCI_HIP(hipMemcpyAsync(list, ids.data(), nsys * sizeof(int), hipMemcpyHostToDevice, s));
   launch_fill_zero(s, win, (size_t)nsys * vbytes);
+  launch_fill_zero(s, wout, (size_t)nsys * vbytes);
   FactorArgs<T2> a{};
   a.win = win;
   a.wout = wout;
+  a.f = a.y1 = wout;  // the extra streams of the first and last launches (zeros as well)
   a.coef = coef;
   a.poles = pole;
   a.list = list;
@@ -503,60 +511,95 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   const KernelTune saved = cur;
   const void* kap = Prec<T2>::kappa(op);
   std::vector<KernelTune> cands;
+  // several factors per pass: kern 1 in registers; kern 2 the complex64 pairs whose streams are
+  // loaded straight into LDS; kern 3 the same with 64 x 28 tiles for the middle pairs, two planes
+  // ahead only
+  for (int kern : {1, 2, 3}) {
+    if (kern >= 2 ? sizeof(T2) != 8 || !streams_fit(op.g) : !Launch<T2>::rows_fits(op.g)) continue;
+    for (int cz : {0, 16, 64})
+      for (int pd : {2, 3})
+        if (pd == 2 || kern == 2) cands.push_back(KernelTune{kern, 8, pd, cz, 1, 1});
+  }
+  // three middle factors per pass
+  if (sizeof(T2) == 8 && streams_fit(op.g))
+    for (int cz : {0, 16, 64}) cands.push_back(KernelTune{3, 8, 2, cz, 2, 1});
+  // one factor per pass, last: the others' times then rule most of them out
   for (int cz : {0, 16, 64}) {
     for (int ty : {4, 8})
       for (int pd : {1, 2}) cands.push_back(KernelTune{0, ty, pd, cz, 0});
     for (int pd : {1, 2, 3}) cands.push_back(KernelTune{1, 4, pd, cz, 0});
     for (int pd : {2, 3}) cands.push_back(KernelTune{1, 8, pd, cz, 0});
   }
-  // several factors per pass (per-factor time = a launch over its factors), with the systems
-  // of a launch taken one, two or four at a time tile by tile: kern 1 in registers; kern 2 the
-  // complex64 pairs whose streams are loaded straight into LDS; kern 3 the same with 64 x 28
-  // tiles for the middle pairs, two planes ahead only
-  for (int kern : {1, 2, 3}) {
-    if (kern >= 2 ? sizeof(T2) != 8 || !streams_fit(op.g) : !Launch<T2>::rows_fits(op.g)) continue;
-    for (int cz : {0, 16, 64})
-      for (int pd : {2, 3})
-        for (int sg : {1, 2, 4})
-          if ((sg == 1 || sg <= nsys) && !((kern == 3 || kern == 1) && pd != 2))
-            cands.push_back(KernelTune{kern, 8, pd, cz, 1, sg});
-  }
-  // three middle factors per pass (kern 3, fuse 2; per-factor time = a third of a launch)
-  if (sizeof(T2) == 8 && streams_fit(op.g))
-    for (int cz : {0, 16, 64})
-      for (int sg : {1, 2, 4})
-        if (sg == 1 || sg <= nsys) cands.push_back(KernelTune{3, 8, 2, cz, 2, sg});
   hipEvent_t e0, e1;
   HFCI_HIP(hipEventCreateWithFlags(&e0, hipEventDisableSystemFence));
   HFCI_HIP(hipEventCreateWithFlags(&e1, hipEventDisableSystemFence));
   KernelTune best = saved;
-  double best_ms = 1e300;
+  double best_ms = 1e300, best_middle = 1e300;
   timings.clear();
   try {
-    for (const KernelTune& t : cands) {
+    bool groups = false;
+    for (size_t ic = 0; ic < cands.size(); ++ic) {
+      const KernelTune t = cands[ic];
+      if (ic + 1 == cands.size() && !groups && best.fuse != 0) {
+        // then the best shape with the systems of a launch taken two or four at a time, tile by tile
+        groups = true;
+        for (int sg : {2, 4})
+          if (sg <= nsys) cands.push_back(KernelTune{best.kern, best.ty, best.pd, best.cz, best.fuse, sg});
+      }
       if (t.cz > 0 && t.cz >= op.g.nz) continue;  // same as one chunk per column: covered by cz = 0 or larger
       cur = t;
-      const int rows = Launch<T2>::rows_run(op.g) ? (sizeof(T2) == 8 ? kRowsMax32 : kRowsMax64) : 0;
       if (t.fuse == 2 && !Launch<T2>::triple_runs(op.g)) continue;  // (an odd nx: the pairs' shape covers it)
-      const RowsShape sh = rows ? Launch<T2>::rows_shape(op.g, rows, 0, nsys) : RowsShape{};
-      auto one = [&] {
-        if (rows) Launch<T2>::factor_rows(s, op.g, kap, a, 0, rows, sh);
-        else if (t.fuse == 2) Launch<T2>::factor_triple(s, op.g, kap, a);
-        else if (t.fuse) Launch<T2>::factor_pair(s, op.g, kap, a, 0);
-        else Launch<T2>::factor(s, op.g, kap, a, 0);
+      // a step's launches: widths of the first, a middle and the last one, and how often the middle
+      const bool rows = Launch<T2>::rows_run(op.g);
+      const std::vector<int> w = rows            ? rows_plan(kTuneQ, sizeof(T2) == 8 ? kRowsMax32 : kRowsMax64, true)
+                                 : t.fuse == 2 ? std::vector<int>{2, 3, 3, 2}
+                                               : std::vector<int>(kTuneQ / (t.fuse ? 2 : 1), t.fuse ? 2 : 1);
+      const double middles = (double)w.size() - 2.0;
+      // milliseconds of one launch over `count` systems
+      auto timed = [&](int width, int kind, int count) {
+        a.count = count;
+        RowsShape sh;
+        if (rows) sh = Launch<T2>::rows_shape(op.g, width, kind, count);
+        const size_t nblk = rows        ? sh.per_sys
+                            : width > 1 ? Launch<T2>::pair_blocks(op.g)
+                                        : Launch<T2>::partial_blocks(op.g);
+        a.partial = (double*)ctx.ws.get("tune_partial", (size_t)nsys * nblk * sizeof(double));
+        auto one = [&] {
+          if (rows) Launch<T2>::factor_rows(s, op.g, kap, a, kind, width, sh);
+          else if (width == 3) Launch<T2>::factor_triple(s, op.g, kap, a);
+          else if (width == 2) Launch<T2>::factor_pair(s, op.g, kap, a, kind);
+          else Launch<T2>::factor(s, op.g, kap, a, kind);
+        };
+        auto run = [&](int reps) {
+          HFCI_HIP(hipEventRecord(e0, s));
+          for (int r = 0; r < reps; ++r) one();
+          HFCI_HIP(hipEventRecord(e1, s));
+          HFCI_HIP(hipEventSynchronize(e1));
+          float ms = 0.f;
+          HFCI_HIP(hipEventElapsedTime(&ms, e0, e1));
+          return (double)ms / reps;
+        };
+        const double warm = run(1);
+        return run(warm > 0.5 ? 1 : 3);
       };
-      one();  // warm-up
-      HFCI_HIP(hipEventRecord(e0, s));
-      const int reps = 3;
-      for (int r = 0; r < reps; ++r) one();
-      HFCI_HIP(hipEventRecord(e1, s));
-      HFCI_HIP(hipEventSynchronize(e1));
-      float ms = 0.f;
-      HFCI_HIP(hipEventElapsedTime(&ms, e0, e1));
-      const double avg = ms / reps / (rows ? (double)rows : t.fuse == 2 ? 3.0 : t.fuse ? 2.0 : 1.0);  // per factor
-      timings.emplace_back(t, avg);
-      if (avg < best_ms) {
-        best_ms = avg;
+      // per factor: the steps of three counts, in proportion to the systems; of a shape whose middle
+      // launches over nsys systems are slower by a quarter, an estimate from those
+      const double middle = timed(w[1], 0, nsys), ratio = middle / w[1] / best_middle;
+      double per = best_ms * ratio;
+      if (ratio < 1.25) {
+        double ms = 0.0, systems = 0.0;
+        for (int c = 0; c < 3; ++c) {
+          const int count = c == 0 ? nsys : c == 1 ? (nsys + 3) / 4 : 1, weight = 1 << c;
+          const double mid = c == 0 ? middle : timed(w[1], 0, count);
+          ms += weight * (timed(w.front(), kFacResid, count) + middles * mid + timed(w.back(), kFacAdd, count));
+          systems += weight * count;
+        }
+        per = ms / systems * nsys / kTuneQ;
+      }
+      timings.emplace_back(t, per);
+      if (per < best_ms) {
+        best_ms = per;
+        best_middle = middle / w[1];
         best = cur;
       }
     }

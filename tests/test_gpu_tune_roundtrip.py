@@ -1,4 +1,4 @@
-"""Reading an operator's launch shape and setting it again changes nothing (needs an MI355X)."""
+"""Launch shapes: read and set again, and tuned against untuned (needs an MI355X)."""
 import numpy as np
 import pytest
 
@@ -30,3 +30,33 @@ def test_setting_the_shape_that_was_read_is_the_identity(ctx, prec, first):  # n
     g.set_tune(prec, *shape)
     y2, s2 = hf.shifted_solve(g, cg, fd, **kw)
     assert np.array_equal(s0, s2) and torch.equal(y0, y2)
+
+
+def test_tuning_does_not_slow_solves_with_few_systems(ctx):  # noqa: F811
+    # 128^3 complex64, 6 systems of which one or two iterate for most steps.  A tuner that looks
+    # at the middle launches over many systems only picks chunks or tiles that cost these solves
+    # 2 to 4.5 times the untuned time; one that looks at whole steps and few systems stays within
+    # 5 % of it or below.  The bar, on medians of nine, lies between.
+    import time
+    c = np.full((128, 128, 128), 2.0)
+    h = 1.0 / 128
+    g = hf.Operator(ctx, dev(c), h, 2 * 2 * np.pi / (8 * h), 8, 1.0)
+    cg = hf.Contour(g, 6, 1.0, 0.05, 10)
+    rng = np.random.default_rng(7)
+    fd = dev(rng.standard_normal((1, 128, 128, 128)) + 1j * rng.standard_normal((1, 128, 128, 128))).to(torch.complex64)
+
+    def median():
+        t = []
+        for _ in range(11):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            hf.shifted_solve(g, cg, fd, reduce=5.0, max_steps=60)
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return sorted(t[2:])[4]
+
+    untuned = median()
+    for nsys in (8, 16):
+        best, rows = g.autotune(32, nsys)
+        assert best == min(rows, key=lambda r: r[1])[0]
+        assert median() <= 1.3 * untuned, (nsys, best)
