@@ -15,7 +15,8 @@
 // Lambda is looked up by place (params: SpecFft::lam).  The lanes of a wave are 64 lines of the
 // other axis, so a stage's indices and twiddles are the wave's (scalar), the loads of the first
 // stage and the stores of the last are coalesced, and with an odd row pitch no LDS access
-// meets a bank twice.  Twiddles are rounded from double.
+// meets a bank twice (planes with a short side: see thin).  Twiddles are rounded from double.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -131,13 +132,18 @@ struct AllAtOnce<S, std::void_t<typename S::AllTag>> : std::true_type {};
 // One stage over `lines` lines of n values split into blocks of L: forward the DFT of R values
 // m = L / R apart, then the twiddles exp(-2 pi i j p / L); inverse the reverse.  MID: the last
 // forward stage (L = R), a factor per place, the first inverse stage.
+// PACK: up to 32 lines, and a wave takes 64 / lines butterflies of every line at once (indices and
+// twiddles are then the lane's).
 enum StageKind { FWD, INV, MID };
-template <int R, StageKind KIND, typename T, class Ld, class St>
+template <int R, StageKind KIND, typename T, bool PACK, class Ld, class St>
 __device__ __forceinline__ void stage_r(int n, int L, int lines, int wave, int nw, int lane,
                                         const typename V2<T>::t* __restrict__ tw, const double* __restrict__ lam,
                                         Ld ld, St st) {
   const int m = L / R, nb = n / R, step = n / L;
-  for (int jj = wave; jj < nb; jj += nw) {  // uniform over the wave
+  const int per = PACK ? 64 / lines : 1, g = PACK ? lane / lines : 0, l0 = PACK ? lane - g * lines : lane;
+  for (int j0 = wave * per; j0 < nb; j0 += nw * per) {  // uniform over the wave
+    const int jj = j0 + g;
+    if (PACK && (g >= per || jj >= nb)) continue;
     const int q = jj / m, j = jj - q * m, base = q * L + j;
     Cp<T> w[R];
     double f[R];
@@ -150,7 +156,7 @@ __device__ __forceinline__ void stage_r(int n, int L, int lines, int wave, int n
         w[p] = {x.x, x.y};
       }
     }
-    for (int l = lane; l < lines; l += 64) {
+    for (int l = l0; l < lines; l += 64) {
       Cp<T> v[R];
 #pragma unroll
       for (int k = 0; k < R; ++k) v[k] = ld(l, base + k * m);
@@ -177,18 +183,27 @@ __device__ __forceinline__ void stage_r(int n, int L, int lines, int wave, int n
     }
   }
 }
-template <StageKind KIND, typename T, class Ld, class St>
+template <StageKind KIND, typename T, bool PACK, class Ld, class St>
+__device__ __forceinline__ void stage_p(int r, int n, int L, int lines, int wave, int nw, int lane,
+                                        const typename V2<T>::t* __restrict__ tw, const double* __restrict__ lam, Ld ld,
+                                        St st) {
+  switch (r) {
+    case 2: return stage_r<2, KIND, T, PACK>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
+    case 3: return stage_r<3, KIND, T, PACK>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
+    case 4: return stage_r<4, KIND, T, PACK>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
+    case 5: return stage_r<5, KIND, T, PACK>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
+    case 7: return stage_r<7, KIND, T, PACK>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
+    default: return stage_r<8, KIND, T, PACK>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
+  }
+}
+// THIN: kernels for planes with a side of few points (thin), which share a wave's lanes
+constexpr int kThin = 32;
+template <StageKind KIND, typename T, bool THIN, class Ld, class St>
 __device__ __forceinline__ void stage(int r, int n, int L, int lines, int wave, int nw, int lane,
                                       const typename V2<T>::t* __restrict__ tw, const double* __restrict__ lam, Ld ld,
                                       St st) {
-  switch (r) {
-    case 2: return stage_r<2, KIND, T>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
-    case 3: return stage_r<3, KIND, T>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
-    case 4: return stage_r<4, KIND, T>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
-    case 5: return stage_r<5, KIND, T>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
-    case 7: return stage_r<7, KIND, T>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
-    default: return stage_r<8, KIND, T>(n, L, lines, wave, nw, lane, tw, lam, ld, st);
-  }
+  if (THIN && lines <= kThin) return stage_p<KIND, T, true>(r, n, L, lines, wave, nw, lane, tw, lam, ld, st);
+  stage_p<KIND, T, false>(r, n, L, lines, wave, nw, lane, tw, lam, ld, st);
 }
 
 template <typename T>
@@ -208,9 +223,23 @@ struct LdsAt {  // value idx of line l at l * ls + idx * is
 
 extern __shared__ double2 sfft_lds[];
 
+// a thin plane from one place to another, point by point and four values per thread at a time
+template <class Ld, class St>
+__device__ __forceinline__ void copy_thin(int nx, int points, int tid, int nt, Ld ld, St st) {
+  for (int p = tid; p < points; p += 4 * nt) {
+    decltype(ld(0, 0)) t[4];
+    auto at = [&](int i) { return min(p + i * nt, points - 1); };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = ld(at(i) % nx, at(i) / nx);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (p + i * nt < points) st(at(i) % nx, at(i) / nx, t[i]);
+  }
+}
+
 // y then x of plane blockIdx.x of vector v = blockIdx.y: from in (of system sys[v], if sys) to out
-template <typename T>
-__global__ __launch_bounds__(1024) void sfft_plane_fwd_kernel(GridDesc g, SpecFft sf, const typename V2<T>::t* in,
+template <typename T, bool THIN>
+__global__ __launch_bounds__(THIN ? 512 : 1024) void sfft_plane_fwd_kernel(GridDesc g, SpecFft sf, const typename V2<T>::t* in,
                                                               typename V2<T>::t* out, const int* __restrict__ sys) {
   using T2 = typename V2<T>::t;
   const int nx = g.nx, ny = g.ny, pitch = nx | 1;
@@ -225,22 +254,27 @@ __global__ __launch_bounds__(1024) void sfft_plane_fwd_kernel(GridDesc g, SpecFf
   int L = ny;
   for (int i = 0; i < sf.y.ns; ++i) {
     if (i == 0)
-      stage<FWD, T>(sf.y.r[0], ny, L, nx, wave, nw, lane, tw + nx, nullptr,
+      stage<FWD, T, THIN>(sf.y.r[0], ny, L, nx, wave, nw, lane, tw + nx, nullptr,
                     [&](int x, int y) {
                       const T2 u = I[(size_t)y * nx + x];
                       return Cp<T>{u.x, u.y};
                     },
                     byx);
     else
-      stage<FWD, T>(sf.y.r[i], ny, L, nx, wave, nw, lane, tw + nx, nullptr, byx, byx);
+      stage<FWD, T, THIN>(sf.y.r[i], ny, L, nx, wave, nw, lane, tw + nx, nullptr, byx, byx);
     L /= sf.y.r[i];
     __syncthreads();
   }
   L = nx;
   for (int i = 0; i < sf.x.ns; ++i) {
-    stage<FWD, T>(sf.x.r[i], nx, L, ny, wave, nw, lane, tw, nullptr, byy, byy);
+    stage<FWD, T, THIN>(sf.x.r[i], nx, L, ny, wave, nw, lane, tw, nullptr, byy, byy);
     L /= sf.x.r[i];
     __syncthreads();
+  }
+  if constexpr (THIN) {
+    copy_thin(nx, nx * ny, threadIdx.x, blockDim.x, [&](int x, int y) { return s[y * pitch + x]; },
+              [&](int x, int y, const T2& v) { O[(size_t)y * nx + x] = v; });
+    return;
   }
   for (int y = wave; y < ny; y += 4 * nw)
     for (int x = lane; x < nx; x += 64) {
@@ -270,20 +304,23 @@ struct Scaled {
   }
 };
 
-// z forward, Lambda / N, z inverse of 64 columns (places) of a vector, in place
-template <typename T>
+// z forward, Lambda / N, z inverse of COLS columns (places) of a vector, in place: 64, or 32 where
+// 64 leave room for one block per CU only (solves of 30 systems: 150 x 64 x 64 complex128 6 % faster
+// with 32, 300 x 64 x 64 complex64 6 %; with 64 KB for 64 columns, 128^3 complex64, 3 % slower)
+template <typename T, int COLS>
 __global__ __launch_bounds__(512) void sfft_z_kernel(GridDesc g, SpecFft sf, typename V2<T>::t* c) {
   using T2 = typename V2<T>::t;
   const int nx = g.nx, ny = g.ny, nz = g.nz;
   const size_t plane = (size_t)nx * ny, n = plane * nz;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x / 64;
-  const int col = blockIdx.x * 64 + lane;
+  constexpr bool PACK = COLS <= 32;
+  const int col = blockIdx.x * COLS + lane % COLS;
   const bool ok = col < (int)plane;
   T2* C = c + (size_t)blockIdx.y * n + (ok ? col : 0);
   T2* s = (T2*)sfft_lds;
   const T2* tw = (const T2*)(sizeof(T) == 4 ? (const void*)sf.tw32 : (const void*)sf.tw64) + nx + ny;
   const double* lz = sf.lam + nx + ny;
-  const LdsAt<T> lds{s, 1, 64};
+  const LdsAt<T> lds{s, 1, COLS};
   const double mine = ok ? sf.lam[col % nx] + sf.lam[nx + col / nx] : 0.0;
   const double inv_n = 1.0 / (double)n;
   auto from = [&](int, int z) {
@@ -298,26 +335,26 @@ __global__ __launch_bounds__(512) void sfft_z_kernel(GridDesc g, SpecFft sf, typ
     C[(size_t)z * plane] = o;
   };
   const int ns = sf.z.ns;
-  if (ns == 1) return stage<MID, T>(sf.z.r[0], nz, nz, 64, wave, nw, lane, tw, lz, from,
+  if (ns == 1) return stage_p<MID, T, PACK>(sf.z.r[0], nz, nz, COLS, wave, nw, lane, tw, lz, from,
                                    Scaled<T, decltype(to)>{to, inv_n, mine});
   int L = nz;
   for (int i = 0; i < ns - 1; ++i) {
     if (i == 0)
-      stage<FWD, T>(sf.z.r[0], nz, L, 64, wave, nw, lane, tw, lz, from, lds);
+      stage_p<FWD, T, PACK>(sf.z.r[0], nz, L, COLS, wave, nw, lane, tw, lz, from, lds);
     else
-      stage<FWD, T>(sf.z.r[i], nz, L, 64, wave, nw, lane, tw, lz, lds, lds);
+      stage_p<FWD, T, PACK>(sf.z.r[i], nz, L, COLS, wave, nw, lane, tw, lz, lds, lds);
     L /= sf.z.r[i];
     __syncthreads();
   }
-  stage<MID, T>(sf.z.r[ns - 1], nz, L, 64, wave, nw, lane, tw, lz, lds,
+  stage_p<MID, T, PACK>(sf.z.r[ns - 1], nz, L, COLS, wave, nw, lane, tw, lz, lds,
                 Scaled<T, LdsAt<T>>{lds, inv_n, mine});
   for (int i = ns - 2; i >= 0; --i) {
     __syncthreads();
     L *= sf.z.r[i];
     if (i == 0)
-      stage<INV, T>(sf.z.r[0], nz, L, 64, wave, nw, lane, tw, lz, lds, to);
+      stage_p<INV, T, PACK>(sf.z.r[0], nz, L, COLS, wave, nw, lane, tw, lz, lds, to);
     else
-      stage<INV, T>(sf.z.r[i], nz, L, 64, wave, nw, lane, tw, lz, lds, lds);
+      stage_p<INV, T, PACK>(sf.z.r[i], nz, L, COLS, wave, nw, lane, tw, lz, lds, lds);
   }
 }
 
@@ -397,8 +434,8 @@ struct Finish {
 
 // inverse over x and y of plane blockIdx.x of vector blockIdx.y at a.sw, then the factor of its
 // system
-template <typename T, int KIND>
-__global__ __launch_bounds__(1024) void sfft_plane_inv_kernel(GridDesc g, SpecFft sf, const T* __restrict__ K,
+template <typename T, int KIND, bool THIN>
+__global__ __launch_bounds__(THIN ? 512 : 1024) void sfft_plane_inv_kernel(GridDesc g, SpecFft sf, const T* __restrict__ K,
                                                               SpecArgs<typename V2<T>::t> a,
                                                               const int* __restrict__ sys) {
   using T2 = typename V2<T>::t;
@@ -412,20 +449,25 @@ __global__ __launch_bounds__(1024) void sfft_plane_inv_kernel(GridDesc g, SpecFf
   const T2* tw = (const T2*)(sizeof(T) == 4 ? (const void*)sf.tw32 : (const void*)sf.tw64);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x / 64;
   const LdsAt<T> byx{s, 1, pitch}, byy{s, pitch, 1};
-  for (int y = wave; y < ny; y += 4 * nw)
-    for (int x = lane; x < nx; x += 64) {
-      T2 t[4];
+  if constexpr (THIN) {
+    copy_thin(nx, nx * ny, threadIdx.x, blockDim.x, [&](int x, int y) { return C[(size_t)y * nx + x]; },
+              [&](int x, int y, const T2& v) { s[y * pitch + x] = v; });
+  } else {
+    for (int y = wave; y < ny; y += 4 * nw)
+      for (int x = lane; x < nx; x += 64) {
+        T2 t[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) t[i] = C[(size_t)min(y + i * nw, ny - 1) * nx + x];
+        for (int i = 0; i < 4; ++i) t[i] = C[(size_t)min(y + i * nw, ny - 1) * nx + x];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (y + i * nw < ny) s[(y + i * nw) * pitch + x] = t[i];
-    }
+        for (int i = 0; i < 4; ++i)
+          if (y + i * nw < ny) s[(y + i * nw) * pitch + x] = t[i];
+      }
+  }
   int L = 1;
   for (int i = sf.x.ns - 1; i >= 0; --i) {
     __syncthreads();
     L *= sf.x.r[i];
-    stage<INV, T>(sf.x.r[i], nx, L, ny, wave, nw, lane, tw, nullptr, byy, byy);
+    stage<INV, T, THIN>(sf.x.r[i], nx, L, ny, wave, nw, lane, tw, nullptr, byy, byy);
   }
   double acc = 0.0;
   Fin fin{};
@@ -454,9 +496,9 @@ __global__ __launch_bounds__(1024) void sfft_plane_inv_kernel(GridDesc g, SpecFf
     __syncthreads();
     L *= sf.y.r[i];
     if (i == 0)
-      stage<INV, T>(sf.y.r[0], ny, L, nx, wave, nw, lane, tw + nx, nullptr, byx, fin);
+      stage<INV, T, THIN>(sf.y.r[0], ny, L, nx, wave, nw, lane, tw + nx, nullptr, byx, fin);
     else
-      stage<INV, T>(sf.y.r[i], ny, L, nx, wave, nw, lane, tw + nx, nullptr, byx, byx);
+      stage<INV, T, THIN>(sf.y.r[i], ny, L, nx, wave, nw, lane, tw + nx, nullptr, byx, byx);
   }
   if constexpr (Fin::RESID) {
 #pragma unroll
@@ -473,15 +515,41 @@ __global__ __launch_bounds__(1024) void sfft_plane_inv_kernel(GridDesc g, SpecFf
 
 template <typename T>
 size_t plane_lds(const GridDesc& g) { return (size_t)g.ny * (g.nx | 1) * 2 * sizeof(T); }
-// two blocks per CU where the planes leave room for them
+// Whether a wave's lanes are shared between butterflies.  With few lines most lanes idle otherwise: 30
+// complex64 systems of 300 x 24 x 24 points (z, y, x) took 1.32 times the library's time, now 0.81 of it.
+// In complex128 the lanes' own twiddles cost registers: from 9 lines on the idle lanes cost less
+// (30 systems of 128 x 128 x 12: 1.15 of the library's time with, 0.9 without; 64 x 4 x 256 0.86 with,
+// 1.75 without), unless there are too few blocks to fill the chip anyway (six of 36 x 128 x 16: 0.74 with,
+// 0.88 without).  The results have the same bits either way.
 template <typename T>
-int plane_threads(const GridDesc& g) { return plane_lds<T>(g) > 52 * 1024 ? 1024 : 512; }
+bool thin(const GridDesc& g, int nvec) {
+  return std::min(g.nx, g.ny) <= (sizeof(T) == 4 || (long)g.nz * nvec <= 384 ? kThin : 8);
+}
+// Two blocks per CU where the planes leave room for them; in a thin plane as many waves as its
+// busiest stage has work for, up to eight (idle ones would hold the registers of other blocks: 30
+// complex128 systems of 64 x 4 x 256 points took 1.45 times the library's time in blocks of eight waves,
+// 0.86 in blocks of four).
+template <typename T>
+int plane_threads(const GridDesc& g, const SpecFft& sf, int nvec) {
+  if (!thin<T>(g, nvec)) return plane_lds<T>(g) > 52 * 1024 ? 1024 : 512;
+  int waves = 1;
+  auto axis = [&](const AxisStages& a, int n, int lines) {
+    const int per = lines <= kThin ? 64 / lines : 1;
+    for (int i = 0; i < a.ns; ++i) waves = std::max(waves, (n / a.r[i] + per - 1) / per);
+  };
+  axis(sf.x, g.nx, g.ny);
+  axis(sf.y, g.ny, g.nx);
+  return 64 * std::min(waves, 8);
+}
 
 template <typename T, int KIND>
 void launch_inv(hipStream_t st, const GridDesc& g, const SpecFft& sf, const T* K,
                 const SpecArgs<typename V2<T>::t>& a, const int* sys, int nvec) {
-  hipLaunchKernelGGL((sfft_plane_inv_kernel<T, KIND>), dim3(g.nz, nvec), dim3(plane_threads<T>(g)), plane_lds<T>(g),
-                     st, g, sf, K, a, sys);
+  const dim3 grid(g.nz, nvec), block(plane_threads<T>(g, sf, nvec));
+  if (thin<T>(g, nvec))
+    hipLaunchKernelGGL((sfft_plane_inv_kernel<T, KIND, true>), grid, block, plane_lds<T>(g), st, g, sf, K, a, sys);
+  else
+    hipLaunchKernelGGL((sfft_plane_inv_kernel<T, KIND, false>), grid, block, plane_lds<T>(g), st, g, sf, K, a, sys);
 }
 
 }  // namespace
@@ -513,10 +581,18 @@ template <typename T2>
 void launch_sfft_fwd(hipStream_t st, const GridDesc& g, const SpecFft& sf, const T2* in, T2* out, const int* sys,
                      int nvec) {
   using T = decltype(T2::x);
-  hipLaunchKernelGGL(sfft_plane_fwd_kernel<T>, dim3(g.nz, nvec), dim3(plane_threads<T>(g)), plane_lds<T>(g), st, g,
-                     sf, in, out, sys);
-  const unsigned tiles = (unsigned)(((size_t)g.nx * g.ny + 63) / 64);
-  hipLaunchKernelGGL(sfft_z_kernel<T>, dim3(tiles, nvec), dim3(512), (size_t)g.nz * 64 * sizeof(T2), st, g, sf, out);
+  const dim3 grid(g.nz, nvec), block(plane_threads<T>(g, sf, nvec));
+  if (thin<T>(g, nvec))
+    hipLaunchKernelGGL((sfft_plane_fwd_kernel<T, true>), grid, block, plane_lds<T>(g), st, g, sf, in, out, sys);
+  else
+    hipLaunchKernelGGL((sfft_plane_fwd_kernel<T, false>), grid, block, plane_lds<T>(g), st, g, sf, in, out, sys);
+  const size_t plane = (size_t)g.nx * g.ny, column = g.nz * sizeof(T2);
+  if (64 * column > 72 * 1024)
+    hipLaunchKernelGGL((sfft_z_kernel<T, 32>), dim3((unsigned)((plane + 31) / 32), nvec), dim3(512), 32 * column, st, g, sf,
+                       out);
+  else
+    hipLaunchKernelGGL((sfft_z_kernel<T, 64>), dim3((unsigned)((plane + 63) / 64), nvec), dim3(512), 64 * column, st, g, sf,
+                       out);
 }
 template void launch_sfft_fwd<float2>(hipStream_t, const GridDesc&, const SpecFft&, const float2*, float2*, const int*,
                                       int);

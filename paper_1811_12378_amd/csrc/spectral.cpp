@@ -65,9 +65,12 @@ namespace {
 
 // The passes of sfft.hip: sides of prime factors up to 7, planes and 64 columns within LDS, and
 // no more planes than spec_blocks: a 256th of the grid's points (the residual partials, one per
-// plane, then need no more room than the others').  Shifted solves of 16 systems, library and own: complex64 32^3 1118 and 876 us,
-// 48^3 2952 and 1246, 80 x 70 x 90 4583 and 2648, 96^3 5034 and 3200; complex128 32^3 1202 and
-// 1027 us, 96^3 6550 and 4837.  No grid that fits was found on which the library is faster.
+// plane, then need no more room than the others').  Shifted solves of 16 systems, library and own:
+// complex64 32^3 1118 and 876 us, 48^3 2952 and 1246, 80 x 70 x 90 4583 and 2648, 96^3 5034 and
+// 3200; complex128 32^3 1202 and 1027 us, 96^3 6550 and 4837.  Of 312 solves of 6 and 30 systems on
+// 90 grids (sides from 2 to 300, thin planes and long columns among them) the library is faster in
+// five, complex128 with 30 systems, by 2 to 9 %: 144 x 5 x 300, 80 x 126 x 10, 64 x 64 x 16,
+// 56 x 5 x 216, 36 x 128 x 16; in the median the own passes take 0.58 of its time.
 template <typename T2>
 bool own_fft(const Op& op) {
   return op.smooth && sfft_fits(op.g, sizeof(T2) == 16) && op.g.nz <= spec_blocks(op.g);
