@@ -237,9 +237,9 @@ hfci_status hfci_op_get_tune(const hfci_op* op, int prec, int* tune6);
 
 /* Launch-shape autotuner: times a step's launches of the fixed-point iteration (first, middle
  * and last of 10 factors) over nsys systems (1..64, e.g. the number of shifted systems that
- * usually iterate together), a quarter of them and one, for every valid shape with sg = 1 and
- * then the best one with other sg, keeps the fastest per factor for this operator and precision
- * and writes it to best6 (HOST, may be NULL).  timings (HOST, may be NULL if cap = 0) receives
+ * usually iterate together), a quarter of them and one, for the valid shapes with sg = 1 (fuse 0
+ * with other z-chunks than cz = 0 only where it is in reach) and then the best one with other
+ * sg, keeps the fastest per factor for this operator and precision and writes it to best6 (HOST, may be NULL).  timings (HOST, may be NULL if cap = 0) receives
  * up to cap rows of {kern, ty, pd, cz, fuse, sg, milliseconds per factor of nsys systems} (for
  * shapes out of reach an estimate from their middle launches); *count (may be NULL) the number
  * of shapes timed.  Uses the context's workspace (2 nsys vectors of the precision); the

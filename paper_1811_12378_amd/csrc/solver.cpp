@@ -534,7 +534,7 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
   HFCI_HIP(hipEventCreateWithFlags(&e0, hipEventDisableSystemFence));
   HFCI_HIP(hipEventCreateWithFlags(&e1, hipEventDisableSystemFence));
   KernelTune best = saved;
-  double best_ms = 1e300, best_middle = 1e300;
+  double best_ms = 1e300, best_middle = 1e300, single_ratio = 1e300;
   timings.clear();
   try {
     bool groups = false;
@@ -547,6 +547,7 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
           if (sg <= nsys) cands.push_back(KernelTune{best.kern, best.ty, best.pd, best.cz, best.fuse, sg});
       }
       if (t.cz > 0 && t.cz >= op.g.nz) continue;  // same as one chunk per column: covered by cz = 0 or larger
+      if (t.fuse == 0 && t.cz > 0 && single_ratio >= 1.25) continue;  // single factors are out of reach
       cur = t;
       if (t.fuse == 2 && !Launch<T2>::triple_runs(op.g)) continue;  // (an odd nx: the pairs' shape covers it)
       // a step's launches: widths of the first, a middle and the last one, and how often the middle
@@ -586,6 +587,7 @@ KernelTune autotune_shapes(Op& op, int nsys, std::vector<std::pair<KernelTune, d
       // launches over nsys systems are slower by a quarter, an estimate from those
       const double middle = timed(w[1], 0, nsys), ratio = middle / w[1] / best_middle;
       double per = best_ms * ratio;
+      if (t.fuse == 0) single_ratio = std::min(single_ratio, ratio);
       if (ratio < 1.25) {
         double ms = 0.0, systems = 0.0;
         for (int c = 0; c < 3; ++c) {
