@@ -109,7 +109,7 @@ def traffic_kernel(t, triple=False):
     """Kernel-name key of the counter summary for the middle kernel at launch shape t."""
     kern, _, pd, _, fuse = t[:5]
     if fuse and kern <= 1:
-        return "zrows_kernel"
+        return "zrows_kernel<float, 0, "  # the launches without residual or y1, of any width
     if triple:
         return "ztrip_kernel"
     if fuse and kern == 3:
